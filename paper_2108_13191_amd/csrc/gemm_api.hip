@@ -118,6 +118,14 @@ bool aligned_for_tiled(int64_t N, int64_t K, const void* A, int64_t lda, const v
            lda <= MAX_TUNED_PITCH && ldb <= MAX_TUNED_PITCH && ldc <= MAX_TUNED_PITCH;
 }
 
+// The kernel behind ID_GENERIC for a problem: the tiled one for any alignment where its chunks of
+// 8 elements exist and its 32-bit tile offsets suffice, else the element-wise one.
+const GemmConfigDesc* any_shape_kernel(int64_t N, int64_t K, int64_t lda, int64_t ldb)
+{
+    const bool tiled = N >= 8 && K >= 8 && lda <= MAX_TUNED_PITCH && ldb <= MAX_TUNED_PITCH;
+    return tiled && !(g_forced >= 0 && g_forced < num_configs()) ? unaligned_config() : config(ID_GENERIC);
+}
+
 // What a call runs: one configuration on all rows, or the 256 x 256 kernel on
 // the first rows1 rows and configuration id2 on the rest (second launch on the
 // same stream; the row ranges of C are disjoint); k_split > 1: one launch whose
@@ -315,9 +323,9 @@ Plan select_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, i
     return pl;
 }
 
-void fill_desc(int id, int64_t grid, gemm_f16_config* out, int64_t split_rows = 0, int id2 = -1)
+void fill_desc(int id, int64_t grid, gemm_f16_config* out, int64_t split_rows = 0, int id2 = -1, const GemmConfigDesc* kernel = nullptr)
 {
-    const GemmConfigDesc* d = config(id);
+    const GemmConfigDesc* d = kernel ? kernel : config(id);
     memset(out, 0, sizeof(*out));
     out->id = id; out->block_m = d->block_m; out->block_n = d->block_n; out->block_k = d->block_k;
     out->waves = d->waves; out->wave_m = d->wave_m; out->wave_n = d->wave_n; out->lds_bytes = d->lds_bytes;
@@ -352,7 +360,8 @@ int run(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, int64_t ld
     a.A = (const half_t*)A; a.lda = lda; a.B = (const half_t*)B; a.ldb = ldb; a.C = C; a.ldc = ldc;
     a.c_is_f16 = c_is_f16; a.stream = (hipStream_t)stream;
     a.k_split = fused ? 0 : plan.k_split;                   // a fused epilogue has to follow the whole sum
-    const int rc1 = config(plan.id)->launch(a);
+    const GemmConfigDesc* first = plan.id == ID_GENERIC ? any_shape_kernel(N, K, lda, ldb) : config(plan.id);
+    const int rc1 = first->launch(a);
     if (rc1 != GEMM_F16_OK || plan.rows1 == M) return rc1;
     a.k_split = 0;
     a.M = M - plan.rows1;                                   // the left-over rows: A and C move down, B stays
@@ -480,7 +489,8 @@ int gemm_f16_query_config(int c_is_f16, int64_t M, int64_t N, int64_t K, const v
     if (rc != GEMM_F16_OK) return rc;
     const Plan plan = select_plan(c_is_f16, M, N, K, a, lda, b, ldb, ldc);
     if (M == 0 || N == 0 || K == 0) { fill_desc(plan.id, 0, out); return GEMM_F16_OK; }
-    int64_t g = config(plan.id)->grid(plan.rows1, N);
+    const GemmConfigDesc* first = plan.id == ID_GENERIC ? any_shape_kernel(N, K, lda, ldb) : config(plan.id);
+    int64_t g = first->grid(plan.rows1, N);
     if (g < 0) return GEMM_F16_ERR_SIZE;
     if (plan.rows1 < M) {
         const int64_t g2 = config(plan.id2)->grid(M - plan.rows1, N);
@@ -488,7 +498,7 @@ int gemm_f16_query_config(int c_is_f16, int64_t M, int64_t N, int64_t K, const v
         g += g2;
     }
     if (plan.k_split > 1) g *= plan.k_split;               // one workgroup per tile and part of the k loop
-    fill_desc(plan.id, g, out, plan.rows1 < M ? plan.rows1 : 0, plan.rows1 < M ? plan.id2 : -1);
+    fill_desc(plan.id, g, out, plan.rows1 < M ? plan.rows1 : 0, plan.rows1 < M ? plan.id2 : -1, first);
     return GEMM_F16_OK;
 }
 

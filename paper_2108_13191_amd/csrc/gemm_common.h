@@ -52,6 +52,9 @@ const ChipShape& chip();                     // gemm_api.hip
 int launch_generic(const GemmArgs& a);
 int64_t grid_generic(int64_t M, int64_t N);
 
+// gemm_unaligned.hip: 128 x 128 tiles at any alignment (N, K >= 8)
+const GemmConfigDesc* unaligned_config();
+
 // gemm_tiled.hip: the plain ring-buffered tiling, 64 x 64 (ladder builds also 128 x 128 and 256 x 256)
 const GemmConfigDesc* tiled_config(int block);
 

@@ -2,8 +2,9 @@
 // element access, so nothing outside the M x K, K x N and M x N extents is
 // touched and the k tail is zero-filled in both operands.  It follows the
 // two-level recipe of the paper's Algorithm "Two-level tiled tensor core
-// Matmul" in its plainest form (one LDS buffer, two barriers per step); the
-// tuned kernels live in gemm_tiled.hip.
+// Matmul" in its plainest form (one LDS buffer, two barriers per step).  It is
+// what is left for N or K below 8 and pitches above 2^22 elements; other
+// unaligned problems take gemm_unaligned.hip.
 #include "gemm_common.h"
 #include "../../include/gemm_f16.h"
 
