@@ -72,7 +72,7 @@ enum {
  * sum is exactly representable, and within the f32 rounding bound otherwise.
  *
  * Skinny problems (at most half as many 128 x 128 tiles as compute units, K >=
- * 2048, M*N small) run with the k loop cut into parts: C is not read, every
+ * 2048, M*N small) may run with the k loop cut into parts: C is not read, every
  * part adds its sum to the C in memory with hardware f32 atomic additions
  * (C0 + part + part + ...; a part that is exactly zero adds nothing, so a C
  * that gets no contribution keeps its bits).  Their order is not fixed, so that two runs may
@@ -147,7 +147,8 @@ int gemm_f16_f16acc_bias_act(int64_t M, int64_t N, int64_t K,
  * 15 against 49; problems of more than 2^20 results run unsplit).
  * gemm_f16_f16acc_workspace_bytes returns the bytes that make a difference
  * for a problem (0: it would run as gemm_f16_f16acc anyway; sizes only, for
- * 16-byte aligned operands with dense rows).  workspace: device memory,
+ * 16-byte aligned operands with dense rows; with them in hand the call still
+ * runs in one launch where that is faster: (16,2048,2048) 5 us).  workspace: device memory,
  * 16-byte aligned (else GEMM_F16_ERR_ALIGN), owned by the caller, used only
  * between the call and the completion of its work on the stream, contents
  * undefined afterwards; NULL or too small: the call runs unsplit.  Two calls
@@ -203,7 +204,7 @@ typedef struct gemm_f16_config {
     int32_t block_m;     /* workgroup tile rows */
     int32_t block_n;     /* workgroup tile columns */
     int32_t block_k;     /* k extent staged in LDS per main-loop step */
-    int32_t waves;       /* 64-lane wavefronts per workgroup */
+    int32_t waves;       /* 64-lane wavefronts per workgroup (of one k group, where several groups take the k steps in turn: names ending in _k8) */
     int32_t wave_m;      /* wavefront tile rows */
     int32_t wave_n;      /* wavefront tile columns */
     int32_t lds_bytes;   /* LDS bytes per workgroup */
@@ -232,7 +233,7 @@ int gemm_f16_describe_config(int id, gemm_f16_config* out);
  * Benchmarking aid: force configuration `id` for every later call of this
  * process (id < 0 restores automatic selection).  A forced configuration whose
  * alignment or pitch requirements the call does not meet is ignored for that
- * call.  The launch forms made for several tiles per compute unit (names
+ * call (the _k8 configurations have no alignment requirement).  The launch forms made for several tiles per compute unit (names
  * ending in _chain and _stag) run the plain 256 x 256 tiling on problems with
  * too few tiles for them (and _stag on devices other than 256 compute units);
  * with a k tail (K not a multiple of 64) a forced _chain still runs chained,

@@ -9,8 +9,8 @@ namespace {
 
 // Configuration table.  The product library holds the any-shape kernel, the phase-alternating
 // eight-wavefront kernel (16x16x32 MFMA) in its five tile shapes and its two launch forms for
-// several tiles per compute unit (chained, staggered), and the plain ring-buffered 64 x 64 tiling
-// for the smallest problems.  A ladder build (GEMM_F16_LADDER, libgemm_f16_ladder.so) appends
+// several tiles per compute unit (chained, staggered), the two kernels with an assembly k loop, the
+// small tiles for small results, and the plain ring-buffered 64 x 64 tiling between them.  A ladder build (GEMM_F16_LADDER, libgemm_f16_ladder.so) appends
 // the comparison kernels and ablation rows behind them; the selector never picks those.
 enum {
     ID_GENERIC = 0,
@@ -24,7 +24,9 @@ enum {
     ID_T64,            // 64 x 64, four LDS stages
     ID_LONG_K,         // 256 x 256, four wavefronts of 128 x 128, k loop in assembly
     ID_RING128,        // 128 x 128, four wavefronts of 64 x 64, k loop in assembly over five LDS stages
-    NUM_PRODUCT
+    ID_KSLICE,         // + 0 .. 4: 16 x 32, 32 x 32, 16 x 64, 32 x 64, 64 x 64, eight wavefronts take the k steps in turn
+    NUM_KSLICE = 5,
+    NUM_PRODUCT = ID_KSLICE + NUM_KSLICE
 };
 
 const GemmConfigDesc kGeneric = {
@@ -52,6 +54,7 @@ const GemmConfigDesc* config(int id)
     case ID_T64:       return tiled_config(64);
     case ID_LONG_K:    return long_k_config();
     case ID_RING128:   return deep_ring_config();
+    case ID_KSLICE + 0: case ID_KSLICE + 1: case ID_KSLICE + 2: case ID_KSLICE + 3: case ID_KSLICE + 4: return kslice_config(id - ID_KSLICE, false);
 #ifdef GEMM_F16_LADDER
     case NUM_PRODUCT + 0: return tiled_config(128);
     case NUM_PRODUCT + 1: return tiled_config(256);
@@ -118,12 +121,61 @@ bool aligned_for_tiled(int64_t N, int64_t K, const void* A, int64_t lda, const v
            lda <= MAX_TUNED_PITCH && ldb <= MAX_TUNED_PITCH && ldc <= MAX_TUNED_PITCH;
 }
 
-// The kernel behind ID_GENERIC for a problem: the tiled one for any alignment where its chunks of
-// 8 elements exist and its 32-bit tile offsets suffice, else the element-wise one.
-const GemmConfigDesc* any_shape_kernel(int64_t N, int64_t K, int64_t lda, int64_t ldb)
+// Small results: the kernel whose eight wavefronts take the k steps of one small tile in turn
+// (gemm_kslice.hip).  Estimated microseconds of a launch: 1.6 for the launch itself, and per round of
+// workgroups a fixed part (first loads, the sums' way through LDS, C) and one per 1024 k; the second
+// pair is a round of two workgroups a compute unit.  Fitted to launches in a row on three sets of operands, us:
+// (256,256,1024) 16x32 4.0, 32x32 4.5, 64x64 7.2; (512,512,1024) 5.9, 4.9, 7.4; (1024,1024,1024) 18.5,
+// 11.6, 8.7; (1024,2048,2048) 64x64 (two rounds) 21.9.  Operands without 16-byte alignment: the loads
+// take up to twice as long ((1001,1003,2003) 64x64 17 us against 11.7 aligned).  Operands
+// beyond what the last-level cache keeps between calls: strips of B 64 or 128 bytes wide come out of
+// the memory at 2.7 TB/s ((128,8192,8192) 64x64 49 us, its k loop from the caches 30).
+struct KsliceCand { int per_cu; double fixed1, rate1, fixed2, rate2; };
+const KsliceCand kKsliceCands[NUM_KSLICE] = {
+    {2, 1.65, 1.2, 2.0, 2.2}, {2, 1.75, 1.6, 2.0, 2.95}, {2, 1.9, 1.7, 2.2, 3.5}, {1, 2.2, 2.2, 2.2, 2.2}, {1, 3.4, 3.2, 3.4, 3.2}};
+
+double operand_mb(int64_t M, int64_t N, int64_t K) { return 2e-6 * (double)K * ((double)M + (double)N); }
+
+double kslice_us(int index, bool aligned, int64_t M, int64_t N, int64_t K)
 {
-    const bool tiled = N >= 8 && K >= 8 && lda <= MAX_TUNED_PITCH && ldb <= MAX_TUNED_PITCH;
-    return tiled && !(g_forced >= 0 && g_forced < num_configs()) ? unaligned_config() : config(ID_GENERIC);
+    const KsliceCand& c = kKsliceCands[index];
+    const int64_t g = kslice_config(index, false)->grid(M, N);
+    if (g < 0) return -1.0;
+    const int64_t cus = chip().cus, full = g / (cus * c.per_cu), left = g % (cus * c.per_cu);
+    const double k = (double)K / 1024.0 * (aligned ? 1.0 : 1.75), f = aligned ? 1.0 : 1.15, mb = operand_mb(M, N, K);
+    const double round1 = f * c.fixed1 + k * c.rate1, round2 = f * c.fixed2 + k * c.rate2;
+    return 1.6 + (double)full * round2 + (left == 0 ? 0.0 : left <= cus ? round1 : round2) + (mb > 80.0 ? 0.19 * mb : 0.0);
+}
+
+// The tile with the least estimated time among those with at most max_grid workgroups (-1: none).
+int best_kslice(bool aligned, int64_t M, int64_t N, int64_t K, int64_t max_grid, double* us)
+{
+    int best = -1;
+    for (int i = 0; i < NUM_KSLICE; i++) {
+        const int64_t g = kslice_config(i, false)->grid(M, N);
+        const double t = kslice_us(i, aligned, M, N, K);
+        if (g < 0 || g > max_grid || t < 0) continue;
+        if (best < 0 || t < *us) { best = i; *us = t; }
+    }
+    return best;
+}
+
+// The kernel behind ID_GENERIC for a problem: where chunks of 8 elements exist and 32-bit tile
+// offsets suffice, the tiled one for any alignment or, on problems of at most one of its tiles per
+// compute unit, the small tiles if they are estimated to be faster than its 12 + 11 us per 1024 k (2 more on a full
+// chip) -- measured, 128 x 128 -> best small tile, us: 513 x 511 x 509 18.7 -> 6.3, 1001 x 1003 x 1005 24.2 -> 12.0,
+// (16,8191,8191) 126 -> 37, (1501,1499,503) 19.8 against 20.4, (2001,1999,255) 16.9 against 22.6; else the
+// element-wise one.
+const GemmConfigDesc* any_shape_kernel(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb)
+{
+    const bool tiled = M <= INT32_MAX - 128 && N >= 8 && K >= 8 && lda <= MAX_TUNED_PITCH && ldb <= MAX_TUNED_PITCH;   // (row numbers of a whole tile in 31 bits)
+    if (tiled && g_forced >= ID_KSLICE && g_forced < ID_KSLICE + NUM_KSLICE) return kslice_config(g_forced - ID_KSLICE, true);
+    if (!tiled || (g_forced >= 0 && g_forced < num_configs())) return config(ID_GENERIC);
+    const int64_t tiles = unaligned_config()->grid(M, N), cus = chip().cus;
+    if (tiles < 0 || tiles > cus) return unaligned_config();
+    double us = 0;
+    const int small = best_kslice(false, M, N, K, INT32_MAX, &us);
+    return small >= 0 && us < (2 * tiles > cus ? 14.0 : 12.0) + 11.0 * (double)K / 1024.0 ? kslice_config(small, true) : unaligned_config();
 }
 
 // What a call runs: one configuration on all rows, or the 256 x 256 kernel on
@@ -311,15 +363,80 @@ int k_split_if_it_pays(int& id, int c_is_f16, int64_t M, int64_t N, int64_t K)
     return (int)parts;
 }
 
-Plan select_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, int64_t ldc)
+// What select_plan knows beyond the sizes: the plain entry points' plans are also those that
+// gemm_f16_query_config reports; a fused epilogue or the workspace form change what can run.
+enum class Form { plain, fused, workspace };
+
+// Estimated microseconds (as kslice_us) of a plan on at most one 128 x 128 tile per compute unit, from
+// launches in a row, us: phase-alternating kernel (1024,2048,K) 14.3 / 22.4 at K = 1024 / 2048; five-stage
+// kernel 30.0 at 4096; its split form (512,512,4096) 14.4, (1024,1024,4096) 26.3 (the additions).
+double other_us(const Plan& pl, int64_t M, int64_t N, int64_t K)
+{
+    const double k = (double)K / 1024.0, mb = operand_mb(M, N, K), memory = mb > 80.0 ? 0.08 * mb : 0.0;
+    if (pl.k_split > 1) {
+        const int64_t steps = (K + 63) / 64, per_part = (steps + pl.k_split - 1) / pl.k_split;
+        return 5.0 + 0.38 * (double)per_part + 3.7e-6 * (double)M * (double)N * pl.k_split + memory;
+    }
+    if (pl.id == ID_RING128) return 9.0 + 5.1 * k + memory;
+    return 6.2 + 7.8 * k + memory;
+}
+
+// Small results go to the small tiles where the estimates say so.  Before -> after, us:
+// 256^3 6.6 -> 3.4, 512^3 7.9 -> 4.1, 1024^3 f16 13.5 -> 8.4, (128,4096,1024) 11.2 -> 6.5, (16,8192,8192)
+// f16 50 -> 37, (8192,16,8192) f16 52 -> 29, (512,1024,4096) f16 30 -> 13.4.
+// Two limits from K = 2048 on.  In f32 mode a skinny problem (a dimension of C more than four times the
+// other) that is cut along k stays so, and others leave the split k loop for a gain of a tenth or
+// more.  In f16 mode a skinny problem, or one with K > 6144, runs on no more workgroups than it has
+// 64 x 64 tiles (the bound of its unsplit plans) -- unless at most 32 rows meet a B of 64 MB and
+// more, which half as many compute units do not read as fast ((16,8192,8192) 37 us on 256, 42 on 128).
+int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_t N, int64_t K)
+{
+    const int64_t tiles = config(ID_PP128x128)->grid(M, N);
+    if (tiles < 0 || tiles > chip().cus) return -1;
+    const bool skinny = M > 4 * N || N > 4 * M;
+    int64_t max_grid = INT32_MAX;
+    double other = other_us(pl, M, N, K);
+    if (form == Form::plain && K >= 2048) {
+        if (pl.k_split > 1) {
+            if (skinny) return -1;
+            other *= 0.9;
+        }
+        if (c_is_f16 && (skinny || K > 6144) && !(M <= 32 && N * K >= (int64_t)1 << 25)) max_grid = config(ID_T64)->grid(M, N);
+    }
+    if (form == Form::workspace && pl.k_split > 1) other += 5.0;     // the passes before and after
+    double us = 0;
+    const int small = best_kslice(true, M, N, K, max_grid, &us);
+    return small >= 0 && us < other ? ID_KSLICE + small : -1;
+}
+
+// The plan on the kernels of 64 x 64 tiles and more.
+Plan select_large_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, int64_t ldc, Form form)
 {
     Plan pl = select_plan_unchained(c_is_f16, M, N, K, A, lda, B, ldb, ldc);
-    if (g_forced >= 0 && g_forced < num_configs()) return pl;        // a forced configuration runs as it is
+    if ((g_forced >= 0 && g_forced < num_configs()) || pl.id == ID_GENERIC) return pl;        // a forced configuration runs as it is
     pl.id = long_k_if_it_pays(chained_if_it_pays(pl.id, pl.rows1, N, K), c_is_f16, pl.rows1, N, K);
     pl.id = deep_ring_if_it_pays(pl.id, pl.rows1, N, K);
     if (pl.id2 >= 0) pl.id2 = long_k_if_it_pays(chained_if_it_pays(pl.id2, M - pl.rows1, N, K), c_is_f16, M - pl.rows1, N, K);
     if (pl.id2 >= 0) pl.id2 = deep_ring_if_it_pays(pl.id2, M - pl.rows1, N, K);
-    if (pl.id2 < 0 && pl.rows1 == M) pl.k_split = k_split_if_it_pays(pl.id, c_is_f16, M, N, K);
+    if (pl.id2 >= 0 || pl.rows1 != M) return pl;
+    if (form == Form::workspace) {
+        // the rule of the f32 mode; the two passes over the workspace: (1024,2048,8192), 8 MB, 56 us against 53 unsplit; (256,4096,16384), 4 MB, 52 against 97
+        int id = pl.id;
+        const int parts = M * N <= 1048576 ? k_split_if_it_pays(id, 0, M, N, K) : 0;
+        if (parts > 1) { pl.id = id; pl.k_split = parts; }
+    } else {
+        pl.k_split = k_split_if_it_pays(pl.id, c_is_f16, M, N, K);
+        if (form == Form::fused) pl.k_split = 0;                 // a fused epilogue has to follow the whole sum
+    }
+    return pl;
+}
+
+Plan select_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, int64_t ldc, Form form)
+{
+    Plan pl = select_large_plan(c_is_f16, M, N, K, A, lda, B, ldb, ldc, form);
+    if ((g_forced >= 0 && g_forced < num_configs()) || pl.id == ID_GENERIC || pl.id2 >= 0) return pl;
+    const int small = kslice_if_it_pays(pl, c_is_f16, form, M, N, K);
+    if (small >= 0) { pl.id = small; pl.k_split = 0; }
     return pl;
 }
 
@@ -337,7 +454,7 @@ void fill_desc(int id, int64_t grid, gemm_f16_config* out, int64_t split_rows = 
 
 int run(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
         const void* B, int64_t ldb, void* C, int64_t ldc, void* stream,
-        const void* bias = nullptr, int act = GEMM_F16_ACT_NONE)
+        const void* bias = nullptr, int act = GEMM_F16_ACT_NONE, Form form = Form::plain)
 {
     const int rc = check_args(c_is_f16, M, N, K, A, lda, B, ldb, C, ldc);
     if (rc != GEMM_F16_OK) return rc;
@@ -355,12 +472,12 @@ int run(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, int64_t ld
         a.c_is_f16 = c_is_f16; a.stream = (hipStream_t)stream;
         return config(ID_GENERIC)->launch(a);
     }
-    const Plan plan = select_plan(c_is_f16, M, N, K, A, lda, B, ldb, ldc);
+    const Plan plan = select_plan(c_is_f16, M, N, K, A, lda, B, ldb, ldc, fused ? Form::fused : form);
     a.M = plan.rows1; a.N = N; a.K = K;
     a.A = (const half_t*)A; a.lda = lda; a.B = (const half_t*)B; a.ldb = ldb; a.C = C; a.ldc = ldc;
     a.c_is_f16 = c_is_f16; a.stream = (hipStream_t)stream;
-    a.k_split = fused ? 0 : plan.k_split;                   // a fused epilogue has to follow the whole sum
-    const GemmConfigDesc* first = plan.id == ID_GENERIC ? any_shape_kernel(N, K, lda, ldb) : config(plan.id);
+    a.k_split = plan.k_split;
+    const GemmConfigDesc* first = plan.id == ID_GENERIC ? any_shape_kernel(M, N, K, lda, ldb) : config(plan.id);
     const int rc1 = first->launch(a);
     if (rc1 != GEMM_F16_OK || plan.rows1 == M) return rc1;
     a.k_split = 0;
@@ -370,17 +487,11 @@ int run(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, int64_t ld
     return config(plan.id2)->launch(a);
 }
 
-// Parts of a split k loop for the half-precision mode through a workspace (0: runs unsplit):
-// the rule of the f32 mode on the plan the f16 mode would take.
-int f16_workspace_parts(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, int64_t ldc)
+// The plan of the half-precision mode with M x N floats of scratch memory: k_split > 1, or it runs without them.
+Plan workspace_plan(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, int64_t ldc)
 {
-    if (M <= 0 || N <= 0 || K <= 0 || !aligned_for_tiled(N, K, A, lda, B, ldb, ldc) || (g_forced >= 0 && g_forced < num_configs())) return 0;
-    const Plan pl = select_plan(1, M, N, K, A, lda, B, ldb, ldc);
-    if (pl.id2 >= 0 || pl.rows1 != M) return 0;
-    // the two passes over the workspace: (1024,2048,8192), 8 MB, 56 us against 53 unsplit; (256,4096,16384), 4 MB, 52 against 97
-    if (M * N > 1048576) return 0;
-    int id = pl.id;
-    return k_split_if_it_pays(id, 0, M, N, K);
+    if (M <= 0 || N <= 0 || K <= 0) return {ID_GENERIC, M, -1};
+    return select_plan(1, M, N, K, A, lda, B, ldb, ldc, Form::workspace);
 }
 
 // The half-precision mode with `ws` (M x N floats, 16-byte aligned, all zero if ws_is_zero) as the
@@ -406,7 +517,7 @@ extern "C" {
 int64_t gemm_f16_f16acc_workspace_bytes(int64_t M, int64_t N, int64_t K)
 {
     if (M <= 0 || N <= 0 || K <= 0 || M > INT32_MAX || N > INT32_MAX || K > INT32_MAX) return 0;
-    return f16_workspace_parts(M, N, K, (const void*)16, K, (const void*)16, N, N) >= 2 ? M * N * 4 : 0;
+    return select_large_plan(1, M, N, K, (const void*)16, K, (const void*)16, N, N, Form::workspace).k_split > 1 ? M * N * 4 : 0;
 }
 
 int gemm_f16_f16acc_workspace(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
@@ -416,8 +527,9 @@ int gemm_f16_f16acc_workspace(int64_t M, int64_t N, int64_t K, const void* A, in
     const int rc = check_args(1, M, N, K, A, lda, B, ldb, C, ldc);
     if (rc != GEMM_F16_OK) return rc;
     if (workspace && ((uintptr_t)workspace & 15)) return GEMM_F16_ERR_ALIGN;
-    const int parts = f16_workspace_parts(M, N, K, A, lda, B, ldb, ldc);
-    if (parts < 2 || !workspace || workspace_bytes < M * N * 4) return run(1, M, N, K, A, lda, B, ldb, C, ldc, stream);
+    if (!workspace || workspace_bytes < M * N * 4) return run(1, M, N, K, A, lda, B, ldb, C, ldc, stream);
+    const int parts = workspace_plan(M, N, K, A, lda, B, ldb, ldc).k_split;
+    if (parts < 2) return run(1, M, N, K, A, lda, B, ldb, C, ldc, stream, nullptr, GEMM_F16_ACT_NONE, Form::workspace);
     return run_f16_split(parts, M, N, K, A, lda, B, ldb, C, ldc, (float*)workspace, false, false, stream);
 }
 
@@ -452,8 +564,8 @@ int gemm_f16_f16acc_static_workspace(int64_t M, int64_t N, int64_t K, const void
 {
     const int rc = check_args(1, M, N, K, A, lda, B, ldb, C, ldc);
     if (rc != GEMM_F16_OK) return rc;
-    const int parts = f16_workspace_parts(M, N, K, A, lda, B, ldb, ldc);
-    if (parts < 2) return run(1, M, N, K, A, lda, B, ldb, C, ldc, stream);      // no scratch memory involved
+    const int parts = workspace_plan(M, N, K, A, lda, B, ldb, ldc).k_split;
+    if (parts < 2) return run(1, M, N, K, A, lda, B, ldb, C, ldc, stream, nullptr, GEMM_F16_ACT_NONE, Form::workspace);      // no scratch memory involved
     float* ws = nullptr;
     int64_t floats = 0;
     const int rc2 = splitk_f16_static_scratch(&ws, &floats);
@@ -487,9 +599,9 @@ int gemm_f16_query_config(int c_is_f16, int64_t M, int64_t N, int64_t K, const v
     const void* c = C ? C : (const void*)16;
     const int rc = check_args(c_is_f16, M, N, K, a, lda, b, ldb, c, ldc);
     if (rc != GEMM_F16_OK) return rc;
-    const Plan plan = select_plan(c_is_f16, M, N, K, a, lda, b, ldb, ldc);
+    const Plan plan = select_plan(c_is_f16, M, N, K, a, lda, b, ldb, ldc, Form::plain);
     if (M == 0 || N == 0 || K == 0) { fill_desc(plan.id, 0, out); return GEMM_F16_OK; }
-    const GemmConfigDesc* first = plan.id == ID_GENERIC ? any_shape_kernel(N, K, lda, ldb) : config(plan.id);
+    const GemmConfigDesc* first = plan.id == ID_GENERIC ? any_shape_kernel(M, N, K, lda, ldb) : config(plan.id);
     int64_t g = first->grid(plan.rows1, N);
     if (g < 0) return GEMM_F16_ERR_SIZE;
     if (plan.rows1 < M) {

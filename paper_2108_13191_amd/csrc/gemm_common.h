@@ -55,6 +55,10 @@ int64_t grid_generic(int64_t M, int64_t N);
 // gemm_unaligned.hip: 128 x 128 tiles at any alignment (N, K >= 8)
 const GemmConfigDesc* unaligned_config();
 
+// gemm_kslice.hip: eight wavefronts share a small tile of C and take its k steps in turn (any alignment, N, K >= 8)
+// index 0 .. 4: 16x32, 32x32, 16x64, 32x64, 64x64; any_shape: under the name that the any-shape family reports
+const GemmConfigDesc* kslice_config(int index, bool any_shape);
+
 // gemm_tiled.hip: the plain ring-buffered tiling, 64 x 64 (ladder builds also 128 x 128 and 256 x 256)
 const GemmConfigDesc* tiled_config(int block);
 
