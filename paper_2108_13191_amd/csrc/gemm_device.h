@@ -22,6 +22,18 @@ struct TiledParams {
     int k_split;           // five-stage 128 x 128 kernel: > 1 = workgroup b works on tile b % tiles, part b / tiles of the k loop, and adds to C atomically
 };
 
+// From this size on C is read and written with the non-temporal hint: it would push A and B out of the
+// caches and not be there at the next call itself, whose read then waits for the write-back.
+// Launches in a row on three sets of operands, without -> with, us: (16384,2304,768) f32 (151 MB) 97.5 -> 84.3,
+// (16384,3072,768) f32 (201 MB) 129.6 -> 116.7, f16 (101 MB) 101.6 -> 92.9, (8192,8192,1024) f32
+// (268 MB) 202 -> 171, f16 (134 MB) 160 -> 143, (6000,6000,1000) f32 (144 MB) 125 -> 117; below the line C
+// often survives in the 256 MB last-level cache: (4096,4096,1024) f32 (67 MB) 45.1 -> 49.9, (5528,3480,1880)
+// f32 (77 MB) 97 -> 100, (1332,13440,1344) f32 (72 MB) 71.5 -> 68.6.  (One C used again and again, which
+// survives up to about 200 MB: (16384,2304,768) f32 79.6 -> 84.7, (8192,8192,1024) f16 139 -> 144.)
+// Not from K = 4096 on, where the traffic of C is a small part: 8192^3 f32 795 -> 798.
+constexpr double C_ONCE_BYTES = 96e6;
+inline bool c_once(const GemmArgs& a) { return a.K < 4096 && (double)a.M * (double)a.N * (a.c_is_f16 ? 2 : 4) >= C_ONCE_BYTES; }
+
 // The fields every launcher fills the same way: the problem, the tile grid for bm x bn tiles,
 // and the tile order (group_m tile rows at a time; an XCD's 32 concurrent tiles should form a
 // near-square block of C).

@@ -116,6 +116,7 @@ __device__ __forceinline__ int b_chunk_position(int chunk, int krow)
 template <int BM, int BN>
 constexpr int pp_lds_bytes() { return 2 * (BM * BK * 2) + 3 * (BK * BN * 2); }     // 160 KB for 256 x 256
 
+// ONCE: C is read and written with the non-temporal hint (large C: C_ONCE_BYTES).
 // One BM x BN tile of C with its first row and column at (m0, n0), by the whole
 // workgroup; smem_base = LDS address of pp_lds_bytes<BM, BN>() bytes, 1 KB aligned.
 // PERSIST: afterwards the tiles next_tile, next_tile + tile_step, ... (indices as
@@ -124,7 +125,7 @@ constexpr int pp_lds_bytes() { return 2 * (BM * BK * 2) + 3 * (BK * BN * 2); }  
 // after it, so that a tile's first operands cross the memory system while C is
 // read and written; the epilogue's transposing buffers lie in the LDS that k step
 // 0 does not use.
-template <typename CT, int MI, bool TAIL, int BM, int BN, bool PERSIST = false, bool ROWWISE = false>
+template <typename CT, int MI, bool TAIL, int BM, int BN, bool PERSIST = false, bool ROWWISE = false, bool ONCE = false>
 __device__ __forceinline__ void pp_tile(const TiledParams& p, const uint32_t smem_base, int m0, int n0,
                                         int next_tile = 0, const int tile_step = 0)
 {
@@ -478,7 +479,8 @@ __device__ __forceinline__ void pp_tile(const TiledParams& p, const uint32_t sme
             const bool ok = col_ok && (!edge || (crow0 + fm * 32 + RPP * ps + orow < p.M));
             // a group outside C reads this lane's first (valid or clamped) group of the tile instead
             const CT* src = ok ? cptr + (int64_t)(fm * 32 + RPP * ps) * p.ldc : Cbase + (int64_t)cm0 * p.ldc + cn0;
-            dst[ps] = *reinterpret_cast<const ctx4*>(src);
+            if constexpr (ONCE) dst[ps] = __builtin_nontemporal_load(reinterpret_cast<const ctx4*>(src));
+            else                dst[ps] = *reinterpret_cast<const ctx4*>(src);
         }
     };
 #pragma unroll
@@ -538,8 +540,11 @@ __device__ __forceinline__ void pp_tile(const TiledParams& p, const uint32_t sme
                 ctx4 o;
 #pragma unroll
                 for (int e = 0; e < 4; e++) o[e] = (CT)epilogue_value(s4[e] + (float)c4[e], bias4[e], p.relu);      // f16: one rounding, to nearest even
-                if (col_ok && (!edge || (crow0 + fm * 32 + RPP * ps + orow < p.M)))
-                    *reinterpret_cast<ctx4*>(cptr + (int64_t)(fm * 32 + RPP * ps) * p.ldc) = o;
+                if (col_ok && (!edge || (crow0 + fm * 32 + RPP * ps + orow < p.M))) {
+                    ctx4* const dst = reinterpret_cast<ctx4*>(cptr + (int64_t)(fm * 32 + RPP * ps) * p.ldc);
+                    if constexpr (ONCE) __builtin_nontemporal_store(o, dst);
+                    else                *dst = o;
+                }
             }
         }
     }
@@ -586,27 +591,27 @@ inline int late_start_ticks()
 template <int BM, int BN>
 int pp_at_once() { return chip().cus * (pp_lds_bytes<BM, BN>() <= 80 * 1024 ? 2 : 1); }
 
-template <typename CT, int MI, bool TAIL, int BM, int BN, bool ROWWISE = false>
+template <typename CT, int MI, bool TAIL, int BM, int BN, bool ROWWISE = false, bool ONCE = false>
 __global__ __launch_bounds__(512) void gemm_pp256_kernel(const TiledParams p)
 {
     __shared__ __attribute__((aligned(1024))) char smem[pp_lds_bytes<BM, BN>()];
     late_start(p);
     int tile_m, tile_n;
     tile_of_block(p, blockIdx.x, tile_m, tile_n);
-    pp_tile<CT, MI, TAIL, BM, BN, false, ROWWISE>(p, (uint32_t)(uintptr_t)(lds_ptr_t)smem, tile_m * BM, tile_n * BN);
+    pp_tile<CT, MI, TAIL, BM, BN, false, ROWWISE, ONCE>(p, (uint32_t)(uintptr_t)(lds_ptr_t)smem, tile_m * BM, tile_n * BN);
 }
 
 // One workgroup per compute unit walks the tiles blockIdx.x, blockIdx.x + gridDim.x,
 // ... (the same tiles, in the same order, that the hardware would hand that unit
 // when every tile is a workgroup of its own and all tiles take equally long).
-template <typename CT, int MI, bool TAIL>
+template <typename CT, int MI, bool TAIL, bool ONCE>
 __global__ __launch_bounds__(512) void gemm_pp256_persistent_kernel(const TiledParams p)
 {
     __shared__ __attribute__((aligned(1024))) char smem[pp_lds_bytes<256, 256>()];
     late_start(p);
     int tile_m, tile_n;
     tile_of_block(p, blockIdx.x, tile_m, tile_n);
-    pp_tile<CT, MI, TAIL, 256, 256, true>(p, (uint32_t)(uintptr_t)(lds_ptr_t)smem, tile_m * 256, tile_n * 256,
+    pp_tile<CT, MI, TAIL, 256, 256, true, false, ONCE>(p, (uint32_t)(uintptr_t)(lds_ptr_t)smem, tile_m * 256, tile_n * 256,
                                           (int)(blockIdx.x + gridDim.x), (int)gridDim.x);
 }
 
@@ -619,7 +624,7 @@ __global__ __launch_bounds__(512) void gemm_pp256_persistent_kernel(const TiledP
 // short-K problems saturates HBM when all units do it at once -- while the other
 // half multiplies.  Results do not depend on where workgroups actually land.
 constexpr int MIXED_HALVES = 128;
-template <typename CT, int MI, bool TAIL>
+template <typename CT, int MI, bool TAIL, bool ONCE>
 __global__ __launch_bounds__(512) void gemm_pp_mixed_kernel(const TiledParams p)
 {
     __shared__ __attribute__((aligned(1024))) char smem[pp_lds_bytes<256, 256>()];
@@ -631,10 +636,10 @@ __global__ __launch_bounds__(512) void gemm_pp_mixed_kernel(const TiledParams p)
     int tile_m, tile_n;
     tile_of_block(p, b, tile_m, tile_n);
     if (half < 0) {
-        pp_tile<CT, MI, TAIL, 256, 256>(p, smem_base, tile_m * 256, tile_n * 256);
+        pp_tile<CT, MI, TAIL, 256, 256, false, false, ONCE>(p, smem_base, tile_m * 256, tile_n * 256);
     } else {
         const int m0 = tile_m * 256 + 128 * half;
-        if (m0 < p.M) pp_tile<CT, MI, TAIL, 128, 256>(p, smem_base, m0, tile_n * 256);
+        if (m0 < p.M) pp_tile<CT, MI, TAIL, 128, 256, false, false, ONCE>(p, smem_base, m0, tile_n * 256);
     }
 }
 
@@ -645,6 +650,19 @@ int64_t grid_pp(int64_t M, int64_t N)
     if (tm > 0 && tn > INT32_MAX / tm) return -1;
     return tm * tn;
 }
+
+// The instantiation for the type of C, a k tail and a large C: LAUNCH(CT, TAIL, ONCE)
+#define PP_DISPATCH(a, LAUNCH)                                                                                       \
+    do {                                                                                                             \
+        const bool tail = (a).K % BK != 0, once = c_once(a);                                                         \
+        if ((a).c_is_f16) {                                                                                          \
+            if (once) { if (tail) { LAUNCH(half_t, true, true); } else { LAUNCH(half_t, false, true); } }            \
+            else      { if (tail) { LAUNCH(half_t, true, false); } else { LAUNCH(half_t, false, false); } }          \
+        } else {                                                                                                     \
+            if (once) { if (tail) { LAUNCH(float, true, true); } else { LAUNCH(float, false, true); } }              \
+            else      { if (tail) { LAUNCH(float, true, false); } else { LAUNCH(float, false, false); } }            \
+        }                                                                                                            \
+    } while (0)
 
 template <int MI, int BM, int BN>
 int launch_pp(const GemmArgs& a, bool xcd_order = true)
@@ -657,14 +675,9 @@ int launch_pp(const GemmArgs& a, bool xcd_order = true)
     // (measured +4 ... +9 % on every tile form; at three rounds of the 128 x 128 form the delay costs more than it gains)
     p.first_generation = pp_at_once<BM, BN>();
     p.stagger_ticks = (a.K <= 2048 && g >= 4 * (int64_t)p.first_generation) ? late_start_ticks() : 0;
-    const bool tail = (a.K % BK) != 0;
-    if (a.c_is_f16) {
-        if (tail) hipLaunchKernelGGL((gemm_pp256_kernel<half_t, MI, true, BM, BN>), dim3((unsigned)g), dim3(512), 0, a.stream, p);
-        else      hipLaunchKernelGGL((gemm_pp256_kernel<half_t, MI, false, BM, BN>), dim3((unsigned)g), dim3(512), 0, a.stream, p);
-    } else {
-        if (tail) hipLaunchKernelGGL((gemm_pp256_kernel<float, MI, true, BM, BN>), dim3((unsigned)g), dim3(512), 0, a.stream, p);
-        else      hipLaunchKernelGGL((gemm_pp256_kernel<float, MI, false, BM, BN>), dim3((unsigned)g), dim3(512), 0, a.stream, p);
-    }
+#define PP_LAUNCH(CT, TAIL, ONCE) hipLaunchKernelGGL((gemm_pp256_kernel<CT, MI, TAIL, BM, BN, false, ONCE>), dim3((unsigned)g), dim3(512), 0, a.stream, p)
+    PP_DISPATCH(a, PP_LAUNCH);
+#undef PP_LAUNCH
     return hipGetLastError() == hipSuccess ? GEMM_F16_OK : GEMM_F16_ERR_LAUNCH;
 }
 template <int MI, int BM, int BN> int launch_pp_plain(const GemmArgs& a) { return launch_pp<MI, BM, BN>(a); }
@@ -688,14 +701,9 @@ int launch_pp_mixed(const GemmArgs& a)
     const int64_t g = tiles + MIXED_HALVES;
     TiledParams p = make_tiled_params(a, 256, 256, 8);
     p.first_generation = chip().cus;
-    const bool tail = (a.K % BK) != 0;
-    if (a.c_is_f16) {
-        if (tail) hipLaunchKernelGGL((gemm_pp_mixed_kernel<half_t, 16, true>), dim3((unsigned)g), dim3(512), 0, a.stream, p);
-        else      hipLaunchKernelGGL((gemm_pp_mixed_kernel<half_t, 16, false>), dim3((unsigned)g), dim3(512), 0, a.stream, p);
-    } else {
-        if (tail) hipLaunchKernelGGL((gemm_pp_mixed_kernel<float, 16, true>), dim3((unsigned)g), dim3(512), 0, a.stream, p);
-        else      hipLaunchKernelGGL((gemm_pp_mixed_kernel<float, 16, false>), dim3((unsigned)g), dim3(512), 0, a.stream, p);
-    }
+#define PP_LAUNCH(CT, TAIL, ONCE) hipLaunchKernelGGL((gemm_pp_mixed_kernel<CT, 16, TAIL, ONCE>), dim3((unsigned)g), dim3(512), 0, a.stream, p)
+    PP_DISPATCH(a, PP_LAUNCH);
+#undef PP_LAUNCH
     return hipGetLastError() == hipSuccess ? GEMM_F16_OK : GEMM_F16_ERR_LAUNCH;
 }
 
@@ -714,14 +722,9 @@ int launch_pp_persistent(const GemmArgs& a)
     TiledParams p = make_tiled_params(a, 256, 256, 8);
     p.first_generation = (int)g;
     p.stagger_ticks = (a.K <= 2048 && tiles >= 3 * (int64_t)g) ? late_start_ticks() : 0;
-    const bool tail = (a.K % BK) != 0;
-    if (a.c_is_f16) {
-        if (tail) hipLaunchKernelGGL((gemm_pp256_persistent_kernel<half_t, 16, true>), dim3(g), dim3(512), 0, a.stream, p);
-        else      hipLaunchKernelGGL((gemm_pp256_persistent_kernel<half_t, 16, false>), dim3(g), dim3(512), 0, a.stream, p);
-    } else {
-        if (tail) hipLaunchKernelGGL((gemm_pp256_persistent_kernel<float, 16, true>), dim3(g), dim3(512), 0, a.stream, p);
-        else      hipLaunchKernelGGL((gemm_pp256_persistent_kernel<float, 16, false>), dim3(g), dim3(512), 0, a.stream, p);
-    }
+#define PP_LAUNCH(CT, TAIL, ONCE) hipLaunchKernelGGL((gemm_pp256_persistent_kernel<CT, 16, TAIL, ONCE>), dim3(g), dim3(512), 0, a.stream, p)
+    PP_DISPATCH(a, PP_LAUNCH);
+#undef PP_LAUNCH
     return hipGetLastError() == hipSuccess ? GEMM_F16_OK : GEMM_F16_ERR_LAUNCH;
 }
 
