@@ -30,9 +30,14 @@ struct TiledParams {
 // often survives in the 256 MB last-level cache: (4096,4096,1024) f32 (67 MB) 45.1 -> 49.9, (5528,3480,1880)
 // f32 (77 MB) 97 -> 100, (1332,13440,1344) f32 (72 MB) 71.5 -> 68.6.  (One C used again and again, which
 // survives up to about 200 MB: (16384,2304,768) f32 79.6 -> 84.7, (8192,8192,1024) f16 139 -> 144.)
-// Not from K = 4096 on, where the traffic of C is a small part: 8192^3 f32 795 -> 798.
+// Not from K = 4096 on, where the traffic of C is a small part (8192^3 f32 795 -> 798), and not
+// where rows of C begin within a 64-byte sector: (14910,2968,256) f32 at a pitch of 3032 91 -> 102.
 constexpr double C_ONCE_BYTES = 96e6;
-inline bool c_once(const GemmArgs& a) { return a.K < 4096 && (double)a.M * (double)a.N * (a.c_is_f16 ? 2 : 4) >= C_ONCE_BYTES; }
+inline bool c_once(const GemmArgs& a)
+{
+    const int64_t size = a.c_is_f16 ? 2 : 4;
+    return a.K < 4096 && (double)a.M * (double)a.N * (double)size >= C_ONCE_BYTES && a.ldc * size % 64 == 0 && (uintptr_t)a.C % 64 == 0;
+}
 
 // The fields every launcher fills the same way: the problem, the tile grid for bm x bn tiles,
 // and the tile order (group_m tile rows at a time; an XCD's 32 concurrent tiles should form a

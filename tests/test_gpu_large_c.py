@@ -1,6 +1,6 @@
 """The forms of the phase-alternating kernel that read and write a large C (96 MB and more, K < 4096) with the
 non-temporal hint: every tile form, with and without a k tail, ragged edges, just above and just
-below the size.  Integers bit for bit against the oracle on sampled rows."""
+below the size, rows of C that begin at 64-byte sectors and that do not.  Integers bit for bit against the oracle on sampled rows."""
 import numpy as np
 import pytest
 
@@ -28,12 +28,13 @@ def _unforce():
 @pytest.mark.parametrize("mode", ["f32", "f16"])
 def test_large_c(oracle_mod, name, mode):
     binding.force_config(config_id(name))
-    for M, N, K in ((5861, 4104, 128), (5861, 4104, 72), (5841, 4104, 64)):        # f32: 96.2 MB twice, then 95.9
+    # 96.2 MB three times, then 95.9
+    for M, N, K, pad in ((5861, 4104, 128, 24), (5861, 4104, 72, 24), (5861, 4104, 72, 0), (5841, 4104, 64, 24)):
         if mode == "f16":
             M *= 2
         A, B, _ = wl.make_inputs(M, N, K, "int2", "zeros", seed=K)
         C0 = ((np.arange(M)[:, None] + np.arange(N)[None, :]) % 9 - 4).astype(CDT[mode])
-        got = run_gemm(A, B, C0, mode)
+        got = run_gemm(A, B, C0, mode, ldc=N + pad)
         rows = np.unique(np.concatenate([[0, 1, 127, 128, 255, 256, M - 257, M - 2, M - 1], np.random.default_rng(K).integers(0, M, 40)]))
         Cref, _ = oracle_mod.gemm_f16(A, B, C0, rows=rows)
         want = oracle_mod.round_to_f32(Cref) if mode == "f32" else Cref.astype(np.float16)
