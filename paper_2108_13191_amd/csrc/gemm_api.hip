@@ -130,30 +130,33 @@ bool aligned_for_tiled(int64_t N, int64_t K, const void* A, int64_t lda, const v
 // take up to twice as long ((1001,1003,2003) 64x64 17 us against 11.7 aligned).  Operands
 // beyond what the last-level cache keeps between calls: strips of B 64 or 128 bytes wide come out of
 // the memory at 2.7 TB/s ((128,8192,8192) 64x64 49 us, its k loop from the caches 30).
+// Rows that begin within a 128-byte line: (1024,1024,2048) 64x64 11.9 us at pitches of 64 elements' multiples, 14.9 at others.
+enum class Operands { lines, chunks, any };              // rows begin at 128-byte lines; at 16 bytes; anywhere
+Operands operands_of(int64_t lda, int64_t ldb) { return lda % 64 || ldb % 64 ? Operands::chunks : Operands::lines; }
 struct KsliceCand { int per_cu; double fixed1, rate1, fixed2, rate2; };
 const KsliceCand kKsliceCands[NUM_KSLICE] = {
     {2, 1.65, 1.2, 2.0, 2.2}, {2, 1.75, 1.6, 2.0, 2.95}, {2, 1.9, 1.7, 2.2, 3.5}, {1, 2.2, 2.2, 2.2, 2.2}, {1, 3.4, 3.2, 3.4, 3.2}};
 
 double operand_mb(int64_t M, int64_t N, int64_t K) { return 2e-6 * (double)K * ((double)M + (double)N); }
 
-double kslice_us(int index, bool aligned, int64_t M, int64_t N, int64_t K)
+double kslice_us(int index, Operands form, int64_t M, int64_t N, int64_t K)
 {
     const KsliceCand& c = kKsliceCands[index];
     const int64_t g = kslice_config(index, false)->grid(M, N);
     if (g < 0) return -1.0;
     const int64_t cus = chip().cus, full = g / (cus * c.per_cu), left = g % (cus * c.per_cu);
-    const double k = (double)K / 1024.0 * (aligned ? 1.0 : 1.75), f = aligned ? 1.0 : 1.15, mb = operand_mb(M, N, K);
+    const double k = (double)K / 1024.0 * (form == Operands::lines ? 1.0 : form == Operands::chunks ? 1.25 : 1.75), f = form == Operands::any ? 1.15 : 1.0, mb = operand_mb(M, N, K);
     const double round1 = f * c.fixed1 + k * c.rate1, round2 = f * c.fixed2 + k * c.rate2;
     return 1.6 + (double)full * round2 + (left == 0 ? 0.0 : left <= cus ? round1 : round2) + (mb > 80.0 ? 0.19 * mb : 0.0);
 }
 
 // The tile with the least estimated time among those with at most max_grid workgroups (-1: none).
-int best_kslice(bool aligned, int64_t M, int64_t N, int64_t K, int64_t max_grid, double* us)
+int best_kslice(Operands form, int64_t M, int64_t N, int64_t K, int64_t max_grid, double* us)
 {
     int best = -1;
     for (int i = 0; i < NUM_KSLICE; i++) {
         const int64_t g = kslice_config(i, false)->grid(M, N);
-        const double t = kslice_us(i, aligned, M, N, K);
+        const double t = kslice_us(i, form, M, N, K);
         if (g < 0 || g > max_grid || t < 0) continue;
         if (best < 0 || t < *us) { best = i; *us = t; }
     }
@@ -174,7 +177,7 @@ const GemmConfigDesc* any_shape_kernel(int64_t M, int64_t N, int64_t K, int64_t 
     const int64_t tiles = unaligned_config()->grid(M, N), cus = chip().cus;
     if (tiles < 0 || tiles > cus) return unaligned_config();
     double us = 0;
-    const int small = best_kslice(false, M, N, K, INT32_MAX, &us);
+    const int small = best_kslice(Operands::any, M, N, K, INT32_MAX, &us);
     return small >= 0 && us < (2 * tiles > cus ? 14.0 : 12.0) + 11.0 * (double)K / 1024.0 ? kslice_config(small, true) : unaligned_config();
 }
 
@@ -297,10 +300,19 @@ int long_k_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K)
 // 0.56, but its start costs 5 us more: 2048^2, K = 3072: -8 / -4 %, 4096: -3 / 0 %, 6144: -3 /
 // -0.5 %, 8192: +3 / +5 %; 1536^2 x 3072 -6 / -5 %; 256 x 7168^2 -3 %.  From K = 6144 on what
 // it gains on cached operands (+15 % and more) outweighs what it loses on cold ones.
-int deep_ring_if_it_pays(int id, int64_t rows, int64_t N, int64_t K)
+//
+// C read and stored by whole rows behind the loop has since made its start cheaper: phase-alternating kernel ->
+// this one, launches in a row on three sets of operands, us: 128 tiles, (1024,2048,K): K = 1024 14.7 ->
+// 13.1 (f16 13.9 -> 11.9), 4096 37.2 -> 27.8; 256 tiles, 2048^2 f16: K = 1024 16.3 -> 14.8, 2048 25.8 -> 21.7, 4096
+// 44.0 -> 35.5.  A k tail is an unpipelined step: (2000,2000,2000) f16 25.9 -> 26.6.  On a full chip the
+// f32 mode's choice stays at K = 6144 (C is twice the traffic; cold operands as above).
+int deep_ring_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K)
 {
-    if (id != ID_PP128x128) return id;
-    return (K >= 6144 && config(ID_RING128)->grid(rows, N) <= chip().cus) ? ID_RING128 : id;
+    const int64_t tiles = config(ID_RING128)->grid(rows, N), cus = chip().cus;
+    if (id != ID_PP128x128 || tiles > cus) return id;
+    const int64_t tail = K % 64 ? 1536 : 0;
+    if (2 * tiles <= cus) return K >= (c_is_f16 ? 1024 : 1536) + tail ? ID_RING128 : id;
+    return K >= (c_is_f16 ? 2048 + tail : 6144) ? ID_RING128 : id;
 }
 
 Plan select_plan_unchained(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, int64_t ldc)
@@ -337,6 +349,25 @@ Plan select_plan_unchained(int c_is_f16, int64_t M, int64_t N, int64_t K, const 
     return best;
 }
 
+// What select_plan knows beyond the sizes: the plain entry points' plans are also those that
+// gemm_f16_query_config reports; a fused epilogue or the workspace form change what can run.
+enum class Form { plain, fused, workspace };
+
+// Estimated microseconds (as kslice_us) of a plan on at most one 128 x 128 tile per compute unit, from
+// launches in a row, us: phase-alternating kernel (1024,2048,K) 14.3 / 22.4 at K = 1024 / 2048; five-stage
+// kernel 13.1 / 27.8 at 1024 / 4096; its split form (512,512,4096) 14.4, (1024,1024,4096) 26.3 (four million additions).
+double other_us(const Plan& pl, int64_t M, int64_t N, int64_t K)
+{
+    const double k = (double)K / 1024.0, mb = operand_mb(M, N, K), memory = mb > 80.0 ? 0.08 * mb : 0.0;
+    if (pl.k_split > 1) {
+        const int64_t steps = (K + 63) / 64, per_part = (steps + pl.k_split - 1) / pl.k_split;
+        const double adds = 1e-6 * (double)M * (double)N * pl.k_split;          // millions
+        return 5.0 + 0.38 * (double)per_part + 2.8 * adds + (adds > 2.7 ? 1.9 * (adds - 2.7) : 0.0) + memory;
+    }
+    if (pl.id == ID_RING128) return 8.2 + 4.9 * k + (K % 64 ? 2.5 : 0.0) + memory;
+    return 6.2 + 7.8 * k + memory;
+}
+
 // Few tiles and a long k loop (skinny problems: a few hundred rows, or few columns, against K
 // and the other dimension in the thousands): the time goes into streaming the larger operand,
 // and a compute unit streams at most the bytes it holds in flight per memory latency (about
@@ -363,24 +394,6 @@ int k_split_if_it_pays(int& id, int c_is_f16, int64_t M, int64_t N, int64_t K)
     return (int)parts;
 }
 
-// What select_plan knows beyond the sizes: the plain entry points' plans are also those that
-// gemm_f16_query_config reports; a fused epilogue or the workspace form change what can run.
-enum class Form { plain, fused, workspace };
-
-// Estimated microseconds (as kslice_us) of a plan on at most one 128 x 128 tile per compute unit, from
-// launches in a row, us: phase-alternating kernel (1024,2048,K) 14.3 / 22.4 at K = 1024 / 2048; five-stage
-// kernel 30.0 at 4096; its split form (512,512,4096) 14.4, (1024,1024,4096) 26.3 (the additions).
-double other_us(const Plan& pl, int64_t M, int64_t N, int64_t K)
-{
-    const double k = (double)K / 1024.0, mb = operand_mb(M, N, K), memory = mb > 80.0 ? 0.08 * mb : 0.0;
-    if (pl.k_split > 1) {
-        const int64_t steps = (K + 63) / 64, per_part = (steps + pl.k_split - 1) / pl.k_split;
-        return 5.0 + 0.38 * (double)per_part + 3.7e-6 * (double)M * (double)N * pl.k_split + memory;
-    }
-    if (pl.id == ID_RING128) return 9.0 + 5.1 * k + memory;
-    return 6.2 + 7.8 * k + memory;
-}
-
 // Small results go to the small tiles where the estimates say so.  Before -> after, us:
 // 256^3 6.6 -> 3.4, 512^3 7.9 -> 4.1, 1024^3 f16 13.5 -> 8.4, (128,4096,1024) 11.2 -> 6.5, (16,8192,8192)
 // f16 50 -> 37, (8192,16,8192) f16 52 -> 29, (512,1024,4096) f16 30 -> 13.4.
@@ -389,7 +402,7 @@ double other_us(const Plan& pl, int64_t M, int64_t N, int64_t K)
 // more.  In f16 mode a skinny problem, or one with K > 6144, runs on no more workgroups than it has
 // 64 x 64 tiles (the bound of its unsplit plans) -- unless at most 32 rows meet a B of 64 MB and
 // more, which half as many compute units do not read as fast ((16,8192,8192) 37 us on 256, 42 on 128).
-int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_t N, int64_t K)
+int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_t N, int64_t K, Operands operands)
 {
     const int64_t tiles = config(ID_PP128x128)->grid(M, N);
     if (tiles < 0 || tiles > chip().cus) return -1;
@@ -405,7 +418,7 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
     }
     if (form == Form::workspace && pl.k_split > 1) other += 5.0;     // the passes before and after
     double us = 0;
-    const int small = best_kslice(true, M, N, K, max_grid, &us);
+    const int small = best_kslice(operands, M, N, K, max_grid, &us);
     return small >= 0 && us < other ? ID_KSLICE + small : -1;
 }
 
@@ -415,9 +428,9 @@ Plan select_large_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void
     Plan pl = select_plan_unchained(c_is_f16, M, N, K, A, lda, B, ldb, ldc);
     if ((g_forced >= 0 && g_forced < num_configs()) || pl.id == ID_GENERIC) return pl;        // a forced configuration runs as it is
     pl.id = long_k_if_it_pays(chained_if_it_pays(pl.id, pl.rows1, N, K), c_is_f16, pl.rows1, N, K);
-    pl.id = deep_ring_if_it_pays(pl.id, pl.rows1, N, K);
+    pl.id = deep_ring_if_it_pays(pl.id, c_is_f16, pl.rows1, N, K);
     if (pl.id2 >= 0) pl.id2 = long_k_if_it_pays(chained_if_it_pays(pl.id2, M - pl.rows1, N, K), c_is_f16, M - pl.rows1, N, K);
-    if (pl.id2 >= 0) pl.id2 = deep_ring_if_it_pays(pl.id2, M - pl.rows1, N, K);
+    if (pl.id2 >= 0) pl.id2 = deep_ring_if_it_pays(pl.id2, c_is_f16, M - pl.rows1, N, K);
     if (pl.id2 >= 0 || pl.rows1 != M) return pl;
     if (form == Form::workspace) {
         // the rule of the f32 mode; the two passes over the workspace: (1024,2048,8192), 8 MB, 56 us against 53 unsplit; (256,4096,16384), 4 MB, 52 against 97
@@ -426,7 +439,10 @@ Plan select_large_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void
         if (parts > 1) { pl.id = id; pl.k_split = parts; }
     } else {
         pl.k_split = k_split_if_it_pays(pl.id, c_is_f16, M, N, K);
-        if (form == Form::fused) pl.k_split = 0;                 // a fused epilogue has to follow the whole sum
+        // a fused epilogue has to follow the whole sum; and two parts of many tiles may cost more additions
+        // than they save k steps: (1024,2048,4096) 33.4 us in two parts, 28.5 whole, (1024,2048,2048) 24.9 and 18.0,
+        // but (1280,1024,2048) 17.8 and 18.0
+        if (form == Form::fused || (pl.k_split > 1 && other_us({ID_RING128, M, -1}, M, N, K) < 0.9 * other_us(pl, M, N, K))) pl.k_split = 0;
     }
     return pl;
 }
@@ -435,7 +451,7 @@ Plan select_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, i
 {
     Plan pl = select_large_plan(c_is_f16, M, N, K, A, lda, B, ldb, ldc, form);
     if ((g_forced >= 0 && g_forced < num_configs()) || pl.id == ID_GENERIC || pl.id2 >= 0) return pl;
-    const int small = kslice_if_it_pays(pl, c_is_f16, form, M, N, K);
+    const int small = kslice_if_it_pays(pl, c_is_f16, form, M, N, K, operands_of(lda, ldb));
     if (small >= 0) { pl.id = small; pl.k_split = 0; }
     return pl;
 }

@@ -8,7 +8,7 @@
 // back, with the 24 LDS reads and 8 copies of the step in their shadow and one barrier
 // (gemm_w4a128_loop.inc, written by gen_w4a128_loop.py).
 //
-// C is read before the loop (into registers), added and stored behind it.  A k tail (K % 64
+// C is read, added and stored behind the loop.  A k tail (K % 64
 // != 0) is one unpipelined step through registers after the loop.  With a split k loop (skinny
 // f32 problems) a workgroup multiplies a part of the k steps of its tile and adds the result to
 // C atomically instead.  Requirements as for the other tuned kernels: A, B 16-byte aligned;
@@ -40,7 +40,7 @@ __device__ __forceinline__ const char* uniform_ptr128(const void* ptr)
     return (const char*)(uintptr_t)(((uint64_t)hi << 32) | lo);
 }
 
-template <typename CT>
+template <typename CT, bool SPLIT>
 __global__ __launch_bounds__(256) void gemm_w4a128_kernel(const TiledParams p)
 {
     __shared__ __attribute__((aligned(1024))) char smem[W4A128_LDS];
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256) void gemm_w4a128_kernel(const TiledParams p)
     // stream operands): workgroup b takes tile b % tiles and part b / tiles of the k steps, and
     // adds its sums to C with atomic f32 additions -- C holds the old C already, the order of the
     // additions is not fixed.  K_len = this workgroup's part of K (all of it without a split).
-    const bool split = p.k_split > 1;
+    constexpr bool split = SPLIT;
     const int num_tiles = p.tiles_m * p.tiles_n;
     const int part = split ? (int)blockIdx.x / num_tiles : 0;
     int tile_m, tile_n;
@@ -124,42 +124,26 @@ __global__ __launch_bounds__(256) void gemm_w4a128_kernel(const TiledParams p)
         }
     }
 
-    // ---- C in: fetched first, so that its way from memory overlaps that of the first k steps
-    // (a wavefront alone on its SIMD has the registers: 64 for an f32 tile) ------------------
-    // Transposed 16 x 16 blocks (B fragment first): register r of lane l is row l%16, column
-    // 4*(l/16) + r of block (fm, fn): one vector access per block.
+    // ---- C: requested behind the loop, by whole row segments of the wavefront's 64 columns, 16 bytes a lane.
+    // (Before the loop, in the order of copies and waits, C kept the first k steps waiting for
+    // longer than it saved behind the loop; and in the accumulators' own layout, consecutive lanes in different rows,
+    // the memory pipeline takes a lane a clock, 1.7 us each way.  2048^2, K = 64 / 1024 / 4096: f32 12.7 / 19.4 /
+    // 40.0 -> 11.0 / 17.4 / 37.5 us, f16 9.0 / 16.1 / 36.6 -> 7.8 / 14.8 / 35.5.)
     CT* const Cbase = (CT*)p.C;
-    typedef typename CVec4<CT>::type ctx4;
-    const int c_lrow = lane & 15, c_lcol = 4 * (lane >> 4);
-    const uint32_t c_voff = ((uint32_t)c_lrow * (uint32_t)p.ldc + (uint32_t)c_lcol) * (uint32_t)sizeof(CT);
+    const int c_lrow = lane & 15, c_lcol = 4 * (lane >> 4);           // transposed 16 x 16 blocks: register r of lane l is row l%16, column 4*(l/16) + r
     const int c_row0 = m0 + wm_base, c_col0 = n0 + wn_base;
-    float bias4[4][4];
+    constexpr int VEC = 16 / (int)sizeof(CT), TPR = 64 / VEC, RPP = 64 / TPR, PASSES = 64 / RPP;   // elements a lane; lanes a row; rows a pass; passes
+    typedef CT ctv __attribute__((ext_vector_type(VEC), aligned(sizeof(CT))));
+    const int r_row = lane / TPR, r_x = VEC * (lane % TPR);
+    const bool r_col_in = c_col0 + r_x < p.N;                         // N is a multiple of 8: all of the lane's columns or none
+    const uint32_t r_voff = ((uint32_t)r_row * (uint32_t)p.ldc + (uint32_t)r_x) * (uint32_t)sizeof(CT);
+    auto r_ok = [&](int ps) -> bool { return !edge || (r_col_in && c_row0 + RPP * ps + r_row < p.M); };
+    auto r_at = [&](int ps) -> ctv* { return reinterpret_cast<ctv*>(reinterpret_cast<char*>(Cbase + (int64_t)(c_row0 + RPP * ps) * p.ldc + c_col0) + r_voff); };
+    ctv rin[PASSES];
+    auto fetch_rows = [&]() {
 #pragma unroll
-    for (int fn = 0; fn < 4; fn++)
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-            const int col = c_col0 + fn * 16 + c_lcol + e;
-            bias4[fn][e] = (p.bias && col < p.N) ? (float)reinterpret_cast<const CT*>(p.bias)[col] : 0.0f;
-        }
-    // block (fm, fn): is this lane's group inside C?  (N is a multiple of 8: all 4 columns or none)
-    auto c_ok = [&](int fm, int fn) -> bool {
-        return !edge || ((c_row0 + fm * 16 + c_lrow < p.M) && (c_col0 + fn * 16 + c_lcol < p.N));
+        for (int ps = 0; ps < PASSES; ps++) { rin[ps] = ctv{}; if (r_ok(ps)) rin[ps] = *r_at(ps); }
     };
-    // a group outside C reads the first four elements of the workgroup's tile instead (always
-    // inside C) and is not used
-    ctx4 cin[4][4];
-    if (!split)
-#pragma unroll
-    for (int fm = 0; fm < 4; fm++)
-#pragma unroll
-        for (int fn = 0; fn < 4; fn++) {
-            const bool ok = c_ok(fm, fn);
-            const char* rowp = ok ? reinterpret_cast<const char*>(Cbase + (int64_t)(c_row0 + fm * 16) * p.ldc + c_col0)
-                                  : reinterpret_cast<const char*>(Cbase + (int64_t)m0 * p.ldc + n0);
-            const uint32_t off = ok ? c_voff + (uint32_t)(fn * 16 * sizeof(CT)) : 0u;
-            cin[fm][fn] = *reinterpret_cast<const ctx4*>(rowp + off);
-        }
-
     floatx4 acc[4][4];
     if (kt_full > 0) {
         // k steps 0..3 into stages 0..3 (a k step beyond the last one: k step 0 once more, which
@@ -196,6 +180,7 @@ __global__ __launch_bounds__(256) void gemm_w4a128_kernel(const TiledParams p)
             for (int fn = 0; fn < 4; fn++) acc[fm][fn] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
     }
 
+    if constexpr (!SPLIT) fetch_rows();
     // ---- k tail: one unpipelined step through registers, zero beyond K ------------------
     if (K_len % BK != 0) {
         __builtin_amdgcn_s_barrier();                // every wavefront is out of the loop and its copies have landed: stage 0 is free
@@ -234,38 +219,47 @@ __global__ __launch_bounds__(256) void gemm_w4a128_kernel(const TiledParams p)
     // (measured 190 G additions/s; in the accumulators' own layout -- 16 rows x 4 floats per
     // instruction -- 70 G/s): the block goes through a wavefront-private 17 KB of the LDS, which
     // is free once every wavefront is through its last k step.
-    if constexpr (sizeof(CT) == 4) {
-        if (split) {
-            constexpr uint32_t T_PITCH = 64 * 4 + 16;                 // bytes per row: rows 8 apart share banks, two at a time
-            const uint32_t tbuf = smem_base + (uint32_t)wave * (64u * T_PITCH);
-            __syncthreads();
+    if constexpr (SPLIT) {
+        constexpr uint32_t T_PITCH = 64 * 4 + 16;                 // bytes per row: rows 8 apart share banks, two at a time
+        const uint32_t tbuf = smem_base + (uint32_t)wave * (64u * T_PITCH);
+        __syncthreads();
 #pragma unroll
-            for (int fm = 0; fm < 4; fm++)
+        for (int fm = 0; fm < 4; fm++)
 #pragma unroll
-                for (int fn = 0; fn < 4; fn++)
-                    *(__attribute__((address_space(3))) floatx4*)(uintptr_t)(tbuf + (uint32_t)(fm * 16 + c_lrow) * T_PITCH + (uint32_t)(fn * 16 + c_lcol) * 4) = acc[fm][fn];
-            const int rows_in = p.M - c_row0 < 64 ? p.M - c_row0 : 64;             // rows of the block inside C (may be <= 0)
-            const bool col_in = c_col0 + lane < p.N;
-            float* const cbase = reinterpret_cast<float*>(Cbase) + (int64_t)c_row0 * p.ldc + c_col0 + lane;
-            for (int r = 0; r < rows_in; r++) {
-                const float v = *(__attribute__((address_space(3))) const float*)(uintptr_t)(tbuf + (uint32_t)r * T_PITCH + 4u * lane);
-                // a part that sums to zero leaves C alone (the memory's adders need not keep a subnormal C + 0)
-                if (col_in && v != 0.0f) unsafeAtomicAdd(cbase + (int64_t)r * p.ldc, v);
-            }
-            return;
+            for (int fn = 0; fn < 4; fn++)
+                *(__attribute__((address_space(3))) floatx4*)(uintptr_t)(tbuf + (uint32_t)(fm * 16 + c_lrow) * T_PITCH + (uint32_t)(fn * 16 + c_lcol) * 4) = acc[fm][fn];
+        const int rows_in = p.M - c_row0 < 64 ? p.M - c_row0 : 64;             // rows of the block inside C (may be <= 0)
+        const bool col_in = c_col0 + lane < p.N;
+        float* const cbase = reinterpret_cast<float*>(Cbase) + (int64_t)c_row0 * p.ldc + c_col0 + lane;
+        for (int r = 0; r < rows_in; r++) {
+            const float v = *(__attribute__((address_space(3))) const float*)(uintptr_t)(tbuf + (uint32_t)r * T_PITCH + 4u * lane);
+            // a part that sums to zero leaves C alone (the memory's adders need not keep a subnormal C + 0)
+            if (col_in && v != 0.0f) unsafeAtomicAdd(cbase + (int64_t)r * p.ldc, v);
         }
-    }
-    // ---- + C, + bias, ReLU, -> C ------------------------------------------------------
+    } else {
+        // ---- + C, + bias, ReLU, -> C: the wavefront's block goes through its part of the LDS ------
+        constexpr uint32_t T_PITCH = 64 * 4 + 16;
+        const uint32_t tbuf = smem_base + (uint32_t)wave * (64u * T_PITCH);
+        __syncthreads();
 #pragma unroll
-    for (int fm = 0; fm < 4; fm++) {
-        char* rowp = reinterpret_cast<char*>(Cbase + (int64_t)(c_row0 + fm * 16) * p.ldc + c_col0);
+        for (int fm = 0; fm < 4; fm++)
 #pragma unroll
-        for (int fn = 0; fn < 4; fn++) {
-            ctx4 v;
+            for (int fn = 0; fn < 4; fn++)
+                *(__attribute__((address_space(3))) floatx4*)(uintptr_t)(tbuf + (uint32_t)(fm * 16 + c_lrow) * T_PITCH + (uint32_t)(fn * 16 + c_lcol) * 4) = acc[fm][fn];
+        asm volatile("" ::: "memory");                                // (a wavefront's LDS operations are carried out in order)
+        float bias_v[VEC];
 #pragma unroll
-            for (int e = 0; e < 4; e++) v[e] = (CT)epilogue_value(acc[fm][fn][e] + (float)cin[fm][fn][e], bias4[fn][e], p.relu);   // f16: one rounding, to nearest even
-            if (c_ok(fm, fn))
-                *reinterpret_cast<ctx4*>(rowp + c_voff + fn * 16 * sizeof(CT)) = v;
+        for (int e = 0; e < VEC; e++) bias_v[e] = (p.bias && r_col_in) ? (float)reinterpret_cast<const CT*>(p.bias)[c_col0 + r_x + e] : 0.0f;
+#pragma unroll
+        for (int ps = 0; ps < PASSES; ps++) {
+            ctv o;
+#pragma unroll
+            for (int v = 0; v < VEC; v += 4) {
+                const floatx4 s4 = *(__attribute__((address_space(3))) const floatx4*)(uintptr_t)(tbuf + (uint32_t)(RPP * ps + r_row) * T_PITCH + (uint32_t)(r_x + v) * 4);
+#pragma unroll
+                for (int e = 0; e < 4; e++) o[v + e] = (CT)epilogue_value(s4[e] + (float)rin[ps][v + e], bias_v[v + e], p.relu);   // f16: one rounding, to nearest even
+            }
+            if (r_ok(ps)) *r_at(ps) = o;
         }
     }
 }
@@ -287,9 +281,12 @@ int launch_w4a128(const GemmArgs& a)
     if (g * parts > INT32_MAX) return GEMM_F16_ERR_SIZE;
     p.k_split = parts;
     if (a.c_is_f16)
-        hipLaunchKernelGGL(gemm_w4a128_kernel<half_t>, dim3((unsigned)g), dim3(256), 0, a.stream, p);
+        hipLaunchKernelGGL((gemm_w4a128_kernel<half_t, false>), dim3((unsigned)g), dim3(256), 0, a.stream, p);
     else
-        hipLaunchKernelGGL(gemm_w4a128_kernel<float>, dim3((unsigned)(g * parts)), dim3(256), 0, a.stream, p);
+    {
+        if (parts > 1) hipLaunchKernelGGL((gemm_w4a128_kernel<float, true>), dim3((unsigned)(g * parts)), dim3(256), 0, a.stream, p);
+        else           hipLaunchKernelGGL((gemm_w4a128_kernel<float, false>), dim3((unsigned)g), dim3(256), 0, a.stream, p);
+    }
     return hipGetLastError() == hipSuccess ? GEMM_F16_OK : GEMM_F16_ERR_LAUNCH;
 }
 
