@@ -14,8 +14,8 @@
 // as long (256 workgroups streaming 128 x 64 and 64 x 128 blocks out of the L2s: 14.7 TB/s at 16- and
 // at 4-byte alignment, 12.7 with an odd pitch, 9.0 with every row odd), so the tile is as large as
 // leaves two workgroups a compute unit to cover each other, and two k steps are in flight in
-// registers.  Before -> after, us: 2001 x 1999 x 2003 f32 264 -> 35, 4001 x 3999 x 4003 f32 2700 ->
-// 217, 16001 x 701 x 1501 697 -> 94, 513 x 511 x 509 34 -> 18 (element-wise kernel before).
+// registers.  Before -> after, us: 2001 x 1999 x 2003 f32 264 -> 34, 4001 x 3999 x 4003 f32 2700 ->
+// 206, (14159,1005,2990) f16 with bias and ReLU 1810 -> 160 (element-wise kernel before).
 //
 // KG = 2: two groups of four wavefronts take the k steps in turn, each on its own LDS stages, and
 // their sums are added at the end -- for problems of at most one tile per compute unit, where
@@ -54,28 +54,27 @@ __global__ __launch_bounds__(256 * KG, 2) void gemm_unaligned_kernel(const Tiled
     const int m0 = tile_m * UBM, n0 = tile_n * UBN;
     const bool edge = (m0 + UBM > p.M) || (n0 + UBN > p.N);
 
-    // ---- copy plan (as in the tuned 128 x 128 kernels; columns of B clamped to the last 8) -----
-    const int a_chunk = (lane & 7) ^ (4 * (wave & 1) + (lane >> 4));
-    uint32_t a_off[4], b_off[4];
+    // ---- copy plan: load t < 4 takes A rows 8 (wave + 4t) .. +7, 8 lanes a row; load 4 + t takes k rows 4 (wave + 4t) .. +3
+    // of B, 16 lanes a row (columns clamped to the last 8).  Consecutive lanes fetch consecutive chunks, and
+    // each chunk goes to the place that it has in the tuned 128 x 128 kernels (chunks fetched in the
+    // order of those places: 2 to 8 % slower, (15552,2147,1467) f32 216 us against 202, (6750,7396,630) f16 142 against 130).
+    const int a_chunk = lane & 7, b_chunk = lane & 15;
+    uint32_t a_off[4];
 #pragma unroll
     for (int t = 0; t < 4; t++) {
         int row = 8 * (wave + 4 * t) + (lane >> 3);
         row = (m0 + row < p.M) ? row : p.M - 1 - m0;
         a_off[t] = ((uint32_t)row * (uint32_t)p.lda + 8 * a_chunk) * 2;
     }
-    const int b_krow0 = 4 * wave + (lane >> 4);                       // k row of copy t: b_krow0 + 16t
-    int b_col;                                                        // first column of this lane's chunk
-    {
-        const int swz = ((lane >> 4) << 2) | (((wave >> 1) & 1) << 1);
-        b_col = n0 + 8 * ((lane & 15) ^ swz);
-        if (b_col > p.N - 8) b_col = p.N - 8;
-#pragma unroll
-        for (int t = 0; t < 4; t++) b_off[t] = ((uint32_t)(b_krow0 + 16 * t) * (uint32_t)p.ldb + (uint32_t)b_col) * 2u;
-    }
+    const int b_krow0 = 4 * wave + (lane >> 4);                       // k row of load 4 + t: b_krow0 + 16t
+    int b_col = n0 + 8 * b_chunk;                                     // first column of this lane's chunk
+    if (b_col > p.N - 8) b_col = p.N - 8;
+    const uint32_t b_off = ((uint32_t)b_krow0 * (uint32_t)p.ldb + (uint32_t)b_col) * 2u;
     const char* const a_tile = (const char*)(p.A + (int64_t)m0 * p.lda);
     const char* const b_mat = (const char*)p.B;
     const uint32_t lds_group = smem_base + (uint32_t)kg * (2 * USTAGE);
-    const uint32_t w_addr = lds_group + 1024u * wave + 16u * lane;
+    const uint32_t a_wr = lds_group + 1024u * wave + 128u * (lane >> 3) + 16u * (a_chunk ^ (4 * (wave & 1) + (lane >> 4)));
+    const uint32_t b_wr = lds_group + UA_BUF + 1024u * wave + 256u * (lane >> 4) + 16u * (b_chunk ^ (((lane >> 4) << 2) | (((wave >> 1) & 1) << 1)));
 
     // ---- fragment read addresses (as in gemm_w4a128.hip) ----------------------------------
     uint32_t a_rd[2], b_rd[4];
@@ -104,7 +103,7 @@ __global__ __launch_bounds__(256 * KG, 2) void gemm_unaligned_kernel(const Tiled
 #pragma unroll
         for (int t = t0; t < t1; t++) {
             if (t < 4) r[t] = *reinterpret_cast<const uintx4_any*>(a_tile + k0 * 2 + a_off[t]);
-            else       r[t] = *reinterpret_cast<const uintx4_any*>(b_mat + k0 * p.ldb * 2 + b_off[t - 4]);
+            else       r[t] = *reinterpret_cast<const uintx4_any*>(b_mat + (k0 + 16 * (t - 4)) * p.ldb * 2 + b_off);
         }
     };
     // The step with the k tail (or beyond it: all zero).  Chunk c of the step covers k = k0 + 8c ..
@@ -139,7 +138,7 @@ __global__ __launch_bounds__(256 * KG, 2) void gemm_unaligned_kernel(const Tiled
     auto put = [&](int stage, const uintx4 (&r)[8], int t0, int t1) {
 #pragma unroll
         for (int t = t0; t < t1; t++)
-            *(__attribute__((address_space(3))) uintx4*)(uintptr_t)(w_addr + (uint32_t)stage * USTAGE + (t < 4 ? 4096u * t : UA_BUF + 4096u * (t - 4))) = r[t];
+            *(__attribute__((address_space(3))) uintx4*)(uintptr_t)((t < 4 ? a_wr + 4096u * t : b_wr + 4096u * (t - 4)) + (uint32_t)stage * USTAGE) = r[t];
     };
 
     floatx4 acc[4][4];
