@@ -63,9 +63,10 @@ enum {
  * C is read once and written once per element, outside the k loop (the paper
  * hoists the C load and store out of it: section Generating WMMA Ops and
  * More).  Where the old value of C enters the sum is the kernel's choice: the
- * large-tile kernels sum the K products starting from zero and add C last
- * (sum + C, one more f32 rounding at the end), the small-tile and any-shape
- * kernels start the accumulators from C (C + sum), and the long-k kernel adds
+ * large-tile kernels, the small tiles and the tiled kernel for any alignment
+ * sum the K products starting from zero and add C last (sum + C, one more f32
+ * rounding at the end), the element-wise any-shape kernel and the plain 64 x 64
+ * tiling start the accumulators from C (C + sum), and the long-k kernel adds
  * C to the running sum while its first few dozen k steps are being summed
  * ((partial sum + C) + rest; on edge tiles it adds C last).  The summation order over
  * k is the kernel's own as well; results are bit-exact wherever every partial
