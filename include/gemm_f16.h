@@ -205,7 +205,7 @@ typedef struct gemm_f16_config {
     int32_t block_m;     /* workgroup tile rows */
     int32_t block_n;     /* workgroup tile columns */
     int32_t block_k;     /* k extent staged in LDS per main-loop step */
-    int32_t waves;       /* 64-lane wavefronts per workgroup (of one k group, where several groups take the k steps in turn: names ending in _k8) */
+    int32_t waves;       /* 64-lane wavefronts per workgroup (of one k group, where several groups take the k steps in turn: names ending in _k2 and _k8) */
     int32_t wave_m;      /* wavefront tile rows */
     int32_t wave_n;      /* wavefront tile columns */
     int32_t lds_bytes;   /* LDS bytes per workgroup */
@@ -234,7 +234,7 @@ int gemm_f16_describe_config(int id, gemm_f16_config* out);
  * Benchmarking aid: force configuration `id` for every later call of this
  * process (id < 0 restores automatic selection).  A forced configuration whose
  * alignment or pitch requirements the call does not meet is ignored for that
- * call (the _k8 configurations have no alignment requirement).  The launch forms made for several tiles per compute unit (names
+ * call (the _k8 and the generic128x128x64 configurations have no alignment requirement).  The launch forms made for several tiles per compute unit (names
  * ending in _chain and _stag) run the plain 256 x 256 tiling on problems with
  * too few tiles for them (and _stag on devices other than 256 compute units);
  * with a k tail (K not a multiple of 64) a forced _chain still runs chained,

@@ -26,7 +26,8 @@ enum {
     ID_RING128,        // 128 x 128, four wavefronts of 64 x 64, k loop in assembly over five LDS stages
     ID_KSLICE,         // + 0 .. 4: 16 x 32, 32 x 32, 16 x 64, 32 x 64, 64 x 64, eight wavefronts take the k steps in turn
     NUM_KSLICE = 5,
-    NUM_PRODUCT = ID_KSLICE + NUM_KSLICE
+    ID_UNALIGNED = ID_KSLICE + NUM_KSLICE,     // + 0, 1: 128 x 128 at any alignment, one k group or two
+    NUM_PRODUCT = ID_UNALIGNED + 2
 };
 
 const GemmConfigDesc kGeneric = {
@@ -55,6 +56,7 @@ const GemmConfigDesc* config(int id)
     case ID_LONG_K:    return long_k_config();
     case ID_RING128:   return deep_ring_config();
     case ID_KSLICE + 0: case ID_KSLICE + 1: case ID_KSLICE + 2: case ID_KSLICE + 3: case ID_KSLICE + 4: return kslice_config(id - ID_KSLICE, false);
+    case ID_UNALIGNED + 0: case ID_UNALIGNED + 1: return unaligned_config(1 + id - ID_UNALIGNED);
 #ifdef GEMM_F16_LADDER
     case NUM_PRODUCT + 0: return tiled_config(128);
     case NUM_PRODUCT + 1: return tiled_config(256);
@@ -173,12 +175,14 @@ const GemmConfigDesc* any_shape_kernel(int64_t M, int64_t N, int64_t K, int64_t 
 {
     const bool tiled = M <= INT32_MAX - 128 && N >= 8 && K >= 8 && lda <= MAX_TUNED_PITCH && ldb <= MAX_TUNED_PITCH;   // (row numbers of a whole tile in 31 bits)
     if (tiled && g_forced >= ID_KSLICE && g_forced < ID_KSLICE + NUM_KSLICE) return kslice_config(g_forced - ID_KSLICE, true);
+    if (tiled && (g_forced == ID_UNALIGNED || g_forced == ID_UNALIGNED + 1)) return config(g_forced);
     if (!tiled || (g_forced >= 0 && g_forced < num_configs())) return config(ID_GENERIC);
-    const int64_t tiles = unaligned_config()->grid(M, N), cus = chip().cus;
-    if (tiles < 0 || tiles > cus) return unaligned_config();
+    // at most one tile per compute unit: two k groups, or one wavefront per SIMD would have nothing to hide its waits
+    const int64_t tiles = unaligned_config(1)->grid(M, N), cus = chip().cus;
+    if (tiles < 0 || tiles > cus) return unaligned_config(1);
     double us = 0;
     const int small = best_kslice(Operands::any, M, N, K, INT32_MAX, &us);
-    return small >= 0 && us < (2 * tiles > cus ? 14.0 : 12.0) + 11.0 * (double)K / 1024.0 ? kslice_config(small, true) : unaligned_config();
+    return small >= 0 && us < (2 * tiles > cus ? 14.0 : 12.0) + 11.0 * (double)K / 1024.0 ? kslice_config(small, true) : unaligned_config(2);
 }
 
 // What a call runs: one configuration on all rows, or the 256 x 256 kernel on

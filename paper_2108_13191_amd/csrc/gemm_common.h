@@ -53,7 +53,8 @@ int launch_generic(const GemmArgs& a);
 int64_t grid_generic(int64_t M, int64_t N);
 
 // gemm_unaligned.hip: 128 x 128 tiles at any alignment (N, K >= 8)
-const GemmConfigDesc* unaligned_config();
+// k_groups: 1, or 2 groups of four wavefronts that take the k steps in turn
+const GemmConfigDesc* unaligned_config(int k_groups);
 
 // gemm_kslice.hip: eight wavefronts share a small tile of C and take its k steps in turn (any alignment, N, K >= 8)
 // index 0 .. 4: 16x32, 32x32, 16x64, 32x64, 64x64; any_shape: under the name that the any-shape family reports

@@ -274,26 +274,22 @@ int64_t grid_unaligned(int64_t M, int64_t N)
     return tm * tn;
 }
 
-template <typename CT>
-void launch_unaligned_as(const TiledParams& p, int64_t g, hipStream_t stream)
-{
-    if (g <= chip().cus) hipLaunchKernelGGL((gemm_unaligned_kernel<CT, 2>), dim3((unsigned)g), dim3(512), 0, stream, p);
-    else                 hipLaunchKernelGGL((gemm_unaligned_kernel<CT, 1>), dim3((unsigned)g), dim3(256), 0, stream, p);
-}
-
+template <int KG>
 int launch_unaligned(const GemmArgs& a)
 {
     const int64_t g = grid_unaligned(a.M, a.N);
     if (g < 0 || a.N < 8 || a.K < 8) return GEMM_F16_ERR_SIZE;
     const TiledParams p = make_tiled_params(a, UBM, UBN, 8);
-    if (a.c_is_f16) launch_unaligned_as<half_t>(p, g, a.stream);
-    else            launch_unaligned_as<float>(p, g, a.stream);
+    const dim3 grid((unsigned)g), block(256 * KG);
+    if (a.c_is_f16) hipLaunchKernelGGL((gemm_unaligned_kernel<half_t, KG>), grid, block, 0, a.stream, p);
+    else            hipLaunchKernelGGL((gemm_unaligned_kernel<float, KG>), grid, block, 0, a.stream, p);
     return hipGetLastError() == hipSuccess ? GEMM_F16_OK : GEMM_F16_ERR_LAUNCH;
 }
 
-const GemmConfigDesc kUnaligned128 = {
-    "generic128x128x64", UBM, UBN, BK, 4, 64, 64, unaligned_lds<1>(), false, launch_unaligned, grid_unaligned};
+const GemmConfigDesc kUnaligned128[2] = {
+    {"generic128x128x64", UBM, UBN, BK, 4, 64, 64, unaligned_lds<1>(), false, launch_unaligned<1>, grid_unaligned},
+    {"generic128x128x64_k2", UBM, UBN, BK, 4, 64, 64, unaligned_lds<2>(), false, launch_unaligned<2>, grid_unaligned}};
 
 }  // namespace
 
-const GemmConfigDesc* unaligned_config() { return &kUnaligned128; }
+const GemmConfigDesc* unaligned_config(int k_groups) { return &kUnaligned128[k_groups - 1]; }

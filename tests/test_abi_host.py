@@ -114,6 +114,24 @@ def test_large_pitches_take_64_bit_addressing(lib):
         binding.force_config(-1)
 
 
+def test_report_of_the_two_forms_for_any_alignment(lib):
+    """The 128 x 128 kernel for operands of any alignment has two forms, one and two k groups (at most
+    one tile per compute unit); a report names the one that runs, with its LDS bytes, and both can be forced."""
+    odd = lambda M, N, K: binding.query_config(0, M, N, K, 2, K, 2, N, 4, N)
+    one, two = odd(2177, 2049, 391), odd(2001, 1999, 2003)             # 306 tiles, 256 tiles
+    assert (one["name"], one["grid"], one["lds_bytes"], one["waves"]) == ("generic128x128x64", 306, 69632, 4)
+    assert (two["name"], two["grid"], two["lds_bytes"], two["waves"]) == ("generic128x128x64_k2", 256, 139264, 4)
+    for name in (one["name"], two["name"]):
+        cfg = [i for i in range(binding.num_configs()) if binding.describe_config(i)["name"] == name][0]
+        binding.force_config(cfg)
+        try:
+            assert odd(130, 141, 9)["name"] == name and odd(2177, 2049, 391)["name"] == name
+            assert binding.query_config(0, 256, 256, 256, 16, 256, 16, 256, 16, 256)["id"] == cfg
+            assert odd(130, 7, 9)["name"] not in (one["name"], two["name"])       # no chunk of 8 elements
+        finally:
+            binding.force_config(-1)
+
+
 def test_header_is_plain_c(tmp_path):
     """include/gemm_f16.h compiles as C99 on its own, and a C program that calls
     the host-only entry points links against the library and runs (no GPU)."""
