@@ -176,7 +176,7 @@ const GemmConfigDesc* any_shape_kernel(int64_t M, int64_t N, int64_t K, int64_t 
     const bool tiled = M <= INT32_MAX - 128 && N >= 8 && K >= 8 && lda <= MAX_TUNED_PITCH && ldb <= MAX_TUNED_PITCH;   // (row numbers of a whole tile in 31 bits)
     if (tiled && g_forced >= ID_KSLICE && g_forced < ID_KSLICE + NUM_KSLICE) return kslice_config(g_forced - ID_KSLICE, true);
     if (tiled && (g_forced == ID_UNALIGNED || g_forced == ID_UNALIGNED + 1)) return config(g_forced);
-    if (!tiled || (g_forced >= 0 && g_forced < num_configs())) return config(ID_GENERIC);
+    if (!tiled || g_forced == ID_GENERIC) return config(ID_GENERIC);       // (another forced configuration, which cannot run here, is ignored)
     // at most one tile per compute unit: two k groups, or one wavefront per SIMD would have nothing to hide its waits
     const int64_t tiles = unaligned_config(1)->grid(M, N), cus = chip().cus;
     if (tiles < 0 || tiles > cus) return unaligned_config(1);

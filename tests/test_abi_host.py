@@ -132,6 +132,24 @@ def test_report_of_the_two_forms_for_any_alignment(lib):
             binding.force_config(-1)
 
 
+def test_forced_configuration_that_cannot_run_is_ignored(lib):
+    """A forced configuration whose alignment the operands do not have: the call runs what it would run
+    without it; configuration 0 forced is the element-wise kernel."""
+    shapes = [(2001, 1999, 2003), (2177, 2049, 391), (130, 141, 9), (130, 7, 9)]
+    odd = lambda M, N, K: binding.query_config(0, M, N, K, 2, K, 2, N, 4, N)
+    want = [odd(*s) for s in shapes]
+    names = [binding.describe_config(i)["name"] for i in range(binding.num_configs())]
+    try:
+        for i, name in enumerate(names):
+            if name.startswith(("pp", "t64", "w4a")):
+                binding.force_config(i)
+                assert [odd(*s) for s in shapes] == want, name
+        binding.force_config(0)
+        assert all(odd(*s)["name"] == names[0] for s in shapes)
+    finally:
+        binding.force_config(-1)
+
+
 def test_header_is_plain_c(tmp_path):
     """include/gemm_f16.h compiles as C99 on its own, and a C program that calls
     the host-only entry points links against the library and runs (no GPU)."""
