@@ -22,21 +22,23 @@ struct TiledParams {
     int k_split;           // five-stage 128 x 128 kernel: > 1 = workgroup b works on tile b % tiles, part b / tiles of the k loop, and adds to C atomically
 };
 
-// From this size on C is read and written with the non-temporal hint: it would push A and B out of the
-// caches and not be there at the next call itself, whose read then waits for the write-back.
-// Launches in a row on three sets of operands, without -> with, us: (16384,2304,768) f32 (151 MB) 97.5 -> 84.3,
-// (16384,3072,768) f32 (201 MB) 129.6 -> 116.7, f16 (101 MB) 101.6 -> 92.9, (8192,8192,1024) f32
-// (268 MB) 202 -> 171, f16 (134 MB) 160 -> 143, (6000,6000,1000) f32 (144 MB) 125 -> 117; below the line C
-// often survives in the 256 MB last-level cache: (4096,4096,1024) f32 (67 MB) 45.1 -> 49.9, (5528,3480,1880)
-// f32 (77 MB) 97 -> 100, (1332,13440,1344) f32 (72 MB) 71.5 -> 68.6.  (One C used again and again, which
-// survives up to about 200 MB: (16384,2304,768) f32 79.6 -> 84.7, (8192,8192,1024) f16 139 -> 144.)
-// Not from K = 4096 on, where the traffic of C is a small part (8192^3 f32 795 -> 798), and not
-// where rows of C begin within a 64-byte sector: (14910,2968,256) f32 at a pitch of 3032 91 -> 102.
-constexpr double C_ONCE_BYTES = 96e6;
+// A launch whose C is larger than what the 256 MB last-level cache can keep reads and writes it with the
+// non-temporal hint: C would push A and B out of the cache and not be there at the next call itself.
+// Below, C = A B + C into one C again and again finds C in the cache, and the hint takes it
+// away; the line lies where no use loses.  us without -> with, one C again | three sets of operands
+// and C in turn: f32 (6142,4720,216) 116 MB 50 -> 69 | 68 -> 71, (6000,6000,1000) 144 MB 104 -> 120 | 127 -> 118,
+// (16384,2304,768) 151 MB 79 -> 84 | 96 -> 83, (2656,20864,64) 222 MB 71 -> 88 | 99 -> 89, (8192,8192,1024)
+// 268 MB 188 -> 172 | 194 -> 169 (but with a kernel that reads C after it 246 -> 253), (3087,32256,448) 398 MB
+// 194 -> 175 | 198 -> 172; f16 (16384,3072,768) 101 MB 89 -> 92 | 99 -> 93, (5602,30592,384) 343 MB 223 -> 201 | 227 -> 200.
+// (The hint on the loads alone or on the stores alone: up to 16 % slower on one C and 2 to 5 % faster on three.)
+// Not below K = 256, where it costs more than it spares up to 340 MB ((4080,18944,64) f32 309 MB 119 -> 133 |
+// 137 -> 134), not from K = 4096 on, where the traffic of C is a small part (8192^3 f32 795 -> 798), and
+// not where rows of C begin within a 64-byte sector: (14910,2968,256) f32 at a pitch of 3032 91 -> 102.
+constexpr double C_ONCE_BYTES = 300e6;
 inline bool c_once(const GemmArgs& a)
 {
     const int64_t size = a.c_is_f16 ? 2 : 4;
-    return a.K < 4096 && (double)a.M * (double)a.N * (double)size >= C_ONCE_BYTES && a.ldc * size % 64 == 0 && (uintptr_t)a.C % 64 == 0;
+    return a.K >= 256 && a.K < 4096 && (double)a.M * (double)a.N * (double)size >= C_ONCE_BYTES && a.ldc * size % 64 == 0 && (uintptr_t)a.C % 64 == 0;
 }
 
 // The fields every launcher fills the same way: the problem, the tile grid for bm x bn tiles,

@@ -1,4 +1,4 @@
-"""The forms of the phase-alternating kernel that read and write a large C (96 MB and more, K < 4096) with the
+"""The forms of the phase-alternating kernel that read and write a large C (300 MB and more, 256 <= K < 4096) with the
 non-temporal hint: every tile form, with and without a k tail, ragged edges, just above and just
 below the size, rows of C that begin at 64-byte sectors and that do not.  Integers bit for bit against the oracle on sampled rows."""
 import numpy as np
@@ -8,7 +8,7 @@ torch = pytest.importorskip("torch")
 if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
-from gpu_util import config_id, run_gemm
+from gpu_util import DevMat, config_id
 from paper_2108_13191_amd import binding
 from paper_2108_13191_amd import workloads as wl
 
@@ -28,14 +28,21 @@ def _unforce():
 @pytest.mark.parametrize("mode", ["f32", "f16"])
 def test_large_c(oracle_mod, name, mode):
     binding.force_config(config_id(name))
-    # 96.2 MB three times, then 95.9
-    for M, N, K, pad in ((5861, 4104, 128, 24), (5861, 4104, 72, 24), (5861, 4104, 72, 0), (5841, 4104, 64, 24)):
+    # 300.0 MB three times (the third at rows within a sector), then 299.4
+    for M, N, K, pad in ((9147, 8200, 320, 24), (9147, 8200, 264, 24), (9147, 8200, 264, 0), (9127, 8200, 256, 24)):
         if mode == "f16":
             M *= 2
         A, B, _ = wl.make_inputs(M, N, K, "int2", "zeros", seed=K)
-        C0 = ((np.arange(M)[:, None] + np.arange(N)[None, :]) % 9 - 4).astype(CDT[mode])
-        got = run_gemm(A, B, C0, mode, ldc=N + pad)
         rows = np.unique(np.concatenate([[0, 1, 127, 128, 255, 256, M - 257, M - 2, M - 1], np.random.default_rng(K).integers(0, M, 40)]))
-        Cref, _ = oracle_mod.gemm_f16(A, B, C0, rows=rows)
+        C0 = ((rows[:, None] + np.arange(N)[None, :]) % 9 - 4).astype(CDT[mode])
+        dA, dB = DevMat(A, nan_canary=True), DevMat(B, nan_canary=True)
+        buf = torch.full((M + 1, N + pad), -1234.0, dtype=torch.float32 if mode == "f32" else torch.float16, device="cuda")
+        C = buf[:M, :N]
+        C.copy_((torch.arange(M, device="cuda", dtype=torch.int16)[:, None] % 9 + torch.arange(N, device="cuda", dtype=torch.int16)[None, :]) % 9 - 4)
+        fn = binding.gemm_f16_f32acc if mode == "f32" else binding.gemm_f16_f16acc
+        binding.check(fn(M, N, K, dA.ptr, dA.ld, dB.ptr, dB.ld, buf, N + pad, torch.cuda.current_stream().cuda_stream))
+        got = C[torch.from_numpy(rows).cuda()].cpu().numpy()
+        assert bool((buf[M] == -1234.0).all()) and bool((buf[:, N:] == -1234.0).all()), "memory outside C was written"
+        Cref, _ = oracle_mod.gemm_f16(A[rows], B, C0)
         want = oracle_mod.round_to_f32(Cref) if mode == "f32" else Cref.astype(np.float16)
-        assert np.array_equal(got[rows], want), (name, M, N, K, mode)
+        assert np.array_equal(got, want), (name, M, N, K, mode)
