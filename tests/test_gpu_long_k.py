@@ -230,6 +230,37 @@ def test_split_k_propagates_nan_and_infinities(oracle_mod):
     assert np.all(err <= (1e-5 * (S + np.abs(C0.astype(np.float64))))[fin])
 
 
+def test_half_precision_mode_cut_along_k(oracle_mod):
+    """gemm_f16_f16acc_workspace on problems that are cut along k: the lent memory, NaN before, holds sums
+    afterwards (a plan that does not cut leaves it alone).  Integers bit for bit, random data to
+    tolerance, a C pitch that is not N and a C at an odd element; with a byte too few the call runs
+    unsplit, with the same integers.  The problems of few rows have a B that takes one launch
+    longer to stream than the parts."""
+    from gpu_util import DevMat
+    cases = [(12, 1032, 8200), (6, 600, 9056), (54, 536, 8904), (237, 1608, 14320), (67, 448, 11920)]
+    for idx, (M, N, K) in enumerate(cases):
+        need = binding.gemm_f16_f16acc_workspace_bytes(M, N, K)
+        assert need == M * N * 4, (M, N, K, need)
+        ws = torch.empty((need // 4 + 4,), device="cuda")
+        for dist, exact in (("int2", True), ("uniform", False)):
+            A, B, C0 = wl.make_inputs(M, N, K, dist, "zeros" if exact else "uniform", seed=1500 + idx, c_dtype=np.float16)
+            if exact:
+                C0 = np.random.default_rng(idx).integers(-4, 5, size=(M, N)).astype(np.float16)
+            Cref, S = oracle_mod.gemm_f16(A, B, C0)
+            for ws_bytes in (need, need - 1):
+                dA, dB, dC = DevMat(A, nan_canary=True), DevMat(B, nan_canary=True), DevMat(C0, N + 8 * (idx % 3), idx % 2)
+                ws.fill_(float("nan"))
+                binding.check(binding.gemm_f16_f16acc_workspace(M, N, K, dA.ptr, dA.ld, dB.ptr, dB.ld, dC.ptr, dC.ld, ws, ws_bytes, 0))
+                torch.cuda.synchronize()
+                left = int(torch.isnan(ws[:need // 4]).sum())
+                assert left == (0 if ws_bytes == need else need // 4), ((M, N, K), ws_bytes, left)
+                assert bool(torch.isnan(ws[need // 4:]).all()), "memory behind the workspace was written"
+                if exact:
+                    assert np.array_equal(dC.fetch(), Cref.astype(np.float16)), f"ints {(M, N, K)} workspace {ws_bytes}"
+                else:
+                    assert_close(dC.fetch(), Cref, S, C0, "f16", what=f"workspace {(M, N, K)} {ws_bytes}")
+
+
 def test_half_precision_mode_with_a_workspace(oracle_mod):
     """gemm_f16_f16acc_workspace: with M x N floats of scratch memory the skinny problems that the
     f32 mode cuts along k are cut in the f16 mode too (the parts add to the zeroed workspace, a last
