@@ -133,10 +133,10 @@ bool aligned_for_tiled(int64_t N, int64_t K, const void* A, int64_t lda, const v
 // beyond what the last-level cache keeps between calls: strips of B 64 or 128 bytes wide come out of
 // the memory at 2.7 TB/s ((128,8192,8192) 64x64 49 us, its k loop from the caches 30).
 // Rows that begin within a 128-byte line: (1024,1024,2048) 64x64 11.9 us at pitches of 64 elements' multiples, 14.9 at others.
-// What a short k loop does not hide on aligned problems: up to 1.5 us for the edges of C in f16 (K < 320), and as
+// What a short k loop does not hide: up to 1.5 us for the edges of C in f16 (K < 320, aligned), and as
 // much where there is more than one round of workgroups (K < 640) -- phase-alternating kernel -> small tiles, us:
 // (144,6768,48) f32 5.7 -> 7.7, (212,4464,24) f16 6.0 -> 7.7, (88,8448,256) f16 7.0 -> 7.9, (2618,200,32) f16
-// 6.1 -> 6.8, (88,9792,320) f16 7.6 -> 9.1, but (567,648,232) f32 7.5 -> 4.9, (320,2304,192) f16 6.6 -> 5.6.
+// 6.1 -> 6.8, (88,9792,320) f16 7.6 -> 9.1; 128 x 128 at any alignment -> small tiles (685,3452,95) f16 9.9 -> 13.2; but (567,648,232) f32 7.5 -> 4.9, (320,2304,192) f16 6.6 -> 5.6.
 enum class Operands { lines, chunks, any };              // rows begin at 128-byte lines; at 16 bytes; anywhere
 Operands operands_of(int64_t lda, int64_t ldb) { return lda % 64 || ldb % 64 ? Operands::chunks : Operands::lines; }
 struct KsliceCand { int per_cu; double fixed1, rate1, fixed2, rate2; };
@@ -153,7 +153,7 @@ double kslice_us(int index, Operands form, int64_t M, int64_t N, int64_t K)
     const int64_t cus = chip().cus, full = g / (cus * c.per_cu), left = g % (cus * c.per_cu);
     const double k = (double)K / 1024.0 * (form == Operands::lines ? 1.0 : form == Operands::chunks ? 1.25 : 1.75), f = form == Operands::any ? 1.15 : 1.0, mb = operand_mb(M, N, K);
     const double round1 = f * c.fixed1 + k * c.rate1, round2 = f * c.fixed2 + k * c.rate2;
-    const double short_k = form == Operands::any ? 0.0 : (K < 320 ? 1.5 : 0.0) + (K < 640 && g > cus * c.per_cu ? 1.5 : 0.0);
+    const double short_k = (K < 320 && form != Operands::any ? 1.5 : 0.0) + (K < 640 && g > cus * c.per_cu ? 1.5 : 0.0);
     return 1.6 + short_k + (double)full * round2 + (left == 0 ? 0.0 : left <= cus ? round1 : round2) + (mb > 80.0 ? 0.19 * mb : 0.0);
 }
 
@@ -176,7 +176,7 @@ int best_kslice(Operands form, int64_t M, int64_t N, int64_t K, int64_t max_grid
 // chip) -- measured, 128 x 128 -> best small tile, us: 513 x 511 x 509 18.7 -> 6.3, 1001 x 1003 x 1005 24.2 -> 12.0,
 // (16,8191,8191) 126 -> 37, (1501,1499,503) 19.8 against 20.4, (2001,1999,255) 16.9 against 22.6; else the
 // element-wise one.
-const GemmConfigDesc* any_shape_kernel(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb)
+const GemmConfigDesc* any_shape_kernel(int c_is_f16, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc)
 {
     const bool tiled = M <= INT32_MAX - 128 && N >= 8 && K >= 8 && lda <= MAX_TUNED_PITCH && ldb <= MAX_TUNED_PITCH;   // (row numbers of a whole tile in 31 bits)
     if (tiled && g_forced >= ID_KSLICE && g_forced < ID_KSLICE + NUM_KSLICE) return kslice_config(g_forced - ID_KSLICE, true);
@@ -184,7 +184,18 @@ const GemmConfigDesc* any_shape_kernel(int64_t M, int64_t N, int64_t K, int64_t 
     if (!tiled || g_forced == ID_GENERIC) return config(ID_GENERIC);       // (another forced configuration, which cannot run here, is ignored)
     // at most one tile per compute unit: two k groups, or one wavefront per SIMD would have nothing to hide its waits
     const int64_t tiles = unaligned_config(1)->grid(M, N), cus = chip().cus;
+    // Not one whole k step and many small tiles, whose rounds and edges the estimates below leave out.  us:
+    // f32, and f16 where rows of C begin at 128-byte lines, 256 or more tiles of 64 x 64: the element-wise kernel (its steps are 32 deep and
+    // its lanes store consecutive elements) -> the estimates' choice: f32 (906,3068,9) 10.7 -> 14.1, (292,7114,13) 9.8 -> 13.5,
+    // (1932,1511,36) 12.0 -> 14.9, (796,1429,11) 8.4 -> 8.5; f16 (567,2278,26) 7.2 -> 10.8 and (1440,1016,10) 6.8 -> 9.3 at
+    // a pitch of 64 elements' multiples.  With K < 24 also where a second round of 128 x 128 tiles would be
+    // less than a third full: (2566,1582,9) 12.3 -> 15.5, (1204,3377,17) 12.9 -> 14.7; but (2980,3319,12), 624 of them, 30 -> 24.
+    // Other f16, two or more tiles of 64 x 64 per compute unit: element-wise, the estimates' choice and this kernel: (1880,1563,12)
+    // 13.6, 15.0, 11.6, (314,6845,19) 12.5, 14.8, 11.4; fewer: (638,3205,9) 12.0, 12.3, 11.9, (1024,1157,34) 12.1, 8.7, 11.8.
+    const int64_t small_tiles = config(ID_GENERIC)->grid(M, N);
+    if (K < 64 && small_tiles >= cus && tiles >= 0 && tiles <= (K < 24 ? cus + cus / 3 : cus) && (!c_is_f16 || ldc % 64 == 0)) return config(ID_GENERIC);
     if (tiles < 0 || tiles > cus) return unaligned_config(1);
+    if (K < 64 && c_is_f16 && small_tiles >= 2 * cus) return unaligned_config(2);
     double us = 0;
     const int small = best_kslice(Operands::any, M, N, K, INT32_MAX, &us);
     return small >= 0 && us < (2 * tiles > cus ? 14.0 : 12.0) + 11.0 * (double)K / 1024.0 ? kslice_config(small, true) : unaligned_config(2);
@@ -509,7 +520,7 @@ int run(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, int64_t ld
     a.A = (const half_t*)A; a.lda = lda; a.B = (const half_t*)B; a.ldb = ldb; a.C = C; a.ldc = ldc;
     a.c_is_f16 = c_is_f16; a.stream = (hipStream_t)stream;
     a.k_split = plan.k_split;
-    const GemmConfigDesc* first = plan.id == ID_GENERIC ? any_shape_kernel(M, N, K, lda, ldb) : config(plan.id);
+    const GemmConfigDesc* first = plan.id == ID_GENERIC ? any_shape_kernel(c_is_f16, M, N, K, lda, ldb, ldc) : config(plan.id);
     const int rc1 = first->launch(a);
     if (rc1 != GEMM_F16_OK || plan.rows1 == M) return rc1;
     a.k_split = 0;
@@ -633,7 +644,7 @@ int gemm_f16_query_config(int c_is_f16, int64_t M, int64_t N, int64_t K, const v
     if (rc != GEMM_F16_OK) return rc;
     const Plan plan = select_plan(c_is_f16, M, N, K, a, lda, b, ldb, ldc, Form::plain);
     if (M == 0 || N == 0 || K == 0) { fill_desc(plan.id, 0, out); return GEMM_F16_OK; }
-    const GemmConfigDesc* first = plan.id == ID_GENERIC ? any_shape_kernel(M, N, K, lda, ldb) : config(plan.id);
+    const GemmConfigDesc* first = plan.id == ID_GENERIC ? any_shape_kernel(c_is_f16, M, N, K, lda, ldb, ldc) : config(plan.id);
     int64_t g = first->grid(plan.rows1, N);
     if (g < 0) return GEMM_F16_ERR_SIZE;
     if (plan.rows1 < M) {
