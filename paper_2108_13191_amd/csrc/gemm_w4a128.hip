@@ -41,10 +41,17 @@ __device__ __forceinline__ const char* uniform_ptr128(const void* ptr)
 }
 
 template <typename CT, bool SPLIT>
-__global__ __launch_bounds__(256) void gemm_w4a128_kernel(const TiledParams p)
+__global__ __launch_bounds__(256) void gemm_w4a128_kernel(const TiledParams params)
 {
     __shared__ __attribute__((aligned(1024))) char smem[W4A128_LDS];
     const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
+
+    // The split form reads its parameters all at once: in the order of their use it waited for scalar
+    // loads four times in a row, 0.45 us of a call ((952,8,7376) f32 13.2 us, at once 12.3).
+    TiledParams p = params;
+    if constexpr (SPLIT)
+        asm volatile("" : "+s"(p.M), "+s"(p.N), "+s"(p.K), "+s"(p.A), "+s"(p.lda), "+s"(p.B), "+s"(p.ldb), "+s"(p.C), "+s"(p.ldc),
+                          "+s"(p.tiles_m), "+s"(p.tiles_n), "+s"(p.group_m), "+s"(p.num_xcd), "+s"(p.k_split));
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
