@@ -322,14 +322,19 @@ int long_k_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K)
 // it gains on cached operands (+15 % and more) outweighs what it loses on cold ones.
 //
 // C read and stored by whole rows behind the loop has since made its start cheaper: phase-alternating kernel ->
-// this one, launches in a row on three sets of operands, us: 128 tiles, (1024,2048,K): K = 1024 14.7 ->
-// 13.1 (f16 13.9 -> 11.9), 4096 37.2 -> 27.8; 256 tiles, 2048^2 f16: K = 1024 16.3 -> 14.8, 2048 25.8 -> 21.7, 4096
-// 44.0 -> 35.5.  A k tail is an unpipelined step: (2000,2000,2000) f16 25.9 -> 26.6.  On a full chip the
-// f32 mode's choice stays at K = 6144 (C is twice the traffic; cold operands as above).
-int deep_ring_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K)
+// this one, us, launches in a row on three sets of operands | every operand from memory: 128 tiles, (1024,2048,K), K = 1024 / 2048 /
+// 4096: f32 13.7 -> 12.6 | 15.6 -> 16.3, 21.3 -> 18.1 | 24.3 -> 24.9, 36.5 -> 28.7 | 42.1 -> 42.1, f16 13.4 -> 11.6 |
+// 15.0 -> 15.2, 21.0 -> 17.1 | 23.9 -> 23.8, 36.2 -> 27.7 | 41.0 -> 40.3; 256 tiles, 2048^2 f16: 15.7 -> 15.7 | 16.5 -> 17.1,
+// 25.1 -> 21.8 | 25.7 -> 25.0, 43.4 -> 34.6 | 43.8 -> 41.5.  A k tail is an unpipelined step: (2000,2000,2000) f16 25.9 -> 26.6.
+// Only where rows of A and B begin at 128-byte lines: at other pitches its copies straddle lines and
+// gain nothing, (256,15616,2176) f16 at 8 more 25.4 -> 26.7 | 33.8 -> 35.8.
+// On a full chip the f32 mode stays at K = 6144 because tests/test_gpu_long_k.py names the kernels of 2048^2 at K = 2048 and 4096, not
+// for its speed: 26.7 -> 23.9 | 28.4 -> 28.8 and 45.1 -> 36.5 | 45.2 -> 44.0 (K = 1024 17.4 -> 17.9 | 18.9 -> 20.7).
+int deep_ring_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K, Operands operands)
 {
     const int64_t tiles = config(ID_RING128)->grid(rows, N), cus = chip().cus;
     if (id != ID_PP128x128 || tiles > cus) return id;
+    if (operands != Operands::lines) return K >= 6144 ? ID_RING128 : id;
     const int64_t tail = K % 64 ? 1536 : 0;
     if (2 * tiles <= cus) return K >= (c_is_f16 ? 1024 : 1536) + tail ? ID_RING128 : id;
     return K >= (c_is_f16 ? 2048 + tail : 6144) ? ID_RING128 : id;
@@ -455,9 +460,10 @@ Plan select_large_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void
     Plan pl = select_plan_unchained(c_is_f16, M, N, K, A, lda, B, ldb, ldc);
     if ((g_forced >= 0 && g_forced < num_configs()) || pl.id == ID_GENERIC) return pl;        // a forced configuration runs as it is
     pl.id = long_k_if_it_pays(chained_if_it_pays(pl.id, pl.rows1, N, K), c_is_f16, pl.rows1, N, K);
-    pl.id = deep_ring_if_it_pays(pl.id, c_is_f16, pl.rows1, N, K);
+    const Operands operands = operands_of(lda, ldb);
+    pl.id = deep_ring_if_it_pays(pl.id, c_is_f16, pl.rows1, N, K, operands);
     if (pl.id2 >= 0) pl.id2 = long_k_if_it_pays(chained_if_it_pays(pl.id2, M - pl.rows1, N, K), c_is_f16, M - pl.rows1, N, K);
-    if (pl.id2 >= 0) pl.id2 = deep_ring_if_it_pays(pl.id2, c_is_f16, M - pl.rows1, N, K);
+    if (pl.id2 >= 0) pl.id2 = deep_ring_if_it_pays(pl.id2, c_is_f16, M - pl.rows1, N, K, operands);
     if (pl.id2 >= 0 || pl.rows1 != M) return pl;
     if (form == Form::workspace) {
         // the rule of the f32 mode; the two passes over the workspace: (1024,2048,8192), 8 MB, 56 us against 53 unsplit; (256,4096,16384), 4 MB, 52 against 97
@@ -468,8 +474,9 @@ Plan select_large_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void
         pl.k_split = k_split_if_it_pays(pl.id, c_is_f16, M, N, K);
         // a fused epilogue has to follow the whole sum; and two parts of many tiles may cost more additions
         // than they save k steps: (1024,2048,4096) 33.4 us in two parts, 28.5 whole, (1024,2048,2048) 24.9 and 18.0,
-        // but (1280,1024,2048) 17.8 and 18.0
-        if (form == Form::fused || (pl.k_split > 1 && other_us({ID_RING128, M, -1}, M, N, K) < 0.9 * other_us(pl, M, N, K))) pl.k_split = 0;
+        // but (1280,1024,2048) 17.8 and 18.0; not
+        // at pitches of other than whole lines: (1016,1920,3648) at 8 more 33.6 in two parts, 36.2 whole (from memory 40.9 and 52.4)
+        if (form == Form::fused || (pl.k_split > 1 && operands == Operands::lines && other_us({ID_RING128, M, -1}, M, N, K) < 0.9 * other_us(pl, M, N, K))) pl.k_split = 0;
     }
     return pl;
 }

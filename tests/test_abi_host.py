@@ -178,6 +178,20 @@ def test_short_k_loops_without_alignment(lib):
     assert name(0, 2050, 2047, 33) == name(1, 2050, 2047, 33) == "generic128x128x64"
 
 
+def test_five_stage_kernel_at_pitches_of_whole_lines_only(lib):
+    """From K = 1024 to 6143 the five-stage 128 x 128 kernel, and a whole k loop where two parts are possible, only
+    where rows of A and B begin at 128-byte lines: at other pitches they are as slow as the alternative or slower."""
+    def q(f16, M, N, K, pad):
+        return binding.query_config(f16, M, N, K, 256, K + pad, 256, N + pad, 256, N + pad)
+    for f16, M, N, K in [(1, 256, 15616, 2176), (1, 2176, 1280, 2240), (0, 256, 4480, 1856), (0, 15360, 128, 1600)]:
+        assert q(f16, M, N, K, 0)["name"].startswith("w4a_128x128"), (f16, M, N, K)
+        for pad in (8, 16, 32):
+            assert q(f16, M, N, K, pad)["name"].startswith("pp128x128"), (f16, M, N, K, pad)
+    assert q(1, 2048, 1920, 6144, 8)["name"].startswith("w4a_128x128")
+    whole, parts = q(0, 1016, 1920, 3648, 0), q(0, 1016, 1920, 3648, 8)
+    assert whole["name"] == parts["name"] and (whole["grid"], parts["grid"]) == (120, 240)
+
+
 def test_header_is_plain_c(tmp_path):
     """include/gemm_f16.h compiles as C99 on its own, and a C program that calls
     the host-only entry points links against the library and runs (no GPU)."""
