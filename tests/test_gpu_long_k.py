@@ -237,7 +237,7 @@ def test_half_precision_mode_cut_along_k(oracle_mod):
     unsplit, with the same integers.  The problems of few rows have a B that takes one launch
     longer to stream than the parts."""
     from gpu_util import DevMat
-    cases = [(12, 1032, 8200), (6, 600, 9056), (54, 536, 8904), (237, 1608, 14320), (67, 448, 11920)]
+    cases = [(12, 1032, 8200), (6, 600, 9056), (54, 536, 8904), (30, 8496, 4168), (237, 1608, 14320), (67, 448, 11920)]
     for idx, (M, N, K) in enumerate(cases):
         need = binding.gemm_f16_f16acc_workspace_bytes(M, N, K)
         assert need == M * N * 4, (M, N, K, need)
