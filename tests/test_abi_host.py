@@ -158,6 +158,7 @@ def test_short_k_loops_on_many_small_tiles(lib):
         assert name(f16, M, N, K).startswith("pp128x128"), (f16, M, N, K)
     for f16, M, N, K in [(0, 256, 256, 256), (1, 24, 24, 24), (0, 567, 648, 232), (1, 320, 2304, 192), (1, 416, 256, 216), (1, 64, 4200, 64)]:
         assert name(f16, M, N, K).startswith("ks"), (f16, M, N, K)
+    assert binding.query_config(1, 600, 1664, 592, 256, 600, 256, 1672, 256, 1672)["name"].startswith("pp128x128") and name(1, 88, 9592, 832).startswith("pp128x128")
 
 
 def test_short_k_loops_without_alignment(lib):
