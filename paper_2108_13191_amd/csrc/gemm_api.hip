@@ -188,12 +188,13 @@ const GemmConfigDesc* any_shape_kernel(int c_is_f16, int64_t M, int64_t N, int64
     // f32, and f16 where rows of C begin at 128-byte lines, 256 or more tiles of 64 x 64: the element-wise kernel (its steps are 32 deep and
     // its lanes store consecutive elements) -> the estimates' choice: f32 (906,3068,9) 10.7 -> 14.1, (292,7114,13) 9.8 -> 13.5,
     // (1932,1511,36) 12.0 -> 14.9, (796,1429,11) 8.4 -> 8.5; f16 (567,2278,26) 7.2 -> 10.8 and (1440,1016,10) 6.8 -> 9.3 at
-    // a pitch of 64 elements' multiples.  With K < 24 also where a second round of 128 x 128 tiles would be
-    // less than a third full: (2566,1582,9) 12.3 -> 15.5, (1204,3377,17) 12.9 -> 14.7; but (2980,3319,12), 624 of them, 30 -> 24.
+    // a pitch of 64 elements' multiples.  Also where a second round of 128 x 128 tiles would hardly have begun, with
+    // K < 24 up to a third of it: (2566,1582,9) 12.3 -> 15.5, (1204,3377,17) 12.9 -> 14.7, (3668,1040,45), 261 of them, 12.3 -> 14.6;
+    // but (1023,4681,56), 296, 26.7 -> 20.2, (2980,3319,12), 624, 30 -> 24.
     // Other f16, two or more tiles of 64 x 64 per compute unit: element-wise, the estimates' choice and this kernel: (1880,1563,12)
     // 13.6, 15.0, 11.6, (314,6845,19) 12.5, 14.8, 11.4; fewer: (638,3205,9) 12.0, 12.3, 11.9, (1024,1157,34) 12.1, 8.7, 11.8.
     const int64_t small_tiles = config(ID_GENERIC)->grid(M, N);
-    if (K < 64 && small_tiles >= cus && tiles >= 0 && tiles <= (K < 24 ? cus + cus / 3 : cus) && (!c_is_f16 || ldc % 64 == 0)) return config(ID_GENERIC);
+    if (K < 64 && small_tiles >= cus && tiles >= 0 && tiles <= cus + (K < 24 ? cus / 3 : cus / 16) && (!c_is_f16 || ldc % 64 == 0)) return config(ID_GENERIC);
     if (tiles < 0 || tiles > cus) return unaligned_config(1);
     if (K < 64 && c_is_f16 && small_tiles >= 2 * cus) return unaligned_config(2);
     double us = 0;

@@ -167,7 +167,7 @@ def test_short_k_loops_without_alignment(lib):
     problems the 128 x 128 one."""
     name = lambda f16, M, N, K, pad=0: binding.query_config(f16, M, N, K, 2, K, 2, N, 4, N + pad)["name"]
     for M, N, K in [(810, 2922, 10), (906, 3068, 9), (292, 7114, 13), (1932, 1511, 36), (2310, 840, 10), (1916, 1513, 52), (1024, 1021, 63),
-                    (2566, 1582, 9), (1204, 3377, 17), (2033, 2571, 11)]:
+                    (2566, 1582, 9), (1204, 3377, 17), (2033, 2571, 11), (3668, 1040, 45), (5481, 688, 39)]:
         assert name(0, M, N, K) == "generic64x64x32", (M, N, K)
     for M, N, K, pad in [(567, 2278, 26, 26), (644, 1716, 9, 12), (1440, 1016, 10, 8), (1431, 2722, 12, 30), (1846, 1276, 21, 4)]:
         assert name(1, M, N, K, pad) == "generic64x64x32" != name(1, M, N, K), (M, N, K)
@@ -175,8 +175,8 @@ def test_short_k_loops_without_alignment(lib):
         assert name(1, M, N, K) == "generic128x128x64_k2", (M, N, K)
     for M, N, K in [(1024, 1021, 64), (960, 1021, 63), (130, 141, 9)]:
         assert name(0, M, N, K).startswith("generic_ks") and name(1, M, N, K).startswith("generic_ks"), (M, N, K)
-    assert name(0, 2980, 3319, 12) == name(0, 1204, 3377, 24) == name(1, 2566, 1582, 9) == "generic128x128x64"
-    assert name(0, 2050, 2047, 33) == name(1, 2050, 2047, 33) == "generic128x128x64"
+    assert name(0, 2980, 3319, 12) == name(0, 1204, 3500, 24) == name(1, 2566, 1582, 9) == "generic128x128x64"
+    assert name(0, 2306, 2047, 33) == name(1, 2306, 2047, 33) == "generic128x128x64"
 
 
 def test_five_stage_kernel_at_pitches_of_whole_lines_only(lib):
