@@ -14,7 +14,7 @@ from paper_2108_13191_amd import binding, workloads as wl   # noqa: E402
 from gpu_util import DevMat, assert_close                    # noqa: E402
 
 
-def _both(A, B, C0, ldc):
+def _both(A, B, C0, ldc, lent=None):
     """C of the static-workspace entry point and of the lent-workspace one, through the C ABI."""
     M, K = A.shape
     N = B.shape[1]
@@ -26,7 +26,7 @@ def _both(A, B, C0, ldc):
         if static:
             rc = binding.gemm_f16_f16acc_static_workspace(M, N, K, dA.ptr, dA.ld, dB.ptr, dB.ld, dC.ptr, dC.ld, 0)
         else:
-            ws = torch.full((need // 4,), float("nan"), device="cuda")
+            ws = torch.full((need // 4,), float("nan"), device="cuda") if lent is None else lent
             rc = binding.gemm_f16_f16acc_workspace(M, N, K, dA.ptr, dA.ld, dB.ptr, dB.ld, dC.ptr, dC.ld, ws, need, 0)
         assert rc == binding.OK, binding.strerror(rc)
         torch.cuda.synchronize()
@@ -49,6 +49,16 @@ def test_static_workspace_entry_point_matches_the_workspace_one(oracle_mod):
         Cref, S = oracle_mod.gemm_f16(A, B, C0)
         assert_close(got_static, Cref, S, C0, "f16", what=f"static workspace {(M, N, K)}")
         assert_close(got_lent, Cref, S, C0, "f16", what=f"lent workspace {(M, N, K)}")
+    # problems whose k loop is cut (the lent memory holds sums afterwards): two calls in a row on the one array,
+    # the second smaller, then the first again
+    for idx, (M, N, K) in enumerate([(237, 1608, 14320), (67, 448, 11920), (237, 1608, 14320)]):
+        A, B, _ = wl.make_inputs(M, N, K, "int2", "zeros", seed=1320 + idx, c_dtype=np.float16)
+        C0 = np.random.default_rng(idx).integers(-4, 5, size=(M, N)).astype(np.float16)
+        lent = torch.full((M * N,), float("nan"), device="cuda")
+        got_static, got_lent = _both(A, B, C0, N + 8, lent)
+        assert not bool(torch.isnan(lent).any()), f"{(M, N, K)} was not cut"
+        Cref, _ = oracle_mod.gemm_f16(A, B, C0)
+        assert np.array_equal(got_static, got_lent) and np.array_equal(got_static, Cref.astype(np.float16)), f"ints {(M, N, K)}"
     # a problem that runs unsplit takes the ordinary path (and the array is not needed)
     A, B, C0 = wl.make_inputs(200, 264, 328, "int2", "zeros", seed=9, c_dtype=np.float16)
     dA, dB, dC = DevMat(A, nan_canary=True), DevMat(B, nan_canary=True), DevMat(C0)
