@@ -448,9 +448,10 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
         other += 5.0;                                                // the passes before and after
         // A wide B that no call has left in the caches (split -> small tiles, us; its latency is spread over
         // more compute units by the split): (12,1032,8200) 17.2 -> 28.7 (in the caches 13.8 -> 17.9), (9,1168,5208) 16.5 -> 18.6,
-        // (54,536,8904) 21.8 -> 24.6, (30,8496,4168) 26.0 -> 28.5, but (5,4352,3464) 16.9 -> 14.3, (62,3440,6120) 25.9 -> 24.7; with the
-        // larger dimension in A it costs less: (1888,8,8264) 23.7 -> 14.7
-        if (N > M) us += 1.4 * (double)K / 1024.0;
+        // (30,8496,4168) 26.0 -> 28.5, but (5,4352,3464) 16.9 -> 14.3; with more rows, tiles above one another share it:
+        // (54,536,8904) 21.8 -> 24.6, (98,896,7192) 23.5 -> 18.0, (96,7832,4608) 35.6 -> 29.5, (503,1160,4728) 30.0 -> 25.6; with the larger dimension
+        // in A it costs less: (1888,8,8264) 23.7 -> 14.7
+        if (N > M) us += (M <= 32 ? 1.4 : M <= 128 ? 0.5 : 0.0) * (double)K / 1024.0;
     }
     return small >= 0 && us < other ? ID_KSLICE + small : -1;
 }
