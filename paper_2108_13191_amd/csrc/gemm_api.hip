@@ -133,10 +133,10 @@ bool aligned_for_tiled(int64_t N, int64_t K, const void* A, int64_t lda, const v
 // beyond what the last-level cache keeps between calls: strips of B 64 or 128 bytes wide come out of
 // the memory at 2.7 TB/s ((128,8192,8192) 64x64 49 us, its k loop from the caches 30).
 // Rows that begin within a 128-byte line: (1024,1024,2048) 64x64 11.9 us at pitches of 64 elements' multiples, 14.9 at others.
-// What a short k loop does not hide: up to 1.5 us for the edges of C in f16 (K < 320, aligned), and up to
-// 3 where there is more than one round of workgroups (K < 1024) -- phase-alternating kernel -> small tiles, us:
+// What a short k loop does not hide: up to 1.5 us for tiles of f16 C with ragged columns (aligned, K < 320), and up
+// to 3 where there is more than one round of workgroups (K < 1024; 1.5 behind the slower loads of any alignment) -- phase-alternating kernel -> small tiles, us:
 // (144,6768,48) f32 5.7 -> 7.7, (212,4464,24) f16 6.0 -> 7.7, (88,8448,256) f16 7.0 -> 7.9, (2618,200,32) f16
-// 6.1 -> 6.8, (88,9792,320) f16 7.6 -> 9.1, (600,1664,592) f16 at a pitch of 8 more 11.7 -> 12.6, (88,9592,832) f16 11.8 -> 12.5; 128 x 128 at any alignment -> small tiles (685,3452,95) f16 9.9 -> 13.2; but (567,648,232) f32 7.5 -> 4.9, (320,2304,192) f16 6.6 -> 5.6.
+// 6.1 -> 6.8, (88,9792,320) f16 7.6 -> 9.1, (600,1664,592) f16 at a pitch of 8 more 11.7 -> 12.6, (88,9592,832) f16 11.8 -> 12.5; 128 x 128 at any alignment -> small tiles (685,3452,95) f16 9.9 -> 13.2; but (567,648,232) f32 7.5 -> 4.9, (1242,448,32) f16 5.7 -> 5.0.
 enum class Operands { lines, chunks, any };              // rows begin at 128-byte lines; at 16 bytes; anywhere
 Operands operands_of(int64_t lda, int64_t ldb) { return lda % 64 || ldb % 64 ? Operands::chunks : Operands::lines; }
 struct KsliceCand { int per_cu; double fixed1, rate1, fixed2, rate2; };
@@ -145,7 +145,7 @@ const KsliceCand kKsliceCands[NUM_KSLICE] = {
 
 double operand_mb(int64_t M, int64_t N, int64_t K) { return 2e-6 * (double)K * ((double)M + (double)N); }
 
-double kslice_us(int index, Operands form, int64_t M, int64_t N, int64_t K)
+double kslice_us(int index, int c_is_f16, Operands form, int64_t M, int64_t N, int64_t K)
 {
     const KsliceCand& c = kKsliceCands[index];
     const int64_t g = kslice_config(index, false)->grid(M, N);
@@ -153,17 +153,17 @@ double kslice_us(int index, Operands form, int64_t M, int64_t N, int64_t K)
     const int64_t cus = chip().cus, full = g / (cus * c.per_cu), left = g % (cus * c.per_cu);
     const double k = (double)K / 1024.0 * (form == Operands::lines ? 1.0 : form == Operands::chunks ? 1.25 : 1.75), f = form == Operands::any ? 1.15 : 1.0, mb = operand_mb(M, N, K);
     const double round1 = f * c.fixed1 + k * c.rate1, round2 = f * c.fixed2 + k * c.rate2;
-    const double short_k = (K < 320 && form != Operands::any ? 1.5 : 0.0) + (K < 1024 && g > cus * c.per_cu ? 3.0 : 0.0);
+    const double short_k = (c_is_f16 && K < 320 && N % 64 && form != Operands::any ? 1.5 : 0.0) + (K < 1024 && g > cus * c.per_cu ? (form == Operands::any ? 1.5 : 3.0) : 0.0);
     return 1.6 + short_k + (double)full * round2 + (left == 0 ? 0.0 : left <= cus ? round1 : round2) + (mb > 80.0 ? 0.19 * mb : 0.0);
 }
 
 // The tile with the least estimated time among those with at most max_grid workgroups (-1: none).
-int best_kslice(Operands form, int64_t M, int64_t N, int64_t K, int64_t max_grid, double* us)
+int best_kslice(int c_is_f16, Operands form, int64_t M, int64_t N, int64_t K, int64_t max_grid, double* us)
 {
     int best = -1;
     for (int i = 0; i < NUM_KSLICE; i++) {
         const int64_t g = kslice_config(i, false)->grid(M, N);
-        const double t = kslice_us(i, form, M, N, K);
+        const double t = kslice_us(i, c_is_f16, form, M, N, K);
         if (g < 0 || g > max_grid || t < 0) continue;
         if (best < 0 || t < *us) { best = i; *us = t; }
     }
@@ -198,7 +198,7 @@ const GemmConfigDesc* any_shape_kernel(int c_is_f16, int64_t M, int64_t N, int64
     if (tiles < 0 || tiles > cus) return unaligned_config(1);
     if (K < 64 && c_is_f16 && small_tiles >= 2 * cus) return unaligned_config(2);
     double us = 0;
-    const int small = best_kslice(Operands::any, M, N, K, INT32_MAX, &us);
+    const int small = best_kslice(c_is_f16, Operands::any, M, N, K, INT32_MAX, &us);
     return small >= 0 && us < (2 * tiles > cus ? 14.0 : 12.0) + 11.0 * (double)K / 1024.0 ? kslice_config(small, true) : unaligned_config(2);
 }
 
@@ -443,7 +443,7 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
         if (c_is_f16 && (skinny || K > 6144) && !(M <= 32 && N * K >= (int64_t)1 << 25)) max_grid = config(ID_T64)->grid(M, N);
     }
     double us = 0;
-    const int small = best_kslice(operands, M, N, K, max_grid, &us);
+    const int small = best_kslice(c_is_f16, operands, M, N, K, max_grid, &us);
     if (form == Form::workspace && pl.k_split > 1) {
         other += 5.0;                                                // the passes before and after
         // A wide B that no call has left in the caches (split -> small tiles, us; its latency is spread over

@@ -156,7 +156,7 @@ def test_short_k_loops_on_many_small_tiles(lib):
     name = lambda f16, M, N, K: binding.query_config(f16, M, N, K, 256, K, 256, N, 256, N)["name"]
     for f16, M, N, K in [(0, 144, 6768, 48), (1, 212, 4464, 24), (1, 88, 8448, 256), (1, 2618, 200, 32), (1, 357, 2488, 32), (1, 9126, 72, 144), (1, 100, 9264, 32), (1, 88, 9792, 320)]:
         assert name(f16, M, N, K).startswith("pp128x128"), (f16, M, N, K)
-    for f16, M, N, K in [(0, 256, 256, 256), (1, 24, 24, 24), (0, 567, 648, 232), (1, 320, 2304, 192), (1, 416, 256, 216), (1, 64, 4200, 64)]:
+    for f16, M, N, K in [(0, 256, 256, 256), (1, 24, 24, 24), (0, 567, 648, 232), (1, 320, 2304, 192), (1, 1242, 448, 32), (0, 2348, 224, 56), (0, 756, 912, 16), (1, 416, 256, 216), (1, 64, 4200, 64)]:
         assert name(f16, M, N, K).startswith("ks"), (f16, M, N, K)
     assert binding.query_config(1, 600, 1664, 592, 256, 600, 256, 1672, 256, 1672)["name"].startswith("pp128x128") and name(1, 88, 9592, 832).startswith("pp128x128")
 
