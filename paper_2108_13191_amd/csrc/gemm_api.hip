@@ -184,17 +184,20 @@ const GemmConfigDesc* any_shape_kernel(int c_is_f16, int64_t M, int64_t N, int64
     if (!tiled || g_forced == ID_GENERIC) return config(ID_GENERIC);       // (another forced configuration, which cannot run here, is ignored)
     // at most one tile per compute unit: two k groups, or one wavefront per SIMD would have nothing to hide its waits
     const int64_t tiles = unaligned_config(1)->grid(M, N), cus = chip().cus;
-    // Not one whole k step and many small tiles, whose rounds and edges the estimates below leave out.  us:
-    // f32, and f16 where rows of C begin at 128-byte lines, 256 or more tiles of 64 x 64: the element-wise kernel (its steps are 32 deep and
-    // its lanes store consecutive elements) -> the estimates' choice: f32 (906,3068,9) 10.7 -> 14.1, (292,7114,13) 9.8 -> 13.5,
-    // (1932,1511,36) 12.0 -> 14.9, (796,1429,11) 8.4 -> 8.5; f16 (567,2278,26) 7.2 -> 10.8 and (1440,1016,10) 6.8 -> 9.3 at
-    // a pitch of 64 elements' multiples.  Also where a second round of 128 x 128 tiles would hardly have begun, with
-    // K < 24 up to a third of it: (2566,1582,9) 12.3 -> 15.5, (1204,3377,17) 12.9 -> 14.7, (3668,1040,45), 261 of them, 12.3 -> 14.6;
-    // but (1023,4681,56), 296, 26.7 -> 20.2, (2980,3319,12), 624, 30 -> 24.
+    // Not one whole k step and many small tiles, whose rounds and edges the estimates below leave out; element-wise -> the
+    // estimates' choice, us.  f32: the element-wise kernel (its steps are 32 deep and its lanes store consecutive elements)
+    // below K = 32 on more 64 x 64 tiles than compute units, below 48 on two to three times as many: (906,3068,9) 10.7 -> 14.1, (292,7114,13)
+    // 9.8 -> 13.5, (1932,1511,36) 12.0 -> 14.9, but (1381,854,42) 10.2 -> 8.6, (2440,1333,39) 13.8 -> 12.3, (990,973,27), one round, 7.5 -> 6.0.
+    // f16: where rows of C begin at 128-byte lines, K < 40: (567,2278,26) 7.2 -> 10.8 and (1440,1016,10) 6.8 -> 9.3 at a
+    // pitch of 64 elements' multiples, but (1046,1728,54) 9.0 -> 8.7.  Also where a second round of 128 x 128 tiles would hardly
+    // have begun: (2566,1582,9) 12.3 -> 15.5, (1204,3377,17) 12.9 -> 14.7, (3668,1040,45) 12.3 -> 14.6 on 261 to 273 of
+    // them; but (1023,4681,56), 296, 26.7 -> 20.2, (2980,3319,12), 624, 30 -> 24.
     // Other f16, two or more tiles of 64 x 64 per compute unit: element-wise, the estimates' choice and this kernel: (1880,1563,12)
     // 13.6, 15.0, 11.6, (314,6845,19) 12.5, 14.8, 11.4; fewer: (638,3205,9) 12.0, 12.3, 11.9, (1024,1157,34) 12.1, 8.7, 11.8.
     const int64_t small_tiles = config(ID_GENERIC)->grid(M, N);
-    if (K < 64 && small_tiles >= cus && tiles >= 0 && tiles <= cus + (K < 24 ? cus / 3 : cus / 16) && (!c_is_f16 || ldc % 64 == 0)) return config(ID_GENERIC);
+    const bool element_wise = c_is_f16 ? K < 40 && ldc % 64 == 0 && small_tiles > cus
+                                       : (K < 32 && small_tiles > cus) || (K < 48 && ((small_tiles >= 2 * cus && small_tiles < 3 * cus) || tiles > cus));
+    if (element_wise && tiles >= 0 && tiles <= cus + cus / 10) return config(ID_GENERIC);
     if (tiles < 0 || tiles > cus) return unaligned_config(1);
     if (K < 64 && c_is_f16 && small_tiles >= 2 * cus) return unaligned_config(2);
     double us = 0;
