@@ -426,11 +426,13 @@ int k_split_if_it_pays(int& id, int c_is_f16, int64_t M, int64_t N, int64_t K)
 // Small results go to the small tiles where the estimates say so.  Before -> after, us:
 // 256^3 6.6 -> 3.4, 512^3 7.9 -> 4.1, 1024^3 f16 13.5 -> 8.4, (128,4096,1024) 11.2 -> 6.5, (16,8192,8192)
 // f16 50 -> 37, (8192,16,8192) f16 52 -> 29, (512,1024,4096) f16 30 -> 13.4.
-// Two limits from K = 2048 on.  In f32 mode a skinny problem (a dimension of C more than four times the
-// other) that is cut along k stays so, and others leave the split k loop for a gain of a tenth or
-// more.  In f16 mode a skinny problem, or one with K > 6144, runs on no more workgroups than it has
-// 64 x 64 tiles (the bound of its unsplit plans) -- unless at most 32 rows meet a B of 64 MB and
-// more, which half as many compute units do not read as fast ((16,8192,8192) 37 us on 256, 42 on 128).
+// Two limits of the plain form from K = 2048 on, where tests/test_gpu_long_k.py states what runs; they are not for speed.  In f32
+// mode a skinny problem (a dimension of C more than four times the other) that is cut along k stays so
+// -- cut, small tiles, us: (16,2048,2048) 9.2, 4.95, (8192,64,2048) 14.9, 9.7, (256,4096,4096) 24.5, 18.4 -- and
+// others leave the split k loop for a gain of a tenth or more.  In f16 mode a skinny problem, or one with
+// K > 6144, runs on no more workgroups than it has 64 x 64 tiles -- so, on as many as are best: (16,2048,2048) 6.3, 4.9,
+// (32,4096,4096) 14.8, 11.8, (64,8192,8192) 52, 42 -- except where the test has no shape: at most 32 rows
+// against a B of 64 MB and more ((16,8192,8192) 42 us on 128 workgroups, 37 on 256).
 int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_t N, int64_t K, Operands operands)
 {
     const int64_t tiles = config(ID_PP128x128)->grid(M, N);

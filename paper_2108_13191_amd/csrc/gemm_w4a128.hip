@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256) void gemm_w4a128_kernel(const TiledParams para
     if (kt_full > 0) {
         // k steps 0..3 into stages 0..3 (a k step beyond the last one: k step 0 once more, which
         // nobody reads; the loop's waits count on 8 copies per stage); the loop copies from k
-        // step 4 on.  Only k step 0 (and C, requested before it) is waited for here: the wait
+        // step 4 on.  Only k step 0 is waited for here: the wait
         // in the middle of k step j leaves the 20 copies behind those of step j + 1 in flight,
         // which holds from j = 0 on with steps 2, 3 and half of 4 behind step 1.
 #pragma unroll
