@@ -201,7 +201,8 @@ const char* gemm_strerror(int code);
  * the rest.
  */
 typedef struct gemm_f16_config {
-    int32_t id;          /* index into the library's configuration table */
+    int32_t id;          /* index into the library's configuration table; 0, unless forced, for every problem without alignment:
+                            the other fields and the name say which kernel of that family runs */
     int32_t block_m;     /* workgroup tile rows */
     int32_t block_n;     /* workgroup tile columns */
     int32_t block_k;     /* k extent staged in LDS per main-loop step */

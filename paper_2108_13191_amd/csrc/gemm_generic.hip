@@ -3,8 +3,10 @@
 // touched and the k tail is zero-filled in both operands.  It follows the
 // two-level recipe of the paper's Algorithm "Two-level tiled tensor core
 // Matmul" in its plainest form (one LDS buffer, two barriers per step).  It is
-// what is left for N or K below 8 and pitches above 2^22 elements; other
-// unaligned problems take gemm_unaligned.hip.
+// what is left for N or K below 8, pitches above 2^22 elements and some
+// problems of not one whole k step of the others (any_shape_kernel in
+// gemm_api.hip); other unaligned problems take gemm_unaligned.hip or
+// gemm_kslice.hip.
 #include "gemm_common.h"
 #include "../../include/gemm_f16.h"
 
