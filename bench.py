@@ -45,22 +45,36 @@ def algorithmic_bytes(M, N, K, c_bytes):
     return 2 * (M * K + K * N) + 2 * M * N * c_bytes
 
 
-def kernel_symbol(tile_name, mode, K=0):
-    """Name of the kernel as it shows in a rocprofv3 kernel trace."""
+# k steps in flight and workgroups per compute unit of the small tiles (template arguments of gemm_kslice_kernel)
+KSLICE_FORMS = {(16, 32): (2, 2), (32, 32): (1, 2), (16, 64): (1, 2), (32, 64): (1, 1), (64, 64): (1, 1)}
+
+
+def kernel_symbol(tile_name, mode, K=0, c_once=False, k_parts=False):
+    """Name of the kernel as it shows in a rocprofv3 kernel trace (c_once: C with the non-temporal
+    hint; k_parts: k loop cut into parts)."""
+    import re
     ct = "float" if mode == "f32" else "_Float16"
+    once = "true" if c_once else "false"
+    ks = re.match(r"(?:generic_)?ks(\d+)x(\d+)x64_k8$", tile_name)
+    if ks:
+        bm, bn = int(ks.group(1)), int(ks.group(2))
+        return f"gemm_kslice_kernel<{ct}, {bm}, {bn}, {KSLICE_FORMS[bm, bn][0]}, {KSLICE_FORMS[bm, bn][1]}>"
+    if tile_name.startswith("generic128"):
+        return f"gemm_unaligned_kernel<{ct}, {2 if tile_name.endswith('_k2') else 1}>"
     if tile_name.startswith("pp"):
         mi = 16 if "mi16" in tile_name else 32
         bm, bn = int(tile_name[2:5]), int(tile_name[6:9])
         tail = "true" if K % 64 else "false"
         if tile_name.endswith("_chain"):
-            return f"gemm_pp256_persistent_kernel<{ct}, {mi}, {tail}>"
+            return f"gemm_pp256_persistent_kernel<{ct}, {mi}, {tail}, {once}>"
         if tile_name.endswith("_stag"):
-            return f"gemm_pp_mixed_kernel<{ct}, {mi}, {tail}>"
-        return f"gemm_pp256_kernel<{ct}, {mi}, {'true' if K % 64 else 'false'}, {bm}, {bn}>"
+            return f"gemm_pp_mixed_kernel<{ct}, {mi}, {tail}, {once}>"
+        rowwise = tile_name.endswith("_rowwise")
+        return f"gemm_pp256_kernel<{ct}, {mi}, {tail}, {bm}, {bn}, {'true' if rowwise else 'false'}, {'false' if rowwise else once}>"
     if tile_name.startswith("ov"):
         return f"gemm_pp_overlap_kernel<{ct}>"
     if tile_name.startswith("w4a_128"):
-        return f"gemm_w4a128_kernel<{ct}>"
+        return f"gemm_w4a128_kernel<{ct}, {'true' if k_parts else 'false'}>"
     if tile_name.startswith("w4a_"):
         return f"gemm_w4a_kernel<{ct}>"
     if tile_name.startswith("w4_"):
@@ -68,9 +82,9 @@ def kernel_symbol(tile_name, mode, K=0):
     if tile_name.startswith("il"):
         return f"gemm_il256_kernel<{ct}>"
     if tile_name.startswith("generic"):
-        return f"gemm_generic_kernel<{ct}, {'true' if tile_name.endswith('_c_in_loop') else 'false'}>"
+        c_in_loop, per_slice = tile_name.endswith("_c_in_loop"), tile_name.endswith("_round_per_slice")
+        return f"gemm_generic_kernel<{ct}, {'true' if c_in_loop else 'false'}, {'true' if per_slice else 'false'}>"
     # t<BM>x<BN>x64_w<WM>x<WN>: template arguments BM, BN, waves along m, along n, LDS stages, C type
-    import re
     bm, bn, wm, wn = (int(x) for x in re.match(r"t(\d+)x(\d+)x\d+_w(\d+)x(\d+)", tile_name).groups())
     return f"gemm_tiled_kernel<{bm}, {bn}, {wm}, {wn}, {4 if bm == 64 else 2}, {ct}, {'false' if tile_name.endswith('_noswz') else 'true'}>"
 
@@ -321,7 +335,7 @@ def main():
         dA, dB, dC = sets[0]
         cfg = binding.query_config(mode != "f32", M, N, K, dA, dA.stride(0), dB, dB.stride(0), dC, dC.stride(0))
         if mode == "f16ws" and binding.gemm_f16_f16acc_workspace_bytes(M, N, K) > 0:
-            cfg["name"] = "w4a_128x128x64, k loop in parts through a workspace of M x N floats"
+            cfg["name"] = "k loop in parts through a workspace of M x N floats, or small tiles where these are faster"
         flops = 2.0 * M * N * K
         if cfg.get("split_rows"):
             cfg["plan"] = f"{cfg['name']} on rows 0..{cfg['split_rows'] - 1} + {binding.describe_config(cfg['id2'])['name']} on the rest"
@@ -371,9 +385,14 @@ def main():
         roofline = {"bound": "hbm", "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                     "frac": round(gbs / PEAK_HBM_GBS, 4), "traffic": None}
     roofline["traffic"], roofline["traffic_source"] = measured_traffic(r["cfg"]["name"], args.workload, args.mode)
-    kernels = kernel_symbol(r["cfg"]["name"], args.mode, K)
+    c_size = 4 if args.mode == "f32" else 2
+    rows1 = r["cfg"].get("split_rows") or M
+
+    def c_once(rows):                       # the library's rule for the hint on C (operands here are dense)
+        return 256 <= K < 4096 and rows * N * c_size >= 300e6 and N * c_size % 64 == 0
+    kernels = kernel_symbol(r["cfg"]["name"], args.mode, K, c_once(rows1), r["cfg"]["grid"] > -(-M // 128) * -(-N // 128))
     if r["cfg"].get("split_rows"):          # two launches: the time below is that of the pair
-        kernels += " + " + kernel_symbol(binding.describe_config(r["cfg"]["id2"])["name"], args.mode, K)
+        kernels += " + " + kernel_symbol(binding.describe_config(r["cfg"]["id2"])["name"], args.mode, K, c_once(M - rows1))
     roofline.update({"kernel": kernels, "avg_launch_ms": round(avg_launch_ms, 5),
                      "algorithmic_bytes": r["bytes"], "flops": 2 * M * N * K})
 

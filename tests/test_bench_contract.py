@@ -18,6 +18,34 @@ def test_more_than_one_gpu_is_refused():
     assert res.returncode != 0 and "one GPU" in (res.stderr + res.stdout)
 
 
+def test_kernel_names_of_every_configuration():
+    """bench.py reports the kernel of whatever configuration a workload takes: for every entry of both
+    libraries' tables, and the names that the any-shape family reports, its name is one that the library holds."""
+    import shutil
+    if shutil.which("nm") is None or shutil.which("c++filt") is None:
+        pytest.skip("no binutils")
+    sys.path.insert(0, ROOT)
+    import bench
+    from paper_2108_13191_amd import binding
+    with binding.library("ladder"):
+        names = [binding.describe_config(i)["name"] for i in range(binding.num_configs())]
+        names += [binding.query_config(False, *s, 2, s[2], 2, s[1], 4, s[1])["name"]
+                  for s in [(500, 501, 503), (1, 8, 9), (2001, 1999, 2003), (2177, 2049, 391), (9, 5, 7)]]
+    mangled = subprocess.run(["nm", binding.LADDER_LIB_PATH], capture_output=True, text=True, check=True).stdout
+    # (binutils may not know the mangling of _Float16: shown as the "half" that it knows)
+    held = subprocess.run(["c++filt"], input=mangled.replace("DF16_", "Dh"), capture_output=True, text=True, check=True).stdout
+    for name in names:
+        for mode in ("f32", "f16"):
+            if (name.endswith("_c_in_loop"), name.endswith("_round_per_slice")) in ((True, False), (False, True)):
+                if (mode == "f32") != name.endswith("_c_in_loop"):
+                    continue                                  # each of these two rows exists in one mode
+            for K in (64, 72):
+                for once in (False, True):
+                    for parts in (False, mode == "f32"):
+                        symbol = bench.kernel_symbol(name, mode, K, once, parts)
+                        assert "::" + symbol.replace("_Float16", "half") + "(" in held, (name, symbol)
+
+
 @pytest.mark.gpu
 def test_one_json_line_with_roofline_and_cpu_baseline():
     torch = pytest.importorskip("torch")
