@@ -176,18 +176,16 @@ __global__ __launch_bounds__(64 * KW, 2 * WG_PER_CU) void gemm_kslice_kernel(con
     const bool active = BM >= ROWS || c_row < BM;
     CT* const cptr = (CT*)p.C + (int64_t)(m0 + c_row) * p.ldc + first;
     ctx4 cin[PASSES];
-    float bias4[4];
+    float bias4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (p.bias) {
 #pragma unroll
-    for (int e = 0; e < 4; e++) bias4[e] = (p.bias && first + e >= nominal) ? (float)reinterpret_cast<const CT*>(p.bias)[first + e] : 0.0f;
+        for (int e = 0; e < 4; e++) bias4[e] = (float)reinterpret_cast<const CT*>(p.bias)[first + e];
+    }
+    // (reads stay in C: columns first .. first + 3 end by N, rows beyond M read the last one)
 #pragma unroll
     for (int ps = 0; ps < PASSES; ps++) {
-        const CT* src = cptr + (int64_t)(ps * ROWS) * p.ldc;
-        cin[ps] = ctx4{};
-        if (!edge) { if (active) cin[ps] = *reinterpret_cast<const ctx4*>(src); }
-        else if (active && m0 + c_row + ps * ROWS < p.M) {
-#pragma unroll
-            for (int e = 0; e < 4; e++) if (first + e >= nominal) cin[ps][e] = src[e];
-        }
+        const int row = m0 + c_row + ps * ROWS, down = (edge && row >= p.M) ? p.M - 1 - m0 - c_row : ps * ROWS;
+        cin[ps] = active ? *reinterpret_cast<const ctx4*>(cptr + (int64_t)down * p.ldc) : ctx4{};
     }
     asm volatile("" ::: "memory");
 
@@ -224,8 +222,9 @@ __global__ __launch_bounds__(64 * KW, 2 * WG_PER_CU) void gemm_kslice_kernel(con
 #pragma unroll
         for (int e = 0; e < 4; e++) o[e] = (CT)epilogue_value(s4[e] + (float)cin[ps][e], bias4[e], p.relu);     // f16: one rounding, to nearest even
         CT* const dst = cptr + (int64_t)(ps * ROWS) * p.ldc;
-        if (!edge) *reinterpret_cast<ctx4*>(dst) = o;
-        else if (m0 + c_row + ps * ROWS < p.M) {
+        const bool row_ok = !edge || m0 + c_row + ps * ROWS < p.M;
+        if (row_ok && (!edge || first >= nominal)) *reinterpret_cast<ctx4*>(dst) = o;
+        else if (row_ok) {
 #pragma unroll
             for (int e = 0; e < 4; e++) if (first + e >= nominal) dst[e] = o[e];
         }
