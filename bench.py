@@ -59,6 +59,8 @@ def kernel_symbol(tile_name, mode, K=0, c_once=False, k_parts=False):
     if ks:
         bm, bn = int(ks.group(1)), int(ks.group(2))
         return f"gemm_kslice_kernel<{ct}, {bm}, {bn}, {KSLICE_FORMS[bm, bn][0]}, {KSLICE_FORMS[bm, bn][1]}>"
+    if tile_name in ("generic256x256x64", "generic128x256x64"):
+        return f"gemm_unaligned_pp_kernel<{ct}, {tile_name[7:10]}>"
     if tile_name.startswith("generic128"):
         return f"gemm_unaligned_kernel<{ct}, {2 if tile_name.endswith('_k2') else 1}>"
     if tile_name.startswith("pp"):

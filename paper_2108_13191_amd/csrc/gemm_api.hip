@@ -27,7 +27,8 @@ enum {
     ID_KSLICE,         // + 0 .. 4: 16 x 32, 32 x 32, 16 x 64, 32 x 64, 64 x 64, eight wavefronts take the k steps in turn
     NUM_KSLICE = 5,
     ID_UNALIGNED = ID_KSLICE + NUM_KSLICE,     // + 0, 1: 128 x 128 at any alignment, one k group or two
-    NUM_PRODUCT = ID_UNALIGNED + 2
+    NUM_UNALIGNED = 4,                         // + 2, 3: 256 x 256 and 128 x 256, phase-alternating
+    NUM_PRODUCT = ID_UNALIGNED + NUM_UNALIGNED
 };
 
 const GemmConfigDesc kGeneric = {
@@ -57,6 +58,8 @@ const GemmConfigDesc* config(int id)
     case ID_RING128:   return deep_ring_config();
     case ID_KSLICE + 0: case ID_KSLICE + 1: case ID_KSLICE + 2: case ID_KSLICE + 3: case ID_KSLICE + 4: return kslice_config(id - ID_KSLICE, false);
     case ID_UNALIGNED + 0: case ID_UNALIGNED + 1: return unaligned_config(1 + id - ID_UNALIGNED);
+    case ID_UNALIGNED + 2: return unaligned_pp_config(256);
+    case ID_UNALIGNED + 3: return unaligned_pp_config(128);
 #ifdef GEMM_F16_LADDER
     case NUM_PRODUCT + 0: return tiled_config(128);
     case NUM_PRODUCT + 1: return tiled_config(256);
@@ -137,6 +140,7 @@ bool aligned_for_tiled(int64_t N, int64_t K, const void* A, int64_t lda, const v
 // to 3 where there is more than one round of workgroups (K < 1024; 1.5 behind the slower loads of any alignment) -- phase-alternating kernel -> small tiles, us:
 // (144,6768,48) f32 5.7 -> 7.7, (212,4464,24) f16 6.0 -> 7.7, (88,8448,256) f16 7.0 -> 7.9, (2618,200,32) f16
 // 6.1 -> 6.8, (88,9792,320) f16 7.6 -> 9.1, (600,1664,592) f16 at a pitch of 8 more 11.7 -> 12.6, (88,9592,832) f16 11.8 -> 12.5; 128 x 128 at any alignment -> small tiles (685,3452,95) f16 9.9 -> 13.2; but (567,648,232) f32 7.5 -> 4.9, (1242,448,32) f16 5.7 -> 5.0.
+constexpr int BK_STEP = 64;                              // k extent of a step of every tiled kernel
 enum class Operands { lines, chunks, any };              // rows begin at 128-byte lines; at 16 bytes; anywhere
 Operands operands_of(int64_t lda, int64_t ldb) { return lda % 64 || ldb % 64 ? Operands::chunks : Operands::lines; }
 struct KsliceCand { int per_cu; double fixed1, rate1, fixed2, rate2; };
@@ -170,6 +174,43 @@ int best_kslice(int c_is_f16, Operands form, int64_t M, int64_t N, int64_t K, in
     return best;
 }
 
+// Problems without alignment on more 128 x 128 tiles than compute units: estimated microseconds of the 128 x 128 form
+// (two workgroups a compute unit) and of the 128 x 256 and 256 x 256 ones.  A whole round of workgroups
+// takes fixed + (f32 C: c32) + step per k step; a first round that does not fill the chip `idle` of the fixed part and
+// `idle_step` a k step where the fill is nothing; a round behind whole ones `rest` of one and `rest_fill` more with its fill.  Fitted to 260 random odd problems of 100 to
+// 6000 tiles, three sets of operands in turn (scatter 9 %; where the estimate decides, the form it takes is 1.4 % slower than the best of the three on average).  128 x 128 -> the form taken, us:
+// (4001,3999,4003) f32 198 -> 144, (2001,3999,4003) f32 116 -> 80, (14159,1005,2990) f16 152 -> 112, (5553,745,4881) f16 105 -> 81.
+// A form has to be 6 % better to be taken, and below 7 k steps none is by more than 5 % ((4363,4915,1146) f32 99.6, 101.7, 103.0, the other way round).
+struct AnyCand { int id, per_cu; double launch, fixed, c32, step, idle, idle_step, rest, rest_fill; };
+const AnyCand kAnyCands[] = {{ID_UNALIGNED, 2, 2.8, 8.9, 2.5, 1.25, 0.72, 0.69, 0.35, 0.62},
+                             {ID_UNALIGNED + 3, 1, 2.2, 10.0, 1.9, 1.07, 0.72, 0.86, 0.60, 0.30},
+                             {ID_UNALIGNED + 2, 1, 0.0, 20.1, 3.7, 1.62, 0.77, 1.21, 0.52, 0.73}};
+double any_us(const AnyCand& c, int c_is_f16, int64_t M, int64_t N, int64_t K)
+{
+    const int64_t g = config(c.id)->grid(M, N), cus = chip().cus, slots = cus * c.per_cu;
+    if (g < 0) return -1.0;
+    const int64_t full = g / slots, left = g % slots;
+    const double steps = (double)K / BK_STEP, fixed = c.fixed + (c_is_f16 ? 0.0 : c.c32), round = fixed + c.step * steps;
+    double last = 0.0;
+    if (left && full) last = (c.rest + c.rest_fill * (double)left / (double)slots) * round;
+    else if (left) {
+        // (two workgroups a compute unit: up to one each the chip is as good as idle, beyond nearly full)
+        const double fill = c.per_cu == 1 ? (double)left / (double)cus : left <= cus ? 0.0 : 0.77 + 0.23 * (double)(left - cus) / (double)cus;
+        last = fixed * (c.idle + (1.0 - c.idle) * fill) + steps * (c.idle_step + (c.step - c.idle_step) * fill);
+    }
+    return c.launch + (double)full * round + last;
+}
+const GemmConfigDesc* large_any_kernel(int c_is_f16, int64_t M, int64_t N, int64_t K)
+{
+    const AnyCand* best = &kAnyCands[0];
+    double us = 0.94 * any_us(*best, c_is_f16, M, N, K);
+    for (const AnyCand& c : kAnyCands) {
+        const double t = K >= 7 * BK_STEP && us > 0 ? any_us(c, c_is_f16, M, N, K) : -1.0;
+        if (t > 0 && t < us) { best = &c; us = t; }
+    }
+    return config(best->id);
+}
+
 // The kernel behind ID_GENERIC for a problem: where chunks of 8 elements exist and 32-bit tile
 // offsets suffice, the tiled one for any alignment or, on problems of at most one of its tiles per
 // compute unit, the small tiles if they are estimated to be faster than its 12 + 11 us per 1024 k (2 more on a full
@@ -178,9 +219,9 @@ int best_kslice(int c_is_f16, Operands form, int64_t M, int64_t N, int64_t K, in
 // element-wise one.
 const GemmConfigDesc* any_shape_kernel(int c_is_f16, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc)
 {
-    const bool tiled = M <= INT32_MAX - 128 && N >= 8 && K >= 8 && lda <= MAX_TUNED_PITCH && ldb <= MAX_TUNED_PITCH;   // (row numbers of a whole tile in 31 bits)
+    const bool tiled = M <= INT32_MAX - 256 && N >= 8 && K >= 8 && lda <= MAX_TUNED_PITCH && ldb <= MAX_TUNED_PITCH;   // (row numbers of a whole tile in 31 bits)
     if (tiled && g_forced >= ID_KSLICE && g_forced < ID_KSLICE + NUM_KSLICE) return kslice_config(g_forced - ID_KSLICE, true);
-    if (tiled && (g_forced == ID_UNALIGNED || g_forced == ID_UNALIGNED + 1)) return config(g_forced);
+    if (tiled && g_forced >= ID_UNALIGNED && g_forced < ID_UNALIGNED + NUM_UNALIGNED) return config(g_forced);
     if (!tiled || g_forced == ID_GENERIC) return config(ID_GENERIC);       // (another forced configuration, which cannot run here, is ignored)
     // at most one tile per compute unit: two k groups, or one wavefront per SIMD would have nothing to hide its waits
     const int64_t tiles = unaligned_config(1)->grid(M, N), cus = chip().cus;
@@ -198,7 +239,7 @@ const GemmConfigDesc* any_shape_kernel(int c_is_f16, int64_t M, int64_t N, int64
     const bool element_wise = c_is_f16 ? K < 40 && ldc % 64 == 0 && small_tiles > cus
                                        : (K < 32 && small_tiles > cus) || (K < 48 && ((small_tiles >= 2 * cus && small_tiles < 3 * cus) || tiles > cus));
     if (element_wise && tiles >= 0 && tiles <= cus + cus / 10) return config(ID_GENERIC);
-    if (tiles < 0 || tiles > cus) return unaligned_config(1);
+    if (tiles < 0 || tiles > cus) return large_any_kernel(c_is_f16, M, N, K);
     if (K < 64 && c_is_f16 && small_tiles >= 2 * cus) return unaligned_config(2);
     double us = 0;
     const int small = best_kslice(c_is_f16, Operands::any, M, N, K, INT32_MAX, &us);

@@ -56,6 +56,9 @@ int64_t grid_generic(int64_t M, int64_t N);
 // k_groups: 1, or 2 groups of four wavefronts that take the k steps in turn
 const GemmConfigDesc* unaligned_config(int k_groups);
 
+// gemm_unaligned_pp.hip: 256 x 256 and 128 x 256 tiles at any alignment (N, K >= 8), phase-alternating
+const GemmConfigDesc* unaligned_pp_config(int block_m);
+
 // gemm_kslice.hip: eight wavefronts share a small tile of C and take its k steps in turn (any alignment, N, K >= 8)
 // index 0 .. 4: 16x32, 32x32, 16x64, 32x64, 64x64; any_shape: under the name that the any-shape family reports
 const GemmConfigDesc* kslice_config(int index, bool any_shape);

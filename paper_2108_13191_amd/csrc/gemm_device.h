@@ -108,6 +108,17 @@ __device__ __forceinline__ half4 lds_read_tr16(uint32_t addr)
     return __builtin_bit_cast(half4, v);
 }
 
+// The workgroup barrier between two phases of the phase-alternating kernels.
+__device__ __forceinline__ void phase_barrier()
+{
+    // nothing may be scheduled across a phase boundary
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // Workgroup id -> C tile.  Ids are dealt to the XCDs round-robin; give XCD x
 // the x-th contiguous slice of a tile order that walks group_m tile rows at a
 // time, column by column.

@@ -69,16 +69,6 @@ using namespace gemm_dev;
 
 constexpr int A_REGION = 0;                  // two A buffers, then three B buffers
 
-__device__ __forceinline__ void phase_barrier()
-{
-    // nothing may be scheduled across a phase boundary
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
-
 // MI = 32: v_mfma_f32_32x32x16_f16 (4 x 2 accumulators of 32 x 32 per wavefront, two
 // 16-wide k slices per phase); MI = 16: v_mfma_f32_16x16x32_f16 (8 x 4 accumulators
 // of 16 x 16, one 32-wide k slice per phase).  Same LDS image, schedule and epilogue.
