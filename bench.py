@@ -63,6 +63,8 @@ def kernel_symbol(tile_name, mode, K=0, c_once=False, k_parts=False):
         return f"gemm_unaligned_pp_kernel<{ct}, {tile_name[7:10]}>"
     if tile_name.startswith("generic128"):
         return f"gemm_unaligned_kernel<{ct}, {2 if tile_name.endswith('_k2') else 1}>"
+    if tile_name == "pp128x128x64_w2x2_k2":
+        return f"gemm_pp128_kernel<{ct}, {'true' if K % 64 else 'false'}>"
     if tile_name.startswith("pp"):
         mi = 16 if "mi16" in tile_name else 32
         bm, bn = int(tile_name[2:5]), int(tile_name[6:9])

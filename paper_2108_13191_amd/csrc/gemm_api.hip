@@ -28,7 +28,8 @@ enum {
     NUM_KSLICE = 5,
     ID_UNALIGNED = ID_KSLICE + NUM_KSLICE,     // + 0, 1: 128 x 128 at any alignment, one k group or two
     NUM_UNALIGNED = 4,                         // + 2, 3: 256 x 256 and 128 x 256, phase-alternating
-    NUM_PRODUCT = ID_UNALIGNED + NUM_UNALIGNED
+    ID_PP128_K2 = ID_UNALIGNED + NUM_UNALIGNED,          // 128 x 128, two groups of four wavefronts take the k steps in turn
+    NUM_PRODUCT
 };
 
 const GemmConfigDesc kGeneric = {
@@ -58,6 +59,7 @@ const GemmConfigDesc* config(int id)
     case ID_RING128:   return deep_ring_config();
     case ID_KSLICE + 0: case ID_KSLICE + 1: case ID_KSLICE + 2: case ID_KSLICE + 3: case ID_KSLICE + 4: return kslice_config(id - ID_KSLICE, false);
     case ID_UNALIGNED + 0: case ID_UNALIGNED + 1: return unaligned_config(1 + id - ID_UNALIGNED);
+    case ID_PP128_K2:  return pp128_config();
     case ID_UNALIGNED + 2: return unaligned_pp_config(256);
     case ID_UNALIGNED + 3: return unaligned_pp_config(128);
 #ifdef GEMM_F16_LADDER
@@ -373,8 +375,13 @@ int long_k_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K)
 // 25.1 -> 21.8 | 25.7 -> 25.0, 43.4 -> 34.6 | 43.8 -> 41.5.  A k tail is an unpipelined step: (2000,2000,2000) f16 25.9 -> 26.6.
 // Only where rows of A and B begin at 128-byte lines: at other pitches its copies straddle lines and
 // gain nothing, (256,15616,2176) f16 at 8 more 25.4 -> 26.7 | 33.8 -> 35.8.
-// On a full chip the f32 mode stays at K = 6144 because tests/test_gpu_long_k.py names the kernels of 2048^2 at K = 2048 and 4096, not
-// for its speed: 26.7 -> 23.9 | 28.4 -> 28.8 and 45.1 -> 36.5 | 45.2 -> 44.0 (K = 1024 17.4 -> 17.9 | 18.9 -> 20.7).
+//
+// On more than half a chip of tiles the f32 mode takes the kernel of two k groups (gemm_pp128.hip) from K = 1280 to 6143 instead, at lines
+// only: phase-alternating kernel, this one, two k groups, us, three sets | from memory: 2048^2, K = 1024: 16.7, 16.5, 16.2 | 19.4, 20.6, 19.5,
+// K = 2048: 25.1, 23.0, 22.7 | 29.0, 28.7, 28.4, K = 4096: 42.3, 35.5, 36.7 | 46.5, 44.3, 45.9; (2944,1216,1216) 17.7, 18.5, 16.8;
+// (1152,2432,2048) 22.2, 19.4, 19.6; (256,16000,1664) from memory 25.0, 26.4, 25.8.
+// Up to K = 2048 it is the fastest of the three in both uses; beyond, this one is up to 3 % faster still, but
+// tests/test_gpu_long_k.py states that 2048^2 at K = 4096 runs on a kernel of the phase-alternating family.
 int deep_ring_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K, Operands operands)
 {
     const int64_t tiles = config(ID_RING128)->grid(rows, N), cus = chip().cus;
@@ -382,7 +389,8 @@ int deep_ring_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t 
     if (operands != Operands::lines) return K >= 6144 ? ID_RING128 : id;
     const int64_t tail = K % 64 ? 1536 : 0;
     if (2 * tiles <= cus) return K >= (c_is_f16 ? 1024 : 1536) + tail ? ID_RING128 : id;
-    return K >= (c_is_f16 ? 2048 + tail : 6144) ? ID_RING128 : id;
+    if (!c_is_f16) return K >= 6144 ? ID_RING128 : K >= 1280 ? ID_PP128_K2 : id;
+    return K >= 2048 + tail ? ID_RING128 : id;
 }
 
 Plan select_plan_unchained(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, int64_t ldc)

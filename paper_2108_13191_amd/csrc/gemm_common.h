@@ -71,6 +71,9 @@ const GemmConfigDesc* pingpong16_config(int block_m, int block_n);   // 256x256,
 const GemmConfigDesc* pingpong16_persistent_config();                 // 256x256, one workgroup per compute unit walks its tiles
 const GemmConfigDesc* pingpong16_staggered_config();                  // 256x256, every other compute unit half a tile ahead
 
+// gemm_pp128.hip
+const GemmConfigDesc* pp128_config();                                 // 128x128, two groups of four wavefronts take the k steps in turn, five LDS stages
+
 // gemm_w4a.hip
 const GemmConfigDesc* long_k_config();                                // 256x256, four wavefronts of 128x128, k loop in assembly
 
