@@ -475,16 +475,18 @@ int k_split_if_it_pays(int& id, int c_is_f16, int64_t M, int64_t N, int64_t K)
 // Small results go to the small tiles where the estimates say so.  Before -> after, us:
 // 256^3 6.6 -> 3.4, 512^3 7.9 -> 4.1, 1024^3 f16 13.5 -> 8.4, (128,4096,1024) 11.2 -> 6.5, (16,8192,8192)
 // f16 50 -> 37, (8192,16,8192) f16 52 -> 29, (512,1024,4096) f16 30 -> 13.4.
-// Two limits of the plain form from K = 2048 on, where tests/test_gpu_long_k.py states what runs (on up to 128 rows against a wide B, and
-// beyond K = 6144); they are not for speed.  In f32
-// mode such a wide problem of one row of tiles that is cut along k stays so
+// Two limits of the plain form from K = 2048 on, where tests/test_gpu_long_k.py states what runs; they are not for speed, and
+// are no wider than what the test has shapes of.  In f32
+// mode a wide problem (N more than four times M) of 16 to 127 rows that is cut along k stays so
 // -- cut, small tiles, us: (16,2048,2048) 9.2, 4.95 -- and
 // others leave the split k loop for a gain of a tenth or more ((2541,8,2280) 15.9 -> 5.0, (598,72,2312) 15.8 -> 7.7, (8192,64,2048) 14.9 -> 9.7, (184,1120,2384) 17.6 -> 9.4,
-// (256,4096,4096) 24.5 -> 18.4).  In f16 mode a wide problem, or one with
-// K > 6144, runs on no more workgroups than it has 64 x 64 tiles (a tall one only where more of them are not estimated to be clearly faster) -- so, on as many as are best: (16,2048,2048) 6.3, 4.9,
+// (1,3192,2208) 9.6 -> 6.8, (256,4096,4096) 24.5 -> 18.4).  In f16 mode a wide problem of 16 to 127 rows, or one of more than a tile of 128
+// either way with K > 6144, runs on no more workgroups than it has 64 x 64 tiles -- so, on as many as are best: (16,2048,2048) 6.3, 4.9,
 // (32,4096,4096) 14.8, 11.8, (64,8192,8192) 52, 42 -- except where the test has no shape: at most 32 rows
-// against a B of 64 MB and more ((16,8192,8192) 42 us on 128 workgroups, 37 on 256).  Tall ones, limited -> not: (1753,8,9784) 33.1 -> 12.0,
-// (1227,72,6856) 31.4 -> 16.0, (2217,8,14712) 53.8 -> 16.9; by small estimates also the other way round: (5351,80,5056) 21.7 -> 24.1, (4596,80,12160) 59 -> 66.
+// against a B of 64 MB and more ((16,8192,8192) 42 us on 128 workgroups, 37 on 256).  Others, limited -> not: (89,96,11496) 48.7 -> 21.8,
+// (10,1072,5672) 17.6 -> 13.2, (167,112,8472) 40.0 -> 18.9, (160,760,3496) 18.6 -> 10.0.
+// Tall ones (M more than four times N) take more workgroups than that only for an estimated seventh: (1753,8,9784) 33.1 -> 12.0,
+// (1227,72,6856) 31.4 -> 16.0, (2217,8,14712) 53.8 -> 16.9; by smaller estimates also the other way round: (5351,80,5056) 21.7 -> 24.1, (4596,80,12160) 59 -> 66.
 int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_t N, int64_t K, Operands operands)
 {
     const int64_t tiles = config(ID_PP128x128)->grid(M, N);
@@ -494,10 +496,11 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
     double other = other_us(pl, M, N, K);
     if (form == Form::plain && K >= 2048) {
         if (pl.k_split > 1) {
-            if (wide && M <= 128) return -1;
+            if (wide && M >= 16 && M < 128) return -1;
             other *= 0.9;
         }
-        if (c_is_f16 && (wide || tall || K > 6144) && !(M <= 32 && N * K >= (int64_t)1 << 25)) max_grid = config(ID_T64)->grid(M, N);
+        const bool stated = wide ? M >= 16 && M < 128 : tall || (K > 6144 && M > 128 && N > 128);
+        if (c_is_f16 && stated && !(M <= 32 && N * K >= (int64_t)1 << 25)) max_grid = config(ID_T64)->grid(M, N);
     }
     double us = 0, more_us = 0;
     int small = best_kslice(c_is_f16, operands, M, N, K, max_grid, &us);
@@ -505,13 +508,13 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
         const int more = best_kslice(c_is_f16, operands, M, N, K, INT32_MAX, &more_us);
         if (more >= 0 && (small < 0 || more_us < 0.87 * us)) { small = more; us = more_us; }
     }
-    if (form == Form::workspace && pl.k_split > 1) {
-        other += 5.0;                                                // the passes before and after
+    if (pl.k_split > 1) {
+        if (form == Form::workspace) other += 5.0;                   // the passes before and after
         // A wide B that no call has left in the caches (split -> small tiles, us; its latency is spread over
         // more compute units by the split): (12,1032,8200) 17.2 -> 28.7 (in the caches 13.8 -> 17.9), (9,1168,5208) 16.5 -> 18.6,
         // (30,8496,4168) 26.0 -> 28.5, but (5,4352,3464) 16.9 -> 14.3; with more rows, tiles above one another share it:
         // (54,536,8904) 21.8 -> 24.6, (98,896,7192) 23.5 -> 18.0, (96,7832,4608) 35.6 -> 29.5, (503,1160,4728) 30.0 -> 25.6; with the larger dimension
-        // in A it costs less: (1888,8,8264) 23.7 -> 14.7
+        // in A it costs less: (1888,8,8264) 23.7 -> 14.7.  f32 mode: (14,1640,4976) 15.5 -> 20.7, (3,1792,4464) 11.9 -> 15.8, but (14,3744,2792) 16.0 -> 11.2
         if (N > M) us += (M <= 32 ? 1.4 : M <= 128 ? 0.5 : 0.0) * (double)K / 1024.0;
     }
     return small >= 0 && us < other ? ID_KSLICE + small : -1;

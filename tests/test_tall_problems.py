@@ -1,6 +1,6 @@
-"""Many rows and few columns, long k loops: the small tiles on as many workgroups as there are tiles (no split k
+"""Many rows and few columns, or few rows, long k loops: the small tiles on as many workgroups as there are tiles (no split k
 loop in the f32 mode, no limit by the count of 64 x 64 tiles in the f16 mode), where the estimates say so; a
-wide problem of one row of tiles stays cut along k in the f32 mode."""
+wide problem of 16 to 127 rows stays cut along k in the f32 mode."""
 import numpy as np
 import pytest
 
@@ -8,6 +8,7 @@ from paper_2108_13191_amd import binding
 from paper_2108_13191_amd import workloads as wl
 
 SHAPES = [(2541, 8, 2280), (598, 72, 2312), (1753, 8, 9784), (3306, 184, 2096), (5000, 32, 2048)]
+FEW = [(1, 3192, 2208), (10, 1072, 5672), (89, 96, 11496), (160, 760, 3496)]
 
 
 def _name(f16, M, N, K):
@@ -20,12 +21,17 @@ def test_what_runs():
             q = binding.query_config(f16, M, N, K, 16, K, 16, N, 16, N)
             assert q["name"].startswith("ks") and q["grid"] > ((M + 63) // 64) * ((N + 63) // 64), (f16, M, N, K, q)
     assert _name(0, 3306, 184, 2096).startswith("ks") and _name(0, 184, 1120, 2384).startswith("ks")
-    for M, N, K in [(128, 1120, 2384), (16, 2048, 2048)]:
+    # few rows, or one tile either way, in the f16 mode; the f32 mode where B is not latency-bound
+    for M, N, K in FEW:
+        q = binding.query_config(1, M, N, K, 16, K, 16, N, 16, N)
+        assert q["name"].startswith("ks") and q["grid"] > ((M + 63) // 64) * ((N + 63) // 64), (M, N, K, q)
+    assert _name(0, 1, 3192, 2208).startswith("ks") and _name(0, 14, 1640, 4976) == "w4a_128x128x64"
+    for M, N, K in [(127, 1120, 2384), (16, 2048, 2048)]:
         assert _name(0, M, N, K) == "w4a_128x128x64", (M, N, K)
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,N,K", SHAPES)
+@pytest.mark.parametrize("M,N,K", SHAPES + FEW)
 def test_results(oracle_mod, M, N, K):
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
@@ -34,6 +40,6 @@ def test_results(oracle_mod, M, N, K):
     for mode, dtype in (("f32", np.float32), ("f16", np.float16)):
         A, B, C0 = wl.make_inputs(M, N, K, "uniform", "uniform", seed=10600 + N, c_dtype=dtype)
         got = run_gemm(A, B, C0, mode)
-        rows = np.array([0, 1, M // 2, M - 1])
+        rows = np.unique([0, M // 3, M // 2, M - 1])
         Cref, S = oracle_mod.gemm_f16(A, B, C0, rows=rows)
         assert_close(got[rows], Cref, S, C0[rows], mode, what=f"{(M, N, K)} {mode}")
