@@ -610,12 +610,11 @@ Plan workspace_plan(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
     return select_plan(1, M, N, K, A, lda, B, ldb, ldc, Form::workspace);
 }
 
-// The half-precision mode with `ws` (M x N floats, 16-byte aligned, all zero if ws_is_zero) as the
-// f32 sum of the parts; clear_after: leave it all zero again.
+// The half-precision mode with `ws` (M x N floats, 16-byte aligned) as the f32 sum of the parts.
 int run_f16_split(int parts, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb,
-                  void* C, int64_t ldc, float* ws, bool ws_is_zero, bool clear_after, void* stream)
+                  void* C, int64_t ldc, float* ws, void* stream)
 {
-    int rc = ws_is_zero ? GEMM_F16_OK : splitk_f16_zero(ws, M * N, (hipStream_t)stream);   // N is a multiple of 8
+    int rc = splitk_f16_zero(ws, M * N, (hipStream_t)stream);   // N is a multiple of 8
     if (rc != GEMM_F16_OK) return rc;
     GemmArgs a;
     a.M = M; a.N = N; a.K = K;
@@ -623,7 +622,7 @@ int run_f16_split(int parts, int64_t M, int64_t N, int64_t K, const void* A, int
     a.c_is_f16 = 0; a.stream = (hipStream_t)stream; a.bias = nullptr; a.relu = 0; a.k_split = parts;
     rc = config(ID_RING128)->launch(a);
     if (rc != GEMM_F16_OK) return rc;
-    return splitk_f16_finish(ws, C, ldc, M, N, clear_after ? 1 : 0, (hipStream_t)stream);
+    return splitk_f16_finish(ws, C, ldc, M, N, (hipStream_t)stream);
 }
 
 }  // namespace
@@ -646,7 +645,7 @@ int gemm_f16_f16acc_workspace(int64_t M, int64_t N, int64_t K, const void* A, in
     if (!workspace || workspace_bytes < M * N * 4) return run(1, M, N, K, A, lda, B, ldb, C, ldc, stream);
     const int parts = workspace_plan(M, N, K, A, lda, B, ldb, ldc).k_split;
     if (parts < 2) return run(1, M, N, K, A, lda, B, ldb, C, ldc, stream, nullptr, GEMM_F16_ACT_NONE, Form::workspace);
-    return run_f16_split(parts, M, N, K, A, lda, B, ldb, C, ldc, (float*)workspace, false, false, stream);
+    return run_f16_split(parts, M, N, K, A, lda, B, ldb, C, ldc, (float*)workspace, stream);
 }
 
 int gemm_f16_f32acc(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
@@ -687,7 +686,7 @@ int gemm_f16_f16acc_static_workspace(int64_t M, int64_t N, int64_t K, const void
     const int rc2 = splitk_f16_static_scratch(&ws, &floats);
     if (rc2 != GEMM_F16_OK) return rc2;
     if (M * N > floats) return GEMM_F16_ERR_WORKSPACE;
-    return run_f16_split(parts, M, N, K, A, lda, B, ldb, C, ldc, ws, false, false, stream);
+    return run_f16_split(parts, M, N, K, A, lda, B, ldb, C, ldc, ws, stream);
 }
 
 const char* gemm_strerror(int code)
