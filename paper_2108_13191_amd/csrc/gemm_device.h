@@ -19,7 +19,8 @@ struct TiledParams {
     int relu;
     int stagger_ticks;     // late start: workgroups on odd XCDs start this many wall-clock ticks late (0: all at once)
     int first_generation;  // late start: workgroups that begin with the launch (only these wait)
-    int k_split;           // five-stage 128 x 128 kernel: > 1 = workgroup b works on tile b % tiles, part b / tiles of the k loop, and adds to C atomically
+    int k_split;           // five-stage 128 x 128 kernel: > 1 = a workgroup takes one tile and one of this many parts of the k loop, and adds to C atomically
+    int parts_apart;       // ... 1: the parts of a tile on different XCDs; 0: workgroup b takes tile b % tiles, part b / tiles
 };
 
 // A launch whose C is larger than what the 256 MB last-level cache can keep reads and writes it with the
@@ -119,15 +120,18 @@ __device__ __forceinline__ void phase_barrier()
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// Workgroup id -> C tile.  Ids are dealt to the XCDs round-robin; give XCD x
-// the x-th contiguous slice of a tile order that walks group_m tile rows at a
-// time, column by column.
-__device__ __forceinline__ void tile_of_block(const TiledParams& p, int pid, int& tile_m, int& tile_n)
+// Workgroup id -> position in an order of `num` items.  Ids are dealt to the XCDs
+// round-robin; give XCD x the x-th contiguous slice of the order.
+__device__ __forceinline__ int xcd_slice(int num, int num_xcd, int pid)
 {
-    const int num = p.tiles_m * p.tiles_n;
-    const int q = num / p.num_xcd, r = num % p.num_xcd;
-    const int x = pid % p.num_xcd;
-    const int l = x * q + (x < r ? x : r) + pid / p.num_xcd;
+    const int q = num / num_xcd, r = num % num_xcd;
+    const int x = pid % num_xcd;
+    return x * q + (x < r ? x : r) + pid / num_xcd;
+}
+
+// The l-th tile of an order that walks group_m tile rows at a time, column by column.
+__device__ __forceinline__ void tile_in_order(const TiledParams& p, int l, int& tile_m, int& tile_n)
+{
     const int group_size = p.group_m * p.tiles_n;
     const int g = l / group_size;
     const int first_m = g * p.group_m;
@@ -135,6 +139,12 @@ __device__ __forceinline__ void tile_of_block(const TiledParams& p, int pid, int
     const int in_group = l % group_size;
     tile_m = first_m + in_group % gm;
     tile_n = in_group / gm;
+}
+
+// Workgroup id -> C tile.
+__device__ __forceinline__ void tile_of_block(const TiledParams& p, int pid, int& tile_m, int& tile_n)
+{
+    tile_in_order(p, xcd_slice(p.tiles_m * p.tiles_n, p.num_xcd, pid), tile_m, tile_n);
 }
 
 // C tile <-> accumulators of one wavefront: FM x FN blocks of 32 x 32, block

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(256) void gemm_w4a128_kernel(const TiledParams para
     TiledParams p = params;
     if constexpr (SPLIT)
         asm volatile("" : "+s"(p.M), "+s"(p.N), "+s"(p.K), "+s"(p.A), "+s"(p.lda), "+s"(p.B), "+s"(p.ldb), "+s"(p.C), "+s"(p.ldc),
-                          "+s"(p.tiles_m), "+s"(p.tiles_n), "+s"(p.group_m), "+s"(p.num_xcd), "+s"(p.k_split));
+                          "+s"(p.tiles_m), "+s"(p.tiles_n), "+s"(p.group_m), "+s"(p.num_xcd), "+s"(p.k_split), "+s"(p.parts_apart));
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -59,14 +59,19 @@ __global__ __launch_bounds__(256) void gemm_w4a128_kernel(const TiledParams para
     const int wm_base = (wave >> 1) * 64, wn_base = (wave & 1) * 64;
 
     // Split k (f32 C, no fused epilogue, few tiles and a long k loop: every compute unit should
-    // stream operands): workgroup b takes tile b % tiles and part b / tiles of the k steps, and
+    // stream operands): a workgroup takes one tile and one part of the k steps, and
     // adds its sums to C with atomic f32 additions -- C holds the old C already, the order of the
-    // additions is not fixed.  K_len = this workgroup's part of K (all of it without a split).
+    // additions is not fixed.  Which XCD takes what: `parts_apart`.  K_len = this workgroup's part of K (all of it without a split).
     constexpr bool split = SPLIT;
     const int num_tiles = p.tiles_m * p.tiles_n;
-    const int part = split ? (int)blockIdx.x / num_tiles : 0;
-    int tile_m, tile_n;
-    tile_of_block(p, (int)blockIdx.x - part * num_tiles, tile_m, tile_n);
+    int part = 0, tile_m, tile_n;
+    if (!split) tile_of_block(p, blockIdx.x, tile_m, tile_n);
+    else {
+        const int l = p.parts_apart ? xcd_slice(num_tiles * p.k_split, p.num_xcd, blockIdx.x) : (int)blockIdx.x;
+        part = l / num_tiles;
+        const int t = l - part * num_tiles;
+        tile_in_order(p, p.parts_apart ? t : xcd_slice(num_tiles, p.num_xcd, t), tile_m, tile_n);
+    }
     const int m0 = tile_m * SBM, n0 = tile_n * SBN;
     const bool edge = (m0 + SBM > p.M) || (n0 + SBN > p.N);
 
@@ -278,6 +283,21 @@ int64_t grid_w4a128(int64_t M, int64_t N)
     return tm * tn;
 }
 
+// Split k: all parts of a tile on one XCD (its column of B is then a narrow strip of every k row, and the XCD reads all of A),
+// or the parts apart, so that an XCD's workgroups share one part's rows of B and k columns of A: a part's operands pass
+// through fewer of the L2s ((256,4096,16384): 205 -> 153 MB from beyond them).  Measured on 110 random problems, three sets of operands | from
+// memory, one XCD -> apart, us: (1024,1024,8192) 40.7 -> 29.7 | 40.9 -> 33.4, (300,1000,9000) 22.2 -> 19.6 | 24.9 -> 23.2, (512,512,8192)
+// 16.6 -> 15.0 | 18.8 -> 18.4, (64,4096,4096) 14.6 -> 13.4 | 17.3 -> 17.2, (5,4096,8192) 15.2 -> 13.5 | 14.8 -> 13.6; equal where the
+// parts are few.  Not with 17 to 255 rows where the operands together take more than 68 MB and have to come
+// from memory: the workgroups of an XCD in step ask for the same lines of A at once,
+// (64,8192,8192) 37.2 -> 40.3, (25,3800,12672) 22.8 -> 23.8, (216,8192,4096) 31.7 -> 32.1 | 30.5 -> 32.0; with fewer rows, or two full tiles of
+// rows, it gains there too: (1,8192,8192) 29.1 -> 27.0, (256,4096,16384) 56.2 -> 54.7.
+int parts_apart(const GemmArgs& a)
+{
+    const double mb = 2e-6 * (double)a.K * (double)(a.M + a.N);
+    return mb <= 68.5 || a.M <= 16 || a.M >= 256;
+}
+
 int launch_w4a128(const GemmArgs& a)
 {
     const int64_t g = grid_w4a128(a.M, a.N);
@@ -287,6 +307,7 @@ int launch_w4a128(const GemmArgs& a)
     const int parts = (a.k_split > 1 && !a.c_is_f16 && !a.bias && !a.relu) ? a.k_split : 1;
     if (g * parts > INT32_MAX) return GEMM_F16_ERR_SIZE;
     p.k_split = parts;
+    p.parts_apart = parts_apart(a);
     if (a.c_is_f16)
         hipLaunchKernelGGL((gemm_w4a128_kernel<half_t, false>), dim3((unsigned)g), dim3(256), 0, a.stream, p);
     else
