@@ -508,6 +508,15 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
         const int more = best_kslice(c_is_f16, operands, M, N, K, INT32_MAX, &more_us);
         if (more >= 0 && (small < 0 || more_us < 0.87 * us)) { small = more; us = more_us; }
     }
+    // Up to 32 columns, f32 mode, cut along k or small tiles: A is all there is to read, the small tiles read it with
+    // a tile of the right width, and the estimates above are those of a wide B.  Split -> small tiles, us, three sets | from memory: (1257,16,5544)
+    // 15.1 -> 8.3 | 18.8 -> 10.9, (2688,8,6584) 15.8 -> 9.3 | 20.3 -> 12.7, (479,8,7872) 12.6 -> 9.6 | 12.6 -> 9.8, (8192,16,8192) 38.3 -> 28.9,
+    // (16384,16,2560) 21.9 -> 14.8.  With longer k loops it depends: (1472,8,8448) 12.7 -> 10.3 and (2736,8,12960) 18.1 -> 14.5, but (334,24,15880)
+    // 14.5 -> 18.6 and (6000,32,9000) 30.5 -> 32.1; and not where a second round of them would be nearly empty: (9421,16,9592) 46.1 -> 55.5, (9000,8,6000) 30.1 -> 31.3.
+    if (pl.k_split > 1 && form == Form::plain && !c_is_f16 && tall && N <= 32 && K <= 8704) {
+        const int64_t g = kslice_config(1, false)->grid(M, N), cus = chip().cus;       // tiles of 32 x 32
+        if (small >= 0 && (g <= cus || 20 * g >= 29 * cus)) return ID_KSLICE + small;
+    }
     if (pl.k_split > 1) {
         if (form == Form::workspace) other += 5.0;                   // the passes before and after
         // A wide B that no call has left in the caches (split -> small tiles, us; its latency is spread over

@@ -8,6 +8,8 @@ from paper_2108_13191_amd import binding
 from paper_2108_13191_amd import workloads as wl
 
 SHAPES = [(2541, 8, 2280), (598, 72, 2312), (1753, 8, 9784), (3306, 184, 2096), (5000, 32, 2048)]
+# up to 32 columns on the small tiles, one round of 32 x 32 or a second one well filled
+NARROW = [(1257, 16, 5544), (479, 8, 7872), (129, 32, 8704), (8192, 24, 2048), (12000, 16, 2176)]
 FEW = [(1, 3192, 2208), (10, 1072, 5672), (89, 96, 11496), (160, 760, 3496)]
 
 
@@ -30,8 +32,17 @@ def test_what_runs():
         assert _name(0, M, N, K) == "w4a_128x128x64", (M, N, K)
 
 
+def test_narrow_problems():
+    """f32 mode, up to 32 columns: small tiles up to K = 8704; cut along k beyond, with 40 columns
+    (by the estimates) and where a second round of the small tiles would be nearly empty."""
+    for M, N, K in NARROW:
+        assert _name(0, M, N, K).startswith("ks"), (M, N, K)
+    for M, N, K in [(334, 24, 15880), (129, 32, 8712), (9421, 16, 8512), (512, 40, 8192), (8200, 16, 8192)]:
+        assert _name(0, M, N, K) == "w4a_128x128x64", (M, N, K)
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,N,K", SHAPES + FEW)
+@pytest.mark.parametrize("M,N,K", SHAPES + FEW + NARROW)
 def test_results(oracle_mod, M, N, K):
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
