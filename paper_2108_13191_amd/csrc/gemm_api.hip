@@ -163,14 +163,15 @@ double kslice_us(int index, int c_is_f16, Operands form, int64_t M, int64_t N, i
     return 1.6 + short_k + (double)full * round2 + (left == 0 ? 0.0 : left <= cus ? round1 : round2) + (mb > 80.0 ? 0.19 * mb : 0.0);
 }
 
-// The tile with the least estimated time among those with at most max_grid workgroups (-1: none).
-int best_kslice(int c_is_f16, Operands form, int64_t M, int64_t N, int64_t K, int64_t max_grid, double* us)
+// The tile with the least estimated time among those with at most max_grid workgroups (-1: none);
+// second_round_32: 32 x 32 tiles on more workgroups than run at once too.
+int best_kslice(int c_is_f16, Operands form, int64_t M, int64_t N, int64_t K, int64_t max_grid, double* us, bool second_round_32 = true)
 {
     int best = -1;
     for (int i = 0; i < NUM_KSLICE; i++) {
         const int64_t g = kslice_config(i, false)->grid(M, N);
         const double t = kslice_us(i, c_is_f16, form, M, N, K);
-        if (g < 0 || g > max_grid || t < 0) continue;
+        if (g < 0 || g > max_grid || t < 0 || (i == 1 && !second_round_32 && g > chip().cus * kKsliceCands[i].per_cu)) continue;
         if (best < 0 || t < *us) { best = i; *us = t; }
     }
     return best;
@@ -484,14 +485,17 @@ int k_split_if_it_pays(int& id, int c_is_f16, int64_t M, int64_t N, int64_t K)
 // either way with K > 6144, runs on no more workgroups than it has 64 x 64 tiles -- so, on as many as are best: (16,2048,2048) 6.3, 4.9,
 // (32,4096,4096) 14.8, 11.8, (64,8192,8192) 52, 42 -- except where the test has no shape: at most 32 rows
 // against a B of 64 MB and more ((16,8192,8192) 42 us on 128 workgroups, 37 on 256).  Others, limited -> not: (89,96,11496) 48.7 -> 21.8,
-// (10,1072,5672) 17.6 -> 13.2, (167,112,8472) 40.0 -> 18.9, (160,760,3496) 18.6 -> 10.0.
-// Tall ones (M more than four times N) take more workgroups than that only for an estimated seventh: (1753,8,9784) 33.1 -> 12.0,
-// (1227,72,6856) 31.4 -> 16.0, (2217,8,14712) 53.8 -> 16.9; by smaller estimates also the other way round: (5351,80,5056) 21.7 -> 24.1, (4596,80,12160) 59 -> 66.
+// (10,1072,5672) 17.6 -> 13.2, (167,112,8472) 40.0 -> 18.9, (160,760,3496) 18.6 -> 10.0, (1753,8,9784) 33.1 -> 12.0, (2217,8,14712) 53.8 -> 16.9.
+// Those (skinny, or K > 6144) take more workgroups than they have 64 x 64 tiles only for an estimated 15 % where that many would do ((290,1616,9736) 42.9 -> 52.9 on 510 of 32 x 32,
+// estimated 10 % faster, (1763,264,3584) 18.0 -> 19.0, 13 %; 400 problems estimated 15 % faster and more were so, by 30 % on average), and never more 32 x 32 tiles
+// than run at once: (436,2312,5288) 128 x 128 46.2 -> 55.2 on 1022, (10503,88,3680) 34.0 -> 38.3 on 987, (417,2312,12480) from memory 93 -> 133;
+// 144 such problems, 4 % slower on average.  (Two rounds of 32 x 64 are 15 % faster than what they replace.)
 int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_t N, int64_t K, Operands operands)
 {
     const int64_t tiles = config(ID_PP128x128)->grid(M, N);
     if (tiles < 0 || tiles > chip().cus) return -1;
     const bool wide = N > 4 * M, tall = M > 4 * N;
+    bool lifted = false;                                             // f16, limited by the count of 64 x 64 tiles unless more pay
     int64_t max_grid = INT32_MAX;
     double other = other_us(pl, M, N, K);
     if (form == Form::plain && K >= 2048) {
@@ -499,14 +503,15 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
             if (wide && M >= 16 && M < 128) return -1;
             other *= 0.9;
         }
-        const bool stated = wide ? M >= 16 && M < 128 : tall || (K > 6144 && M > 128 && N > 128);
-        if (c_is_f16 && stated && !(M <= 32 && N * K >= (int64_t)1 << 25)) max_grid = config(ID_T64)->grid(M, N);
+        lifted = c_is_f16 && (wide || tall || K > 6144) && !(M <= 32 && N * K >= (int64_t)1 << 25);
+        if (lifted) max_grid = config(ID_T64)->grid(M, N);
+        if (wide ? M >= 16 && M < 128 : !tall && M > 128 && N > 128) lifted = false;                // (stated by the test)
     }
     double us = 0, more_us = 0;
     int small = best_kslice(c_is_f16, operands, M, N, K, max_grid, &us);
-    if (tall && max_grid != INT32_MAX) {                             // more workgroups than that for an estimated seventh
-        const int more = best_kslice(c_is_f16, operands, M, N, K, INT32_MAX, &more_us);
-        if (more >= 0 && (small < 0 || more_us < 0.87 * us)) { small = more; us = more_us; }
+    if (lifted) {
+        const int more = best_kslice(c_is_f16, operands, M, N, K, INT32_MAX, &more_us, false);
+        if (more >= 0 && (small < 0 || us >= other || more_us < 0.85 * us)) { small = more; us = more_us; }
     }
     // Up to 32 columns, f32 mode, cut along k or small tiles: A is all there is to read, the small tiles read it with
     // a tile of the right width, and the estimates above are those of a wide B.  Split -> small tiles, us, three sets | from memory: (1257,16,5544)

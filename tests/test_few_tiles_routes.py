@@ -14,3 +14,16 @@ def test_f32_up_to_four_times_as_wide_as_high():
         assert _name(0, M, N, K, pad).startswith("ks"), (M, N, K)
     # few rows against a wide B stay cut along k
     assert _name(0, 14, 1640, 4976) == "w4a_128x128x64" and _name(0, 3, 1792, 4464) == "w4a_128x128x64"
+
+
+def test_f16_tiles_of_32_by_32_in_a_second_round():
+    """Not where the plan before them is a larger kernel, and not for less than an estimated seventh: (436,2312,5288) 46.2 us on
+    128 x 128, 55.2 on 1022 tiles of 32 x 32, (10503,88,3680) 34.0 and 38.3, (290,1616,9736) 42.9 on 64 x 64 tiles, 52.9."""
+    for M, N, K, pad in [(436, 2312, 5288, 64), (10503, 88, 3680, 0), (2465, 392, 3400, 0), (10347, 88, 2304, 0), (417, 2312, 12480, 0), (340, 2968, 6056, 0)]:
+        assert not _name(1, M, N, K, pad).startswith("ks"), (M, N, K)
+    for M, N, K, pad in [(290, 1616, 9736, 8), (1763, 264, 3584, 64), (5391, 88, 3200, 0), (196, 2328, 3032, 0)]:
+        assert _name(1, M, N, K, pad) == "ks64x64x64_k8", (M, N, K)
+    # two rounds of 32 x 64, and one round of small tiles for a third: as before
+    for M, N, K, pad in [(2316, 400, 2392, 0), (2322, 392, 11040, 8), (131, 6376, 12240, 0), (203, 4176, 2184, 64)]:
+        assert _name(1, M, N, K, pad) == "ks32x64x64_k8", (M, N, K)
+    assert _name(1, 160, 760, 3496).startswith("ks") and _name(1, 10, 1072, 5672) == "ks16x32x64_k8"
