@@ -473,6 +473,18 @@ int k_split_if_it_pays(int& id, int c_is_f16, int64_t M, int64_t N, int64_t K)
     return (int)parts;
 }
 
+// f16 mode: small tiles in place of two of the larger kernels do not pay where the rows of tiles leave a short last group (a group of the tile order is eight rows; the XCD that gets a last one of one
+// row reads all of B for it), us, three sets | from memory, larger kernel -> 32 x 64 tiles: nine rows, five-stage kernel (272,3584,8128) 46.6 -> 59.9 | 68.1 -> 60.5,
+// (265,3584,3968) 25.5 -> 31.1 | 37.6 -> 32.3, 64 x 64 tiling (275,3536,13872) 97.5 -> 117 | 99.6 -> 121; seven rows (207,4672,5504) 34.6 -> 31.1 | 48.3 -> 38.0.
+// The 64 x 64 tiling on up to eight tiles more than there are compute units is faster also against up to three rows more than a group, and at M <= 192, whose five or six rows are uneven too:
+// (339,2816,11584) 82.1 -> 82.2 | 91.6 -> 109, (137,5448,12688) 86.7 -> 103 | 91.0 -> 103; but 264 tiles, seven rows (217,4224,14480) 15 % the other way round.
+bool leaves_a_short_group(const Plan& pl, int64_t M, int64_t N, int small)
+{
+    const int64_t bm = config(ID_KSLICE + small)->block_m, rows = (M + bm - 1) / bm, over = rows > 8 ? rows % 8 : 0, cus = chip().cus;
+    if (pl.id == ID_RING128) return over == 1;
+    return pl.id == ID_T64 && (over == 1 || (config(ID_T64)->grid(M, N) <= cus + cus / 32 && (M <= 192 || (over >= 1 && over <= 3))));
+}
+
 // Small results go to the small tiles where the estimates say so.  Before -> after, us:
 // 256^3 6.6 -> 3.4, 512^3 7.9 -> 4.1, 1024^3 f16 13.5 -> 8.4, (128,4096,1024) 11.2 -> 6.5, (16,8192,8192)
 // f16 50 -> 37, (8192,16,8192) f16 52 -> 29, (512,1024,4096) f16 30 -> 13.4.
@@ -511,7 +523,10 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
     int small = best_kslice(c_is_f16, operands, M, N, K, max_grid, &us);
     if (lifted) {
         const int more = best_kslice(c_is_f16, operands, M, N, K, INT32_MAX, &more_us, false);
-        if (more >= 0 && (small < 0 || us >= other || more_us < 0.85 * us)) { small = more; us = more_us; }
+        if (more >= 0 && (small < 0 || us >= other)) {
+            if (wide && leaves_a_short_group(pl, M, N, more)) return -1;
+            small = more; us = more_us;
+        } else if (more >= 0 && more_us < 0.85 * us) { small = more; us = more_us; }
     }
     // Up to 32 columns, f32 mode, cut along k or small tiles: A is all there is to read, the small tiles read it with
     // a tile of the right width, and the estimates above are those of a wide B.  Split -> small tiles, us, three sets | from memory: (1257,16,5544)

@@ -27,3 +27,16 @@ def test_f16_tiles_of_32_by_32_in_a_second_round():
     for M, N, K, pad in [(2316, 400, 2392, 0), (2322, 392, 11040, 8), (131, 6376, 12240, 0), (203, 4176, 2184, 64)]:
         assert _name(1, M, N, K, pad) == "ks32x64x64_k8", (M, N, K)
     assert _name(1, 160, 760, 3496).startswith("ks") and _name(1, 10, 1072, 5672) == "ks16x32x64_k8"
+
+
+def test_f16_nine_rows_of_small_tiles():
+    """Rows of 32 x 64 tiles that leave one over the groups of eight that the tile order walks: that row reads all of B alone.
+    (272,3584,8128) five stages 46.6 us, small tiles 59.9; (275,3536,13872) 64 x 64 tiling 97.5, 117.  The same against the
+    64 x 64 tiling on little more than one of its tiles a compute unit: (137,5448,12688) 86.7, 102.6."""
+    for M, N, K, pad in [(272, 3584, 8128, 0), (265, 3584, 3968, 0), (283, 3456, 3136, 0), (265, 3544, 6520, 8)]:
+        assert _name(1, M, N, K, pad) == "w4a_128x128x64", (M, N, K)
+    for M, N, K, pad in [(275, 3536, 13872, 64), (286, 3304, 14656, 64), (137, 5448, 12688, 0), (156, 5624, 16176, 64), (339, 2816, 11584, 8)]:
+        assert _name(1, M, N, K, pad) == "t64x64x64_w2x2", (M, N, K)
+    # other counts of rows, more tiles, and against the phase-alternating kernel
+    for M, N, K, pad in [(207, 4672, 5504, 0), (323, 2944, 2752, 0), (155, 5824, 15488, 0), (217, 4224, 14480, 0), (468, 2064, 15080, 0), (277, 3344, 6136, 64)]:
+        assert _name(1, M, N, K, pad) == "ks32x64x64_k8", (M, N, K)
