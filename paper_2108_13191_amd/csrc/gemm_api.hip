@@ -513,7 +513,12 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
     if (form == Form::plain && K >= 2048) {
         if (pl.k_split > 1) {
             if (wide && M >= 16 && M < 128) return -1;
-            other *= 0.9;
+            // Rows at lines, long k loops: the estimates (of three sets in turn) leave out what operands from memory cost the small tiles.  Cut -> small tiles, us,
+            // three sets | from memory, estimated 11 to 15 % faster: (205,1984,5504) at a pitch of 64 more 15.3 -> 18.0 | 18.3 -> 22.6, (3274,64,6144) 15.9 -> 15.1 | 18.1 -> 22.0,
+            // (2289,64,5632) 13.0 -> 13.2 | 16.7 -> 18.7, (721,64,6912) 12.8 -> 12.9 | 16.0 -> 17.5; smaller operands, shorter loops and rows within lines gain in both: (136,960,5504) 11 and 2 %,
+            // (157,4736,3520) 7 and 6, (929,96,6016) at a pitch of 8 more 5 and 14.
+            const bool slow_from_memory = (wide || tall) && operands == Operands::lines && (K > 6200 || (K >= 4500 && operand_mb(M, N, K) >= 19.5));
+            other *= slow_from_memory ? 0.83 : 0.9;
         }
         lifted = c_is_f16 && (wide || tall || K > 6144) && !(M <= 32 && N * K >= (int64_t)1 << 25);
         if (lifted) max_grid = config(ID_T64)->grid(M, N);

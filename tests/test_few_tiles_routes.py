@@ -40,3 +40,13 @@ def test_f16_nine_rows_of_small_tiles():
     # other counts of rows, more tiles, and against the phase-alternating kernel
     for M, N, K, pad in [(207, 4672, 5504, 0), (323, 2944, 2752, 0), (155, 5824, 15488, 0), (217, 4224, 14480, 0), (468, 2064, 15080, 0), (277, 3344, 6136, 64)]:
         assert _name(1, M, N, K, pad) == "ks32x64x64_k8", (M, N, K)
+
+
+def test_f32_long_k_loops_with_rows_at_lines():
+    """The small tiles' estimates leave out what operands from memory cost there: (205,1984,5504) cut along k 15.3 us, small tiles
+    18.0, (3274,64,6144) from memory 18.1 and 22.0, (721,64,6912) 16.0 and 17.5."""
+    for M, N, K, pad in [(205, 1984, 5504, 64), (2289, 64, 5632, 0), (3274, 64, 6144, 0), (145, 1472, 6400, 64), (721, 64, 6912, 0), (147, 704, 7744, 64), (173, 2048, 4864, 0)]:
+        assert _name(0, M, N, K, pad) == "w4a_128x128x64", (M, N, K)
+    # smaller operands up to K = 6200, shorter k loops, clearly better estimates, rows within a line
+    for M, N, K, pad in [(136, 960, 5504, 0), (164, 768, 5888, 0), (157, 4736, 3520, 0), (3588, 192, 3584, 0), (5605, 128, 2432, 0), (159, 640, 6336, 0), (929, 96, 6016, 8), (508, 64, 5056, 0)]:
+        assert _name(0, M, N, K, pad).startswith("ks"), (M, N, K)
