@@ -502,7 +502,7 @@ bool leaves_a_short_group(const Plan& pl, int64_t M, int64_t N, int small)
 // estimated 10 % faster, (1763,264,3584) 18.0 -> 19.0, 13 %; 400 problems estimated 15 % faster and more were so, by 30 % on average), and never more 32 x 32 tiles
 // than run at once: (436,2312,5288) 128 x 128 46.2 -> 55.2 on 1022, (10503,88,3680) 34.0 -> 38.3 on 987, (417,2312,12480) from memory 93 -> 133;
 // 144 such problems, 4 % slower on average.  (Two rounds of 32 x 64 are 15 % faster than what they replace.)
-int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_t N, int64_t K, Operands operands)
+int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_t N, int64_t K, int64_t ldb, Operands operands)
 {
     const int64_t tiles = config(ID_PP128x128)->grid(M, N);
     if (tiles < 0 || tiles > chip().cus) return -1;
@@ -535,12 +535,16 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
     }
     // Up to 32 columns, f32 mode, cut along k or small tiles: A is all there is to read, the small tiles read it with
     // a tile of the right width, and the estimates above are those of a wide B.  Split -> small tiles, us, three sets | from memory: (1257,16,5544)
-    // 15.1 -> 8.3 | 18.8 -> 10.9, (2688,8,6584) 15.8 -> 9.3 | 20.3 -> 12.7, (479,8,7872) 12.6 -> 9.6 | 12.6 -> 9.8, (8192,16,8192) 38.3 -> 28.9,
-    // (16384,16,2560) 21.9 -> 14.8.  With longer k loops it depends: (1472,8,8448) 12.7 -> 10.3 and (2736,8,12960) 18.1 -> 14.5, but (334,24,15880)
-    // 14.5 -> 18.6 and (6000,32,9000) 30.5 -> 32.1; and not where a second round of them would be nearly empty: (9421,16,9592) 46.1 -> 55.5, (9000,8,6000) 30.1 -> 31.3.
-    if (pl.k_split > 1 && form == Form::plain && !c_is_f16 && tall && N <= 32 && K <= 8704) {
+    // 15.1 -> 8.3 | 18.8 -> 10.9, (2688,8,6584) 15.8 -> 9.3 | 20.3 -> 12.7, (479,8,7872) 12.6 -> 9.6 | 12.6 -> 9.8,
+    // (16384,16,2560) 21.9 -> 14.8.  Every workgroup reads all of B, so the gain shrinks as k grows: 150 problems, 0.35 to 0.6 of the time at K = 2048 to 4096, 0.6 to 0.9 at 5500 to 8700, where
+    // (1228,32,8576) 12.6 -> 11.4 | 15.5 -> 17.5 is the worst; beyond, (334,24,15880) 14.5 -> 18.6, (6000,32,9000) 30.5 -> 32.1.  Rows of B on lines of their own (a pitch of 64 and more) come to
+    // that sooner: (1465,16,5520) 0.79 | 0.91, (6173,8,5856) 0.83 | 1.15, (1358,32,8536) 15.8 -> 17.3 | 20.2 -> 26.3.  So does a second round of workgroups (8 columns (13312,8,7432) 50.3 -> 45.2 |
+    // 50.4 -> 45.2; more (14081,24,5744) 0.91 | 0.91, (13118,16,6208) 35.0 -> 35.7, (13988,32,6784) 39.6 -> 43.4; pitch of 64 more (14737,16,3560) 0.98 | 0.99, (13191,16,5008) 39.8 -> 42.7), which
+    // must not be nearly empty: (9421,16,9592) 46.1 -> 55.5, (9000,8,6000) 30.1 -> 31.3.
+    if (pl.k_split > 1 && form == Form::plain && !c_is_f16 && tall && N <= 32) {
         const int64_t g = kslice_config(1, false)->grid(M, N), cus = chip().cus;       // tiles of 32 x 32
-        if (small >= 0 && (g <= cus || 20 * g >= 29 * cus)) return ID_KSLICE + small;
+        const bool b_compact = ldb < 64;
+        if (small >= 0 && (g <= cus ? K <= (b_compact ? 8704 : 5504) : 20 * g >= 29 * cus && K <= (!b_compact ? 4096 : N == 8 ? 8192 : 6144))) return ID_KSLICE + small;
     }
     if (pl.k_split > 1) {
         if (form == Form::workspace) other += 5.0;                   // the passes before and after
@@ -587,7 +591,7 @@ Plan select_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, i
 {
     Plan pl = select_large_plan(c_is_f16, M, N, K, A, lda, B, ldb, ldc, form);
     if ((g_forced >= 0 && g_forced < num_configs()) || pl.id == ID_GENERIC || pl.id2 >= 0) return pl;
-    const int small = kslice_if_it_pays(pl, c_is_f16, form, M, N, K, operands_of(lda, ldb));
+    const int small = kslice_if_it_pays(pl, c_is_f16, form, M, N, K, ldb, operands_of(lda, ldb));
     if (small >= 0) { pl.id = small; pl.k_split = 0; }
     return pl;
 }

@@ -50,3 +50,19 @@ def test_f32_long_k_loops_with_rows_at_lines():
     # smaller operands up to K = 6200, shorter k loops, clearly better estimates, rows within a line
     for M, N, K, pad in [(136, 960, 5504, 0), (164, 768, 5888, 0), (157, 4736, 3520, 0), (3588, 192, 3584, 0), (5605, 128, 2432, 0), (159, 640, 6336, 0), (929, 96, 6016, 8), (508, 64, 5056, 0)]:
         assert _name(0, M, N, K, pad).startswith("ks"), (M, N, K)
+
+
+def _narrow(M, N, K, ldb):
+    return binding.query_config(0, M, N, K, 16, K + (-K) % 64, 16, ldb, 16, N)["name"]
+
+
+def test_f32_up_to_32_columns():
+    """Every workgroup of the small tiles reads all of B: where its rows lie on lines of their own (a pitch of 64 and more), and in
+    a second round, that pays only up to shorter k loops ((1358,32,8536) at a pitch of 96 cut along k 15.8 us, small tiles 17.3, from
+    memory 20.2 and 26.3; (16037,8,5056) at 72 36.5 and 41.1; (13988,32,6784) 39.6 and 43.4)."""
+    cut, small = "w4a_128x128x64", "ks"
+    for M, N, K, ldb, want in [(1358, 32, 8536, 96, cut), (313, 8, 7368, 72, cut), (6173, 8, 5856, 72, cut), (1465, 16, 5504, 80, small), (5764, 16, 4824, 80, small),
+                               (1358, 32, 8536, 32, small), (313, 8, 7368, 8, small),
+                               (16037, 8, 5056, 72, cut), (13187, 24, 7408, 88, cut), (14737, 16, 4096, 80, small), (12000, 16, 2176, 80, small),
+                               (13988, 32, 6784, 32, cut), (14905, 32, 7472, 32, cut), (13339, 8, 6120, 8, small), (13312, 8, 7432, 8, small), (14081, 24, 5744, 24, small)]:
+        assert _narrow(M, N, K, ldb).startswith(want), (M, N, K, ldb)
