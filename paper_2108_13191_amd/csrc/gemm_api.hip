@@ -377,12 +377,16 @@ int long_k_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K)
 // Only where rows of A and B begin at 128-byte lines: at other pitches its copies straddle lines and
 // gain nothing, (256,15616,2176) f16 at 8 more 25.4 -> 26.7 | 33.8 -> 35.8.
 //
-// On more than half a chip of tiles the f32 mode takes the kernel of two k groups (gemm_pp128.hip) from K = 1280 to 6143 instead, at lines
-// only: phase-alternating kernel, this one, two k groups, us, three sets | from memory: 2048^2, K = 1024: 16.7, 16.5, 16.2 | 19.4, 20.6, 19.5,
-// K = 2048: 25.1, 23.0, 22.7 | 29.0, 28.7, 28.4, K = 4096: 42.3, 35.5, 36.7 | 46.5, 44.3, 45.9; (2944,1216,1216) 17.7, 18.5, 16.8;
-// (1152,2432,2048) 22.2, 19.4, 19.6; (256,16000,1664) from memory 25.0, 26.4, 25.8.
-// Up to K = 2048 it is the fastest of the three in both uses; beyond, this one is up to 3 % faster still, but
-// tests/test_gpu_long_k.py states that 2048^2 at K = 4096 runs on a kernel of the phase-alternating family.
+// On more than half a chip of tiles the f32 mode takes the kernel of two k groups (gemm_pp128.hip) from K = 1472 to 6143 instead, at lines
+// only: phase-alternating kernel, this one, two k groups, us, three sets | from memory: 2048^2, K = 2048: 25.1, 23.0, 22.7 | 29.0, 28.7, 28.4, K = 4096: 42.3, 35.5, 36.7 | 46.5, 44.3, 45.9;
+// (1152,2432,2048) 22.2, 19.4, 19.6.  Two k groups against the phase-alternating kernel on 250 random problems of at most 86 MB: three sets 9 % faster on average below
+// K = 2048, 13 to 3000, 17 to 19 beyond, with a k tail as well (60 problems, 7 to 22 %); from memory 2 % slower up to K = 3000 ((1152,2432,2048) 24.9 -> 25.7,
+// (2415,1280,1664) 22.6 -> 23.9, but (2048,2048,2048) 28.5 -> 28.2; with 160 KB of LDS a launch's workgroups do not start beside the last one's), 0 to 2 % faster
+// beyond.  Below 23 k steps it gains 6 % in the one use and loses 4 in the other ((2048,2048,1280) 19.4 -> 18.4 | 21.3 -> 22.4, (12608,256,1280) 16.7 -> 16.5 |
+// 21.1 -> 22.7).  Where three calls' A, B and C exceed the last-level cache every use is one from memory: 61 problems of more than 86 MB, 0.81 to 1.07 of the
+// time in turn, 0.92 to 1.08 from memory, on average 0.97 and 1.00: (12672,256,2944) 32.5 -> 34.4, (133,11776,4736) 44.2 -> 47.3, (180,16000,5504) 59.6 -> 62.3.
+// Beyond K = 2048 the five-stage kernel is up to 3 % faster still, but tests/test_gpu_long_k.py states that 2048^2 at K = 4096 runs on a kernel of the phase-alternating family.
+constexpr double TWO_GROUPS_MB = 86.0;
 int deep_ring_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K, Operands operands)
 {
     const int64_t tiles = config(ID_RING128)->grid(rows, N), cus = chip().cus;
@@ -390,7 +394,7 @@ int deep_ring_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t 
     if (operands != Operands::lines) return K >= 6144 ? ID_RING128 : id;
     const int64_t tail = K % 64 ? 1536 : 0;
     if (2 * tiles <= cus) return K >= (c_is_f16 ? 1024 : 1536) + tail ? ID_RING128 : id;
-    if (!c_is_f16) return K >= 6144 ? ID_RING128 : K >= 1280 ? ID_PP128_K2 : id;
+    if (!c_is_f16) return K >= 6144 ? ID_RING128 : K >= 1472 && operand_mb(rows, N, K) + 4e-6 * (double)rows * (double)N <= TWO_GROUPS_MB ? ID_PP128_K2 : id;
     return K >= 2048 + tail ? ID_RING128 : id;
 }
 
