@@ -203,12 +203,22 @@ double any_us(const AnyCand& c, int c_is_f16, int64_t M, int64_t N, int64_t K)
     }
     return c.launch + (double)full * round + last;
 }
-const GemmConfigDesc* large_any_kernel(int c_is_f16, int64_t M, int64_t N, int64_t K)
+// ... and 12 % better to be taken at a little more than one round of 256 x 256 (up to a quarter of a second one) where the rows of A and B begin at
+// 8-byte addresses, or one's at 4 and the other's at 16: the 128 x 128 form's loads, a lane a clock at odd elements, cost less there, which the estimates leave out.  128 x 128 -> 256 x 256, us:
+// (2840,6261,3235) f32 at pitches of 3264 and 6262 165 -> 182, (2971,6185,3640) f16 at 3648 and 6188 183 -> 196, (4125,4199,2854) f32 at 2854 and 4224 153 -> 163;
+// the other way round with 80 k steps and more ((2689,6875,11807) f32 11 %, (11344,1625,6149) 7 %) and at odd pitches ((4464,3834,2779) f16 4 to 8 %).  Left as it is: at 257 to 270 tiles of 128 x 128 three of some 200 problems are slower on
+// 128 x 256 in both uses ((265,11069,1776) f16 36.9 -> 40.6, (1112,3639,1434) f16 31.4 -> 36.1, (1542,2435,703) f16 20.5 -> 22.0), most others 5 to 30 % faster.
+int64_t row_bytes(const void* p, int64_t ld) { const int64_t x = (int64_t)((uintptr_t)p | 16u) | 2 * ld; return x & -x; }     // the largest power of two, up to a load's 16, that divides every row's address
+const GemmConfigDesc* large_any_kernel(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb)
 {
     const AnyCand* best = &kAnyCands[0];
     double us = 0.94 * any_us(*best, c_is_f16, M, N, K);
+    const bool fast_rows = row_bytes(A, lda) * row_bytes(B, ldb) >= 64;
+    const int64_t cus = chip().cus;
     for (const AnyCand& c : kAnyCands) {
-        const double t = K >= 7 * BK_STEP && us > 0 ? any_us(c, c_is_f16, M, N, K) : -1.0;
+        const int64_t g = config(c.id)->grid(M, N);
+        const bool short_round = c.id == ID_UNALIGNED + 2 && K < 80 * BK_STEP && g > cus && 4 * g <= 5 * cus;
+        const double t = K >= 7 * BK_STEP && us > 0 ? any_us(c, c_is_f16, M, N, K) * (short_round && fast_rows ? 0.94 / 0.88 : 1.0) : -1.0;
         if (t > 0 && t < us) { best = &c; us = t; }
     }
     return config(best->id);
@@ -220,7 +230,7 @@ const GemmConfigDesc* large_any_kernel(int c_is_f16, int64_t M, int64_t N, int64
 // chip) -- measured, 128 x 128 -> best small tile, us: 513 x 511 x 509 18.7 -> 6.3, 1001 x 1003 x 1005 24.2 -> 12.0,
 // (16,8191,8191) 126 -> 37, (1501,1499,503) 19.8 against 20.4, (2001,1999,255) 16.9 against 22.6; else the
 // element-wise one.
-const GemmConfigDesc* any_shape_kernel(int c_is_f16, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc)
+const GemmConfigDesc* any_shape_kernel(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, int64_t ldc)
 {
     const bool tiled = M <= INT32_MAX - 256 && N >= 8 && K >= 8 && lda <= MAX_TUNED_PITCH && ldb <= MAX_TUNED_PITCH;   // (row numbers of a whole tile in 31 bits)
     if (tiled && g_forced >= ID_KSLICE && g_forced < ID_KSLICE + NUM_KSLICE) return kslice_config(g_forced - ID_KSLICE, true);
@@ -242,7 +252,7 @@ const GemmConfigDesc* any_shape_kernel(int c_is_f16, int64_t M, int64_t N, int64
     const bool element_wise = c_is_f16 ? K < 40 && ldc % 64 == 0 && small_tiles > cus
                                        : (K < 32 && small_tiles > cus) || (K < 48 && ((small_tiles >= 2 * cus && small_tiles < 3 * cus) || tiles > cus));
     if (element_wise && tiles >= 0 && tiles <= cus + cus / 10) return config(ID_GENERIC);
-    if (tiles < 0 || tiles > cus) return large_any_kernel(c_is_f16, M, N, K);
+    if (tiles < 0 || tiles > cus) return large_any_kernel(c_is_f16, M, N, K, A, lda, B, ldb);
     if (K < 64 && c_is_f16 && small_tiles >= 2 * cus) return unaligned_config(2);
     double us = 0;
     const int small = best_kslice(c_is_f16, Operands::any, M, N, K, INT32_MAX, &us);
@@ -637,7 +647,7 @@ int run(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, int64_t ld
     a.A = (const half_t*)A; a.lda = lda; a.B = (const half_t*)B; a.ldb = ldb; a.C = C; a.ldc = ldc;
     a.c_is_f16 = c_is_f16; a.stream = (hipStream_t)stream;
     a.k_split = plan.k_split;
-    const GemmConfigDesc* first = plan.id == ID_GENERIC ? any_shape_kernel(c_is_f16, M, N, K, lda, ldb, ldc) : config(plan.id);
+    const GemmConfigDesc* first = plan.id == ID_GENERIC ? any_shape_kernel(c_is_f16, M, N, K, A, lda, B, ldb, ldc) : config(plan.id);
     const int rc1 = first->launch(a);
     if (rc1 != GEMM_F16_OK || plan.rows1 == M) return rc1;
     a.k_split = 0;
@@ -760,7 +770,7 @@ int gemm_f16_query_config(int c_is_f16, int64_t M, int64_t N, int64_t K, const v
     if (rc != GEMM_F16_OK) return rc;
     const Plan plan = select_plan(c_is_f16, M, N, K, a, lda, b, ldb, ldc, Form::plain);
     if (M == 0 || N == 0 || K == 0) { fill_desc(plan.id, 0, out); return GEMM_F16_OK; }
-    const GemmConfigDesc* first = plan.id == ID_GENERIC ? any_shape_kernel(c_is_f16, M, N, K, lda, ldb, ldc) : config(plan.id);
+    const GemmConfigDesc* first = plan.id == ID_GENERIC ? any_shape_kernel(c_is_f16, M, N, K, a, lda, b, ldb, ldc) : config(plan.id);
     int64_t g = first->grid(plan.rows1, N);
     if (g < 0) return GEMM_F16_ERR_SIZE;
     if (plan.rows1 < M) {

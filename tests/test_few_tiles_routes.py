@@ -76,3 +76,16 @@ def test_f32_two_k_groups():
         assert _name(0, M, N, K) == two, (M, N, K)
     for M, N, K in [(12608, 256, 1280), (2048, 2048, 1408), (12672, 256, 2944), (133, 11776, 4736), (180, 16000, 5504), (150, 13440, 5184)]:
         assert _name(0, M, N, K) == "pp128x128x64_w2x4_mi16", (M, N, K)
+
+
+def test_any_alignment_little_more_than_a_round_of_256_by_256():
+    """Rows at 8-byte addresses and better cost the 128 x 128 form no lane a clock: (2840,6261,3235) at pitches of 3264 and 6262 165 us on it,
+    182 on 300 workgroups of 256 x 256."""
+    def name(f16, M, N, K, lda, ldb, a=16, b=16):
+        return binding.query_config(f16, M, N, K, a, lda, b, ldb, 16, N + 1)["name"]
+    large, small = "generic256x256x64", "generic128x128x64"
+    assert name(0, 2840, 6261, 3235, 3264, 6262) == small and name(1, 2971, 6185, 3640, 3648, 6188) == small and name(0, 4125, 4199, 2854, 2854, 4224) == small
+    assert name(0, 2840, 6261, 3235, 3235, 6261) == large                       # odd rows
+    assert name(0, 2840, 6261, 3235, 3264, 6262, a=18) == large                 # odd rows: where they begin counts too
+    assert name(0, 3260, 6055, 8565, 8568, 6056) == large                       # clearly estimated faster
+    assert name(0, 10925, 1975, 7443, 7448, 1980) == large                      # more than a quarter of a second round
