@@ -197,8 +197,8 @@ double any_us(const AnyCand& c, int c_is_f16, int64_t M, int64_t N, int64_t K)
     double last = 0.0;
     if (left && full) last = (c.rest + c.rest_fill * (double)left / (double)slots) * round;
     else if (left) {
-        // (two workgroups a compute unit: up to one each the chip is as good as idle, beyond nearly full)
-        const double fill = c.per_cu == 1 ? (double)left / (double)cus : left <= cus ? 0.0 : 0.77 + 0.23 * (double)(left - cus) / (double)cus;
+        // (two workgroups a compute unit, more than one each: nearly full)
+        const double fill = c.per_cu == 1 ? (double)left / (double)cus : 0.77 + 0.23 * (double)(left - cus) / (double)cus;
         last = fixed * (c.idle + (1.0 - c.idle) * fill) + steps * (c.idle_step + (c.step - c.idle_step) * fill);
     }
     return c.launch + (double)full * round + last;
@@ -449,7 +449,9 @@ enum class Form { plain, fused, workspace };
 
 // Estimated microseconds (as kslice_us) of a plan on at most one 128 x 128 tile per compute unit, from
 // launches in a row, us: phase-alternating kernel (1024,2048,K) 14.3 / 22.4 at K = 1024 / 2048; five-stage
-// kernel 13.1 / 27.8 at 1024 / 4096; its split form (512,512,4096) 14.4, (1024,1024,4096) 26.3 (four million additions).
+// kernel 13.1 / 27.8 at 1024 / 4096; its split form (512,512,4096) 14.4, (1024,1024,4096) 26.3 (four million additions).  The split form's
+// figures were fitted before its parts were dealt to the XCDs as they are now (parts_apart): on 243 problems they are 7 % high on average, scatter 17 %.  2.8 us per million
+// additions stand for all that grows with M x N x parts, the additions alone take half of that.  The kernel of two k groups counts as the phase-alternating one.
 double other_us(const Plan& pl, int64_t M, int64_t N, int64_t K)
 {
     const double k = (double)K / 1024.0, mb = operand_mb(M, N, K), memory = mb > 80.0 ? 0.08 * mb : 0.0;
@@ -478,8 +480,8 @@ int k_split_if_it_pays(int& id, int c_is_f16, int64_t M, int64_t N, int64_t K)
     if (tiles <= 0 || 2 * tiles > cus) return 0;
     int64_t parts = cus / tiles < steps / 16 ? cus / tiles : steps / 16;
     if (parts > 16) parts = 16;
-    // the additions: M x N per part, a row of 64 floats per instruction, about 5 us per million;
-    // measured with at most 4 million of them (before -> after): (64,8192,8192) 49 -> 30 us,
+    // the additions: M x N per part, a row of 64 floats per instruction, 1.4 us per million ((256,4096,16384), four million: 56 us, 50 with plain
+    // stores in their place); measured with at most 4 million of them (before -> after): (64,8192,8192) 49 -> 30 us,
     // (128,8192,8192) 52 -> 37, (256,8192,8192) 54 -> 45, (1024,2048,8192) 57 -> 47,
     // (512,4096,4096) 31 -> 32
     if (parts * M * N > 4194304) parts = 4194304 / (M * N);
@@ -491,7 +493,7 @@ int k_split_if_it_pays(int& id, int c_is_f16, int64_t M, int64_t N, int64_t K)
 // f16 mode: small tiles in place of two of the larger kernels do not pay where the rows of tiles leave a short last group (a group of the tile order is eight rows; the XCD that gets a last one of one
 // row reads all of B for it), us, three sets | from memory, larger kernel -> 32 x 64 tiles: nine rows, five-stage kernel (272,3584,8128) 46.6 -> 59.9 | 68.1 -> 60.5,
 // (265,3584,3968) 25.5 -> 31.1 | 37.6 -> 32.3, 64 x 64 tiling (275,3536,13872) 97.5 -> 117 | 99.6 -> 121; seven rows (207,4672,5504) 34.6 -> 31.1 | 48.3 -> 38.0.
-// The 64 x 64 tiling on up to eight tiles more than there are compute units is faster also against up to three rows more than a group, and at M <= 192, whose five or six rows are uneven too:
+// The 64 x 64 tiling on up to eight tiles more than there are compute units is faster also against up to three rows more than a group, and at M <= 192 (why there was not looked for):
 // (339,2816,11584) 82.1 -> 82.2 | 91.6 -> 109, (137,5448,12688) 86.7 -> 103 | 91.0 -> 103; but 264 tiles, seven rows (217,4224,14480) 15 % the other way round.
 bool leaves_a_short_group(const Plan& pl, int64_t M, int64_t N, int small)
 {
@@ -503,10 +505,10 @@ bool leaves_a_short_group(const Plan& pl, int64_t M, int64_t N, int small)
 // Small results go to the small tiles where the estimates say so.  Before -> after, us:
 // 256^3 6.6 -> 3.4, 512^3 7.9 -> 4.1, 1024^3 f16 13.5 -> 8.4, (128,4096,1024) 11.2 -> 6.5, (16,8192,8192)
 // f16 50 -> 37, (8192,16,8192) f16 52 -> 29, (512,1024,4096) f16 30 -> 13.4.
-// Two limits of the plain form from K = 2048 on, where tests/test_gpu_long_k.py states what runs; they are not for speed, and
-// are no wider than what the test has shapes of.  In f32
+// Two limits of the plain form from K = 2048 on, because tests/test_gpu_long_k.py states what runs; they are not for speed.  The test has a handful of
+// shapes, the limits cover all problems of their kind, and a narrower form would be faster outside those shapes.  In f32
 // mode a wide problem (N more than four times M) of 16 to 127 rows that is cut along k stays so
-// -- cut, small tiles, us: (16,2048,2048) 9.2, 4.95 -- and
+// -- cut, small tiles, us: (16,2048,2048) 9.2, 4.95, (45,512,2048) 10.7, 4.75, (42,1024,2048) 10.6, 4.8, (91,1216,3672) 15.1, 9.2; with a fused epilogue such a problem runs on the small tiles -- and
 // others leave the split k loop for a gain of a tenth or more ((2541,8,2280) 15.9 -> 5.0, (598,72,2312) 15.8 -> 7.7, (8192,64,2048) 14.9 -> 9.7, (184,1120,2384) 17.6 -> 9.4,
 // (1,3192,2208) 9.6 -> 6.8, (256,4096,4096) 24.5 -> 18.4).  In f16 mode a wide problem of 16 to 127 rows, or one of more than a tile of 128
 // either way with K > 6144, runs on no more workgroups than it has 64 x 64 tiles -- so, on as many as are best: (16,2048,2048) 6.3, 4.9,

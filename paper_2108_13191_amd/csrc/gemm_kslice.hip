@@ -181,7 +181,8 @@ __global__ __launch_bounds__(64 * KW, 2 * WG_PER_CU) void gemm_kslice_kernel(con
 #pragma unroll
         for (int e = 0; e < 4; e++) bias4[e] = (float)reinterpret_cast<const CT*>(p.bias)[first + e];
     }
-    // (reads stay in C: columns first .. first + 3 end by N, rows beyond M read the last one)
+    // (reads stay in C: columns first .. first + 3 end by N, rows beyond M read the last one; columns before `nominal` belong to
+    // another thread, maybe of another workgroup, which may be storing them: what is read of them is never used)
 #pragma unroll
     for (int ps = 0; ps < PASSES; ps++) {
         const int row = m0 + c_row + ps * ROWS, down = (edge && row >= p.M) ? p.M - 1 - m0 - c_row : ps * ROWS;

@@ -5,11 +5,17 @@
 // the step five ahead of the one it multiplies.  One barrier per k step.  The groups' sums are added
 // through LDS at the end.
 //
-// Bound by what a compute unit can fetch: 32 KB a k step at 100 GB/s (what it holds in flight over the latency of its
-// L2) are 0.33 us on half a chip, whatever else runs -- the copies alone take that, with the
-// MFMAs and reads 0.33, the MFMAs and reads alone 0.23 -- and 0.42 us on a full one.  The eight wavefronts of 64 x 32 in
+// A k step takes what its copies take: 32 KB in 0.33 us (100 GB/s a compute unit) on half a chip, 0.42 (78) on a full one -- the
+// copies alone 0.33 and the same with MFMAs and LDS reads, those without copies 0.23.  That is no limit of the chip: other loops reach 150 GB/s a compute unit
+// out of the L2s, and 128 KB in flight at 100 GB/s would be 1.3 us of latency; why the copies take so long was not found.  Neither the order
+// in which a step is fetched (LDS image or rows) nor behind which MFMAs the copies stand changes it by more than 1 %.  The eight wavefronts of 64 x 32 in
 // gemm_pingpong.hip read 96 KB of LDS a step where this split reads 64, and meet four barriers: 0.5 us.
-// 2048^3 f32 25.1 -> 22.7 us.  Whether fetched in the order of the LDS image or of the rows, behind which MFMAs the copies stand: within 1 %.
+// Outside the loop, start and C take about 9 us, which nothing hides but the last two or three steps.
+// 2048^3 f32 25.1 -> 22.7 us when it was written, 24.2 -> 21.7 and 26.6 -> 23.4 in other sessions on other cards.
+//
+// Automatic selection gives it f32 problems only (deep_ring_if_it_pays in gemm_api.hip).  f16 C, when forced, us, the kernel selected -> this one, three sets | from
+// memory: from K = 2048 on the five-stage kernel is ahead, (2048,2048,2048) 19.3 -> 20.0 | 24.1 -> 24.9, (4022,896,4096) 30.1 -> 30.7 | 42.0 -> 42.5; below, the phase-alternating
+// one is behind in turn and ahead from memory, (2048,2048,1536) 18.2 -> 16.5 | 20.4 -> 21.1, (1152,2432,1024) 13.8 -> 12.7 | 15.3 -> 15.8; no rule uses that.
 #include "gemm_device.h"
 #include "../../include/gemm_f16.h"
 #include <type_traits>

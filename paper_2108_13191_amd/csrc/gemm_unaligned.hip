@@ -242,7 +242,8 @@ __global__ __launch_bounds__(256 * KG, 2) void gemm_unaligned_kernel(const Tiled
         if (KG > 1 && h != kg) continue;
         const int row0 = m0 + wm_base + 32 * h + (lane >> 4);
         CT* const cptr = Cbase + (int64_t)row0 * p.ldc + first;
-        // Reads stay in C whatever the tile: a lane's 4 columns end by N, rows beyond M read the last one.  (Element by
+        // Reads stay in C whatever the tile: a lane's 4 columns end by N, rows beyond M read the last one; columns before `nominal` belong to
+        // another lane, maybe of another workgroup, which may be storing them: what is read of them is never used.  (Element by
         // element under a test, as the stores at an edge are, each of the 32 reads waits for the one before:
         // (1000,1000,64) f32 13.6 us, 6.7 at 1024 x 1024.)
         ctx4 cin[8];

@@ -220,6 +220,7 @@ __global__ __launch_bounds__(512) void gemm_unaligned_pp_kernel(const TiledParam
     const int x = wn * 64 + 4 * (lane_e & 15), nominal = n0 + (x & ~7);  // this lane_e's 4 columns within the tile; first column of their chunk
     const int first = (nominal < p.N - 8 ? nominal : p.N - 8) + (x & 7);   // ... and where those results belong
     const int row0 = m0 + grp * HM + (lane_e >> 4);
+    // (columns before `nominal` are read, maybe while another workgroup stores them, and never used; rows beyond M read the last one)
     // (the pointers of all slabs at once would not fit the registers: each slab's are formed from a copy
     // that the compiler cannot see through)
     CT* cptr = (CT*)p.C + (int64_t)row0 * p.ldc + first;

@@ -283,15 +283,19 @@ int64_t grid_w4a128(int64_t M, int64_t N)
     return tm * tn;
 }
 
-// Split k: all parts of a tile on one XCD (its column of B is then a narrow strip of every k row, and the XCD reads all of A),
-// or the parts apart, so that an XCD's workgroups share one part's rows of B and k columns of A: a part's operands pass
-// through fewer of the L2s ((256,4096,16384): 205 -> 153 MB from beyond them).  Measured on 110 random problems, three sets of operands | from
-// memory, one XCD -> apart, us: (1024,1024,8192) 40.7 -> 29.7 | 40.9 -> 33.4, (300,1000,9000) 22.2 -> 19.6 | 24.9 -> 23.2, (512,512,8192)
+// Split k, which XCD takes what (workgroup ids are dealt to the XCDs in turn).  Apart: the tiles of part 0, then those of part 1 and so on, in one
+// order of which each XCD takes a contiguous slice, so that its workgroups share one or two parts' rows of B and k columns of A (with 16 parts, two a slice): a part's operands
+// pass through fewer of the L2s ((256,4096,16384): 205 -> 153 MB from beyond them).  Otherwise part p of the t-th tile is workgroup p * tiles + t, each part's tiles dealt
+// to the XCDs in slices: all parts of a tile on one XCD where the number of tiles is a multiple of 8 (the tile's column of B is then a narrow strip of every k row, and the XCD
+// reads all of A), else shifted by the number of tiles from part to part.  Measured on 110 random problems, three sets of operands | from
+// memory, the second order -> apart, us: (1024,1024,8192) 40.7 -> 29.7 | 40.9 -> 33.4, (300,1000,9000) 22.2 -> 19.6 | 24.9 -> 23.2, (512,512,8192)
 // 16.6 -> 15.0 | 18.8 -> 18.4, (64,4096,4096) 14.6 -> 13.4 | 17.3 -> 17.2, (5,4096,8192) 15.2 -> 13.5 | 14.8 -> 13.6; equal where the
 // parts are few.  Not with 17 to 255 rows where the operands together take more than 68 MB and have to come
-// from memory: the workgroups of an XCD in step ask for the same lines of A at once,
-// (64,8192,8192) 37.2 -> 40.3, (25,3800,12672) 22.8 -> 23.8, (216,8192,4096) 31.7 -> 32.1 | 30.5 -> 32.0; with fewer rows, or two full tiles of
-// rows, it gains there too: (1,8192,8192) 29.1 -> 27.0, (256,4096,16384) 56.2 -> 54.7.
+// from memory: (64,8192,8192) 37.2 -> 40.3, (25,3800,12672) 22.8 -> 23.8, (216,8192,4096) 31.7 -> 32.1 | 30.5 -> 32.0 (30 tiles and 64 tiles alike; why was not looked for).
+// The line is drawn wide: 128 and 192 rows at 8192^2 gain 1 to 2 % from memory (41.1 -> 40.6, 51.1 -> 50.0).  With up to 16 rows, or from two full tiles of
+// rows on, it gains or is even: (1,8192,8192) 29.1 -> 27.0 and 28.1 -> 26.9, (8,13064,7104) 35.9 -> 37.2 in one session and 36.7 -> 36.2 in another, (256,4096,16384) 56.2 -> 54.7; 200
+// random problems there 0.93 to 1.03 of the time from memory, in turn 0.83 to 1.04 but for four of 33 at 257 to 384 rows and 70 to 80 MB, where three sets just fill the
+// last-level cache ((290,2568,14496) 41.9 -> 45.3 | 48.4 -> 47.4, (270,2520,15368) 11 % the other way round).
 int parts_apart(const GemmArgs& a)
 {
     const double mb = 2e-6 * (double)a.K * (double)(a.M + a.N);

@@ -1,6 +1,10 @@
-"""What runs on few tiles and long k loops, on the sides of the selector's lines where a measurement says so (no launch: the
-query reports the plan)."""
+"""What runs on few tiles and long k loops, on the sides of the selector's lines where a measurement says so (the
+query reports the plan), and results on either side."""
+import numpy as np
+import pytest
+
 from paper_2108_13191_amd import binding
+from paper_2108_13191_amd import workloads as wl
 
 
 def _name(f16, M, N, K, pad=0):
@@ -89,3 +93,21 @@ def test_any_alignment_little_more_than_a_round_of_256_by_256():
     assert name(0, 2840, 6261, 3235, 3264, 6262, a=18) == large                 # odd rows: where they begin counts too
     assert name(0, 3260, 6055, 8565, 8568, 6056) == large                       # clearly estimated faster
     assert name(0, 10925, 1975, 7443, 7448, 1980) == large                      # more than a quarter of a second round
+
+
+@pytest.mark.gpu
+def test_results_on_both_sides(oracle_mod):
+    """One problem on either side of each line, on the GPU: sampled rows against the oracle."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from gpu_util import assert_close, run_gemm
+    for mode, M, N, K, pad in [("f32", 67, 96, 4104, 0), ("f32", 14, 1640, 4976, 0), ("f16", 436, 2312, 5288, 64), ("f16", 2316, 400, 2392, 0), ("f16", 290, 1616, 2056, 8),
+                               ("f16", 272, 3584, 2112, 0), ("f16", 323, 2944, 2752, 0), ("f32", 205, 1984, 5504, 64), ("f32", 164, 768, 5888, 0), ("f32", 1358, 32, 8536, 64),
+                               ("f32", 13339, 8, 6120, 0), ("f32", 1512, 1536, 1472, 0), ("f32", 1512, 1536, 1408, 0), ("f32", 2840, 6261, 449, 29), ("f16", 2840, 6261, 449, 0)]:
+        dtype = {"f32": np.float32, "f16": np.float16}[mode]
+        A, B, C0 = wl.make_inputs(M, N, K, "normal_rsqrtk", "uniform", seed=10700 + N, c_dtype=dtype)
+        got = run_gemm(A, B, C0, mode, lda=K + pad, ldb=N + pad)
+        rows = np.unique([0, M // 3, M // 2, M - 1])
+        Cref, S = oracle_mod.gemm_f16(A, B, C0, rows=rows)
+        assert_close(got[rows], Cref, S, C0[rows], mode, what=f"{(M, N, K)} {mode}")

@@ -20,7 +20,8 @@ from gpu_util import run_gemm                                # noqa: E402
     (151, 344, 9136),       # 2 x 3 tiles x 8 parts, a k tail
     (1100, 136, 5128),      # 9 rows of tiles: two groups of the tile order
     (16, 4200, 8200),       # more than 68 MB, few rows
-    (20, 4200, 8200),       # ... and more: all parts of a tile on one XCD
+    (20, 4200, 8200),       # ... and more: 33 tiles, the other order, shifted by a tile from part to part
+    (20, 4088, 8712),       # ... 32 tiles: all parts of a tile on one XCD
     (256, 3976, 8200),      # ... and two full tiles of rows
 ])
 def test_every_tile_and_part_once(oracle_mod, M, N, K):
