@@ -391,7 +391,7 @@ int long_k_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K)
 // only: phase-alternating kernel, this one, two k groups, us, three sets | from memory: 2048^2, K = 2048: 25.1, 23.0, 22.7 | 29.0, 28.7, 28.4, K = 4096: 42.3, 35.5, 36.7 | 46.5, 44.3, 45.9;
 // (1152,2432,2048) 22.2, 19.4, 19.6.  Two k groups against the phase-alternating kernel on 250 random problems of at most 86 MB: three sets 9 % faster on average below
 // K = 2048, 13 to 3000, 17 to 19 beyond, with a k tail as well (60 problems, 7 to 22 %); from memory 2 % slower up to K = 3000 ((1152,2432,2048) 24.9 -> 25.7,
-// (2415,1280,1664) 22.6 -> 23.9, but (2048,2048,2048) 28.5 -> 28.2; with 160 KB of LDS a launch's workgroups do not start beside the last one's), 0 to 2 % faster
+// (2415,1280,1664) 22.6 -> 23.9, but (2048,2048,2048) 28.5 -> 28.2; its 160 KB of LDS keep a launch's workgroups from starting beside the last one's, but that this is why was not shown), 0 to 2 % faster
 // beyond.  Below 23 k steps it gains 6 % in the one use and loses 4 in the other ((2048,2048,1280) 19.4 -> 18.4 | 21.3 -> 22.4, (12608,256,1280) 16.7 -> 16.5 |
 // 21.1 -> 22.7).  Where three calls' A, B and C exceed the last-level cache every use is one from memory: 61 problems of more than 86 MB, 0.81 to 1.07 of the
 // time in turn, 0.92 to 1.08 from memory, on average 0.97 and 1.00: (12672,256,2944) 32.5 -> 34.4, (133,11776,4736) 44.2 -> 47.3, (180,16000,5504) 59.6 -> 62.3.
@@ -480,8 +480,8 @@ int k_split_if_it_pays(int& id, int c_is_f16, int64_t M, int64_t N, int64_t K)
     if (tiles <= 0 || 2 * tiles > cus) return 0;
     int64_t parts = cus / tiles < steps / 16 ? cus / tiles : steps / 16;
     if (parts > 16) parts = 16;
-    // the additions: M x N per part, a row of 64 floats per instruction, 1.4 us per million ((256,4096,16384), four million: 56 us, 50 with plain
-    // stores in their place); measured with at most 4 million of them (before -> after): (64,8192,8192) 49 -> 30 us,
+    // the additions: M x N per part, a row of 64 floats per instruction, 1.4 us per million beside other workgroups' k loops ((256,4096,16384),
+    // four million: 56 us, 50 with plain stores in their place), 5 with nothing beside them (190 G a second); measured with at most 4 million of them (before -> after): (64,8192,8192) 49 -> 30 us,
     // (128,8192,8192) 52 -> 37, (256,8192,8192) 54 -> 45, (1024,2048,8192) 57 -> 47,
     // (512,4096,4096) 31 -> 32
     if (parts * M * N > 4194304) parts = 4194304 / (M * N);
