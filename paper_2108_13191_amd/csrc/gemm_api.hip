@@ -163,15 +163,14 @@ double kslice_us(int index, int c_is_f16, Operands form, int64_t M, int64_t N, i
     return 1.6 + short_k + (double)full * round2 + (left == 0 ? 0.0 : left <= cus ? round1 : round2) + (mb > 80.0 ? 0.19 * mb : 0.0);
 }
 
-// The tile with the least estimated time among those with at most max_grid workgroups (-1: none);
-// second_round_32: 32 x 32 tiles on more workgroups than run at once too.
-int best_kslice(int c_is_f16, Operands form, int64_t M, int64_t N, int64_t K, int64_t max_grid, double* us, bool second_round_32 = true)
+// The tile with the least estimated time among those with at most max_grid workgroups, of 32 x 32 at most max_grid_32 (-1: none).
+int best_kslice(int c_is_f16, Operands form, int64_t M, int64_t N, int64_t K, int64_t max_grid, double* us, int64_t max_grid_32 = INT32_MAX)
 {
     int best = -1;
     for (int i = 0; i < NUM_KSLICE; i++) {
         const int64_t g = kslice_config(i, false)->grid(M, N);
         const double t = kslice_us(i, c_is_f16, form, M, N, K);
-        if (g < 0 || g > max_grid || t < 0 || (i == 1 && !second_round_32 && g > chip().cus * kKsliceCands[i].per_cu)) continue;
+        if (g < 0 || g > max_grid || t < 0 || (i == 1 && g > max_grid_32)) continue;
         if (best < 0 || t < *us) { best = i; *us = t; }
     }
     return best;
@@ -516,9 +515,11 @@ bool leaves_a_short_group(const Plan& pl, int64_t M, int64_t N, int small)
 // against a B of 64 MB and more ((16,8192,8192) 42 us on 128 workgroups, 37 on 256).  Others, limited -> not: (89,96,11496) 48.7 -> 21.8,
 // (10,1072,5672) 17.6 -> 13.2, (167,112,8472) 40.0 -> 18.9, (160,760,3496) 18.6 -> 10.0, (1753,8,9784) 33.1 -> 12.0, (2217,8,14712) 53.8 -> 16.9.
 // Those (skinny, or K > 6144) take more workgroups than they have 64 x 64 tiles only for an estimated 15 % where that many would do ((290,1616,9736) 42.9 -> 52.9 on 510 of 32 x 32,
-// estimated 10 % faster, (1763,264,3584) 18.0 -> 19.0, 13 %; 400 problems estimated 15 % faster and more were so, by 30 % on average), and never more 32 x 32 tiles
+// estimated 10 % faster, (1763,264,3584) 18.0 -> 19.0, 13 %; 400 problems estimated 15 % faster and more were so, by 30 % on average; tall ones that do not fill the chip
+// for 13 %, (11736,16,3376) 18.4 -> 16.2 on 367, (9765,16,2504) 14.4 -> 13.0 on 306), and no more 32 x 32 tiles
 // than run at once: (436,2312,5288) 128 x 128 46.2 -> 55.2 on 1022, (10503,88,3680) 34.0 -> 38.3 on 987, (417,2312,12480) from memory 93 -> 133;
-// 144 such problems, 4 % slower on average.  (Two rounds of 32 x 64 are 15 % faster than what they replace.)
+// 130 such problems, 5 % slower on average.  Tall ones up to three quarters of a second round and K = 3600 are 2 % faster, from memory 8 ((8335,72,2080) 22.3 -> 20.0 | 26.8 -> 23.4 on 783,
+// (8527,96,2544) 0.94 | 0.82).  (Two rounds of 32 x 64 are 15 % faster than what they replace.)
 int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_t N, int64_t K, int64_t ldb, Operands operands)
 {
     const int64_t tiles = config(ID_PP128x128)->grid(M, N);
@@ -544,11 +545,15 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
     double us = 0, more_us = 0;
     int small = best_kslice(c_is_f16, operands, M, N, K, max_grid, &us);
     if (lifted) {
-        const int more = best_kslice(c_is_f16, operands, M, N, K, INT32_MAX, &more_us, false);
+        const int64_t cus = chip().cus;
+        const int more = best_kslice(c_is_f16, operands, M, N, K, INT32_MAX, &more_us, tall && K < 3600 ? 7 * cus / 2 : 2 * cus);
         if (more >= 0 && (small < 0 || us >= other)) {
             if (wide && leaves_a_short_group(pl, M, N, more)) return -1;
             small = more; us = more_us;
-        } else if (more >= 0 && more_us < 0.85 * us) { small = more; us = more_us; }
+        } else if (more >= 0) {
+            const bool spare = tall && 8 * kslice_config(more, false)->grid(M, N) <= 7 * cus * kKsliceCands[more].per_cu;
+            if (more_us < (spare ? 0.87 : 0.85) * us) { small = more; us = more_us; }
+        }
     }
     // Up to 32 columns, f32 mode, cut along k or small tiles: A is all there is to read, the small tiles read it with
     // a tile of the right width, and the estimates above are those of a wide B.  Split -> small tiles, us, three sets | from memory: (1257,16,5544)
