@@ -577,7 +577,8 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
         // in A it costs less: (1888,8,8264) 23.7 -> 14.7.  f32 mode: (14,1640,4976) 15.5 -> 20.7, (3,1792,4464) 11.9 -> 15.8, but (14,3744,2792) 16.0 -> 11.2
         // The plain form counts it where B is more than four times as wide as A is high: below, small tiles -> cut along k by the
         // term, us: (67,96,4104) 6.5 -> 12.0 | 10.4 -> 13.8, (84,128,4608) at a pitch of 64 more 8.4 -> 12.4 | 12.7 -> 16.8, (107,240,4632) 11.5 -> 12.7 | 14.6 -> 22.4.
-        if (form == Form::workspace ? N > M : wide) us += (M <= 32 ? 1.4 : M <= 128 ? 0.5 : 0.0) * (double)K / 1024.0;
+        // Nor below K = 2048, where no problem was held to the split: (105,4712,2032) 13.7 -> 16.2 | 17.3 -> 20.8, (69,6000,2024) 13.7 -> 15.5 | 17.6 -> 19.8.
+        if (form == Form::workspace ? N > M : wide && K >= 2048) us += (M <= 32 ? 1.4 : M <= 128 ? 0.5 : 0.0) * (double)K / 1024.0;
     }
     return small >= 0 && us < other ? ID_KSLICE + small : -1;
 }

@@ -14,7 +14,8 @@ def _name(f16, M, N, K, pad=0):
 def test_f32_up_to_four_times_as_wide_as_high():
     """B is not wide there: the small tiles are not charged for its latency ((67,96,4104) 6.5 us against 12.0 cut along k,
     from memory 10.4 against 13.8)."""
-    for M, N, K, pad in [(67, 96, 4104, 0), (96, 336, 4496, 8), (84, 128, 4608, 64), (107, 240, 4632, 64), (128, 408, 4048, 64)]:
+    for M, N, K, pad in [(67, 96, 4104, 0), (96, 336, 4496, 8), (84, 128, 4608, 64), (107, 240, 4632, 64), (128, 408, 4048, 64),
+                       (105, 4712, 2032, 0), (69, 6000, 2024, 0), (82, 5640, 2000, 0)]:           # (... nor at K < 2048)
         assert _name(0, M, N, K, pad).startswith("ks"), (M, N, K)
     # few rows against a wide B stay cut along k
     assert _name(0, 14, 1640, 4976) == "w4a_128x128x64" and _name(0, 3, 1792, 4464) == "w4a_128x128x64"
