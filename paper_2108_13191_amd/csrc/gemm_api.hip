@@ -531,12 +531,7 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
     if (form == Form::plain && K >= 2048) {
         if (pl.k_split > 1) {
             if (wide && M >= 16 && M < 128) return -1;
-            // Rows at lines, long k loops: the estimates (of three sets in turn) leave out what operands from memory cost the small tiles.  Cut -> small tiles, us,
-            // three sets | from memory, estimated 11 to 15 % faster: (205,1984,5504) at a pitch of 64 more 15.3 -> 18.0 | 18.3 -> 22.6, (3274,64,6144) 15.9 -> 15.1 | 18.1 -> 22.0,
-            // (2289,64,5632) 13.0 -> 13.2 | 16.7 -> 18.7, (721,64,6912) 12.8 -> 12.9 | 16.0 -> 17.5; smaller operands, shorter loops and rows within lines gain in both: (136,960,5504) 11 and 2 %,
-            // (157,4736,3520) 7 and 6, (929,96,6016) at a pitch of 8 more 5 and 14.
-            const bool slow_from_memory = (wide || tall) && operands == Operands::lines && (K > 6200 || (K >= 4500 && operand_mb(M, N, K) >= 19.5));
-            other *= slow_from_memory ? 0.83 : 0.9;
+            other *= 0.9;
         }
         lifted = c_is_f16 && (wide || tall || K > 6144) && !(M <= 32 && N * K >= (int64_t)1 << 25);
         if (lifted) max_grid = config(ID_T64)->grid(M, N);
@@ -568,6 +563,13 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
         const bool b_compact = ldb < 64;
         if (small >= 0 && (g <= cus ? K <= (b_compact ? 8704 : 5504) : 20 * g >= 29 * cus && K <= (!b_compact ? 4096 : N == 8 ? 8192 : 6144))) return ID_KSLICE + small;
     }
+    // Rows at lines, long k loops, f32 mode, skinny: the estimates (of three sets in turn) leave out what operands from memory cost the tiles that run two workgroups a
+    // compute unit, and the 32 x 64 ones against a wide B.  Cut -> small tiles, us, three sets | from memory, estimated 11 to 15 % faster: (205,1984,5504) at a pitch of 64 more, 32 x 64, 15.3 -> 18.0 |
+    // 18.3 -> 22.6, (3274,64,6144), 32 x 32, 15.9 -> 15.1 | 18.1 -> 22.0, (721,64,6912), 16 x 32, 12.8 -> 12.9 | 16.0 -> 17.5; 46 such problems 0.99 and 1.10 of the time on average.  Larger tiles,
+    // smaller operands, shorter loops and rows within lines gain: (3388,128,5376) at 64 more, 32 x 64, 18.3 -> 15.9 | 22.2 -> 21.2, (2047,448,5248), 64 x 64, 0.81 | 0.92 (but with 64 columns 32 x 64 are
+    // 0.75 to 0.89 of the time in turn and 0.94 to 1.13 from memory), (136,960,5504) 0.89 | 0.98, (157,4736,3520) 0.93 | 0.94.
+    if (pl.k_split > 1 && form == Form::plain && !c_is_f16 && (wide || tall) && operands == Operands::lines && (K > 6200 || (K >= 4500 && operand_mb(M, N, K) >= 19.5)) &&
+        (kKsliceCands[small >= 0 ? small : 0].per_cu == 2 || (wide && small == 3))) other *= 0.83 / 0.9;
     if (pl.k_split > 1) {
         if (form == Form::workspace) other += 5.0;                   // the passes before and after
         // A wide B that no call has left in the caches (split -> small tiles, us; its latency is spread over

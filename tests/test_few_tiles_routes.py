@@ -56,7 +56,7 @@ def test_f32_long_k_loops_with_rows_at_lines():
     for M, N, K, pad in [(205, 1984, 5504, 64), (2289, 64, 5632, 0), (3274, 64, 6144, 0), (145, 1472, 6400, 64), (721, 64, 6912, 0), (147, 704, 7744, 64), (173, 2048, 4864, 0)]:
         assert _name(0, M, N, K, pad) == "w4a_128x128x64", (M, N, K)
     # smaller operands up to K = 6200, shorter k loops, clearly better estimates, rows within a line
-    for M, N, K, pad in [(136, 960, 5504, 0), (164, 768, 5888, 0), (157, 4736, 3520, 0), (3588, 192, 3584, 0), (5605, 128, 2432, 0), (159, 640, 6336, 0), (929, 96, 6016, 8), (508, 64, 5056, 0)]:
+    for M, N, K, pad in [(136, 960, 5504, 0), (164, 768, 5888, 0), (157, 4736, 3520, 0), (3588, 192, 3584, 0), (5605, 128, 2432, 0), (159, 640, 6336, 0), (3388, 128, 5376, 64), (6495, 64, 5120, 0), (2047, 448, 5248, 0), (1456, 320, 5696, 64), (183, 5376, 4608, 64), (929, 96, 6016, 8), (508, 64, 5056, 0)]:
         assert _name(0, M, N, K, pad).startswith("ks"), (M, N, K)
 
 
