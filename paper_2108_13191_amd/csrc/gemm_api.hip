@@ -555,13 +555,14 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
     // 15.1 -> 8.3 | 18.8 -> 10.9, (2688,8,6584) 15.8 -> 9.3 | 20.3 -> 12.7, (479,8,7872) 12.6 -> 9.6 | 12.6 -> 9.8,
     // (16384,16,2560) 21.9 -> 14.8.  Every workgroup reads all of B, so the gain shrinks as k grows: 150 problems, 0.35 to 0.6 of the time at K = 2048 to 4096, 0.6 to 0.9 at 5500 to 8700, where
     // (1228,32,8576) 12.6 -> 11.4 | 15.5 -> 17.5 is the worst; beyond, (334,24,15880) 14.5 -> 18.6, (6000,32,9000) 30.5 -> 32.1.  Rows of B on lines of their own (a pitch of 64 and more) come to
-    // that sooner: (1465,16,5520) 0.79 | 0.91, (6173,8,5856) 0.83 | 1.15, (1358,32,8536) 15.8 -> 17.3 | 20.2 -> 26.3.  So does a second round of workgroups (8 columns (13312,8,7432) 50.3 -> 45.2 |
-    // 50.4 -> 45.2; more (14081,24,5744) 0.91 | 0.91, (13118,16,6208) 35.0 -> 35.7, (13988,32,6784) 39.6 -> 43.4; pitch of 64 more (14737,16,3560) 0.98 | 0.99, (13191,16,5008) 39.8 -> 42.7), which
+    // that sooner: (1465,16,5520) 0.79 | 0.91, (614,16,6120) 0.83 | 0.95, (6173,8,5856) 0.83 | 1.15, (313,8,7368) 1.03 | 1.16, (1358,32,8536) 15.8 -> 17.3 | 20.2 -> 26.3.  So does a second round
+    // of workgroups: 8 columns (15488,8,8616) 0.91 | 0.91; 16 and 24 (13068,16,7344) 48.5 -> 45.5 | 48.8 -> 45.3, (13118,16,6208) 35.0 -> 35.7, (12176,16,8448) 1.04 | 1.04; 32 (14182,32,5032) 0.96 | 0.96, (13988,32,6784)
+    // 39.6 -> 43.4; pitch of 64 more (14737,16,3560) 0.98 | 0.99, (13191,16,5008) 39.8 -> 42.7.  It
     // must not be nearly empty: (9421,16,9592) 46.1 -> 55.5, (9000,8,6000) 30.1 -> 31.3.
     if (pl.k_split > 1 && form == Form::plain && !c_is_f16 && tall && N <= 32) {
         const int64_t g = kslice_config(1, false)->grid(M, N), cus = chip().cus;       // tiles of 32 x 32
         const bool b_compact = ldb < 64;
-        if (small >= 0 && (g <= cus ? K <= (b_compact ? 8704 : 5504) : 20 * g >= 29 * cus && K <= (!b_compact ? 4096 : N == 8 ? 8192 : 6144))) return ID_KSLICE + small;
+        if (small >= 0 && (g <= cus ? K <= (b_compact ? 8704 : 6200) : 20 * g >= 29 * cus && K <= (!b_compact ? 4096 : N == 8 ? 8704 : N <= 24 ? 7744 : 6144))) return ID_KSLICE + small;
     }
     // Rows at lines, long k loops, f32 mode, skinny: the estimates (of three sets in turn) leave out what operands from memory cost the tiles that run two workgroups a
     // compute unit, and the 32 x 64 ones against a wide B.  Cut -> small tiles, us, three sets | from memory, estimated 11 to 15 % faster: (205,1984,5504) at a pitch of 64 more, 32 x 64, 15.3 -> 18.0 |
