@@ -392,11 +392,17 @@ int long_k_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K)
 // K = 2048, 13 to 3000, 17 to 19 beyond, with a k tail as well (60 problems, 7 to 22 %); from memory 2 % slower up to K = 3000 ((1152,2432,2048) 24.9 -> 25.7,
 // (2415,1280,1664) 22.6 -> 23.9, but (2048,2048,2048) 28.5 -> 28.2; its 160 KB of LDS keep a launch's workgroups from starting beside the last one's, but that this is why was not shown), 0 to 2 % faster
 // beyond.  Below 23 k steps it gains 6 % in the one use and loses 4 in the other ((2048,2048,1280) 19.4 -> 18.4 | 21.3 -> 22.4, (12608,256,1280) 16.7 -> 16.5 |
-// 21.1 -> 22.7).  Where three calls' A, B and C exceed the last-level cache every use is one from memory: 61 problems of more than 86 MB, 0.81 to 1.07 of the
-// time in turn, 0.92 to 1.08 from memory, on average 0.97 and 1.00: (12672,256,2944) 32.5 -> 34.4, (133,11776,4736) 44.2 -> 47.3, (180,16000,5504) 59.6 -> 62.3.
+// 21.1 -> 22.7).  Where three calls' A, B and C exceed the last-level cache every use is one from memory: 54 problems of more than 86 MB with one or two rows or columns of tiles
+// 0.81 to 1.07 of the time in turn, 0.92 to 1.08 from memory, on average 0.97 and 1.00: (12672,256,2944) 32.5 -> 34.4, (133,11776,4736) 44.2 -> 47.3, (180,16000,5504) 59.6 -> 62.3; with
+// three or more (17 problems) 0.77 to 1.02 and 0.92 to 1.03, on average 0.93 and 0.98: (428,6848,5248) 52.0 -> 40.1 | 51.7 -> 47.6, (9536,320,5888) 0.92 | 0.94, (336,10752,5376) 1.00 | 1.00.
 // Beyond K = 2048 the five-stage kernel is up to 3 % faster still, but tests/test_gpu_long_k.py states that 2048^2 at K = 4096 runs on a kernel of the phase-alternating family.
 // Below 28 k steps 55 MB are the line: (134,15744,1536) 19.9 -> 21.3 | 21.3 -> 24.5, (190,14784,1472) 19.1 -> 21.4 | 21.1 -> 22.2, (256,16000,1664) 22.4 -> 21.5 | 24.3 -> 25.5; at 44 to 55 MB still 6 % the other way round in turn.
-double two_groups_mb(int64_t K) { return K < 28 * BK_STEP ? 55.0 : 86.0; }
+bool two_groups_fit(int64_t rows, int64_t N, int64_t K)
+{
+    const double mb = operand_mb(rows, N, K) + 4e-6 * (double)rows * (double)N;
+    if (K < 28 * BK_STEP) return mb <= 55.0;
+    return mb <= 86.0 || (rows > 256 && N > 256);
+}
 int deep_ring_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K, Operands operands)
 {
     const int64_t tiles = config(ID_RING128)->grid(rows, N), cus = chip().cus;
@@ -404,7 +410,7 @@ int deep_ring_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t 
     if (operands != Operands::lines) return K >= 6144 ? ID_RING128 : id;
     const int64_t tail = K % 64 ? 1536 : 0;
     if (2 * tiles <= cus) return K >= (c_is_f16 ? 1024 : 1536) + tail ? ID_RING128 : id;
-    if (!c_is_f16) return K >= 6144 ? ID_RING128 : K >= 1472 && operand_mb(rows, N, K) + 4e-6 * (double)rows * (double)N <= two_groups_mb(K) ? ID_PP128_K2 : id;
+    if (!c_is_f16) return K >= 6144 ? ID_RING128 : K >= 1472 && two_groups_fit(rows, N, K) ? ID_PP128_K2 : id;
     return K >= 2048 + tail ? ID_RING128 : id;
 }
 

@@ -80,7 +80,7 @@ def test_f32_two_k_groups():
     """From 23 k steps on and where three calls' matrices fit the last-level cache: (12672,256,2944) 34.4 us, 32.5 on the
     phase-alternating kernel, (12608,256,1280) from memory 22.7 and 21.1."""
     two = "pp128x128x64_w2x2_k2"
-    for M, N, K in [(2048, 2048, 2048), (1512, 1536, 1472), (4022, 896, 2944), (2048, 2048, 4096), (335, 8192, 4032), (11712, 192, 3008), (2048, 1920, 1984), (140, 12672, 1664), (256, 11968, 1920)]:
+    for M, N, K in [(2048, 2048, 2048), (1512, 1536, 1472), (4022, 896, 2944), (2048, 2048, 4096), (335, 8192, 4032), (11712, 192, 3008), (2048, 1920, 1984), (140, 12672, 1664), (256, 11968, 1920), (428, 6848, 5248), (9536, 320, 5888)]:
         assert _name(0, M, N, K) == two, (M, N, K)
     for M, N, K in [(12608, 256, 1280), (2048, 2048, 1408), (12672, 256, 2944), (133, 11776, 4736), (180, 16000, 5504), (150, 13440, 5184), (134, 15744, 1536), (256, 16000, 1664)]:
         assert _name(0, M, N, K) == "pp128x128x64_w2x4_mi16", (M, N, K)
