@@ -521,8 +521,8 @@ bool leaves_a_short_group(const Plan& pl, int64_t M, int64_t N, int small)
 // against a B of 64 MB and more ((16,8192,8192) 42 us on 128 workgroups, 37 on 256).  Others, limited -> not: (89,96,11496) 48.7 -> 21.8,
 // (10,1072,5672) 17.6 -> 13.2, (167,112,8472) 40.0 -> 18.9, (160,760,3496) 18.6 -> 10.0, (1753,8,9784) 33.1 -> 12.0, (2217,8,14712) 53.8 -> 16.9.
 // Those (skinny, or K > 6144) take more workgroups than they have 64 x 64 tiles only for an estimated 15 % where that many would do ((290,1616,9736) 42.9 -> 52.9 on 510 of 32 x 32,
-// estimated 10 % faster, (1763,264,3584) 18.0 -> 19.0, 13 %; 400 problems estimated 15 % faster and more were so, by 30 % on average; tall ones that do not fill the chip
-// for 13 %, (11736,16,3376) 18.4 -> 16.2 on 367, (9765,16,2504) 14.4 -> 13.0 on 306), and no more 32 x 32 tiles
+// estimated 10 % faster, (1763,264,3584) 18.0 -> 19.0, 13 %; 400 problems estimated 15 % faster and more were so, by 30 % on average; tall ones that do not fill the chip or have up to 32 columns
+// for 13 %, (11736,16,3376) 18.4 -> 16.2 on 367, (4345,96,2616) 15.5 -> 14.2 on 408, (14949,16,2592) 16.4 -> 14.2 on 468), and no more 32 x 32 tiles
 // than run at once: (436,2312,5288) 128 x 128 46.2 -> 55.2 on 1022, (10503,88,3680) 34.0 -> 38.3 on 987, (417,2312,12480) from memory 93 -> 133;
 // 130 such problems, 5 % slower on average.  Tall ones up to three quarters of a second round and K = 3600 are 2 % faster, from memory 8 ((8335,72,2080) 22.3 -> 20.0 | 26.8 -> 23.4 on 783,
 // (8527,96,2544) 0.94 | 0.82).  (Two rounds of 32 x 64 are 15 % faster than what they replace.)
@@ -552,7 +552,7 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
             if (wide && leaves_a_short_group(pl, M, N, more)) return -1;
             small = more; us = more_us;
         } else if (more >= 0) {
-            const bool spare = tall && 8 * kslice_config(more, false)->grid(M, N) <= 7 * cus * kKsliceCands[more].per_cu;
+            const bool spare = tall && (N <= 32 || 8 * kslice_config(more, false)->grid(M, N) <= 7 * cus * kKsliceCands[more].per_cu);
             if (more_us < (spare ? 0.87 : 0.85) * us) { small = more; us = more_us; }
         }
     }

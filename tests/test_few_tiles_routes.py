@@ -29,7 +29,7 @@ def test_f16_tiles_of_32_by_32_in_a_second_round():
     for M, N, K, pad in [(290, 1616, 9736, 8), (1763, 264, 3584, 64), (5391, 88, 3200, 0), (196, 2328, 3032, 0)]:
         assert _name(1, M, N, K, pad) == "ks64x64x64_k8", (M, N, K)
     # tall ones up to three quarters of a second round; and one round for an estimated 13 % where it leaves room
-    for M, N, K, pad in [(8335, 72, 2080, 0), (8527, 96, 2544, 0), (8213, 88, 3208, 0), (11736, 16, 3376, 0), (9765, 16, 2504, 0), (4330, 96, 3480, 64)]:
+    for M, N, K, pad in [(8335, 72, 2080, 0), (8527, 96, 2544, 0), (8213, 88, 3208, 0), (11736, 16, 3376, 0), (9765, 16, 2504, 0), (4330, 96, 3480, 64), (14949, 16, 2592, 0)]:
         assert _name(1, M, N, K, pad) == "ks32x32x64_k8", (M, N, K)
     # two rounds of 32 x 64, and one round of small tiles for a third: as before
     for M, N, K, pad in [(2316, 400, 2392, 0), (2322, 392, 11040, 8), (131, 6376, 12240, 0), (203, 4176, 2184, 64)]:
