@@ -10,8 +10,10 @@
 // out of the L2s, and 128 KB in flight at 100 GB/s would be 1.3 us of latency; why the copies take so long was not found.  Neither the order
 // in which a step is fetched (LDS image or rows) nor behind which MFMAs the copies stand changes it by more than 1 %.  The eight wavefronts of 64 x 32 in
 // gemm_pingpong.hip read 96 KB of LDS a step where this split reads 64, and meet four barriers: 0.5 us.
-// Outside the loop, start and C take about 9 us, which nothing hides but the last two or three steps.
-// 2048^3 f32 25.1 -> 22.7 us when it was written, 24.2 -> 21.7 and 26.6 -> 23.4 in other sessions on other cards.
+// Outside the loop, start and C take about 8 us: an empty launch of this size 2.4, the stores and the sums' way through LDS 4.5 (17 MB; a kernel that
+// only stores them 1.8 more than an empty one), the first operands; the read of C, requested during the last steps, 1.
+// 2048^3 f32 25.1 -> 22.7 us when it was written, 24.2 -> 21.7 and 26.6 -> 23.4 in other sessions on other cards; C requested earlier, stored by whole rows and
+// one barrier less 23.7 -> 23.0, (2048,2048,4096) 37.5 -> 36.2, (2048,2048,1536) 20.2 -> 19.6, (1152,2432,2048) 19.4 -> 19.0.
 //
 // Automatic selection gives it f32 problems only (deep_ring_if_it_pays in gemm_api.hip).  f16 C, when forced, us, the kernel selected -> this one, three sets | from
 // memory: from K = 2048 on the five-stage kernel is ahead, (2048,2048,2048) 19.3 -> 20.0 | 24.1 -> 24.9, (4022,896,4096) 30.1 -> 30.7 | 42.0 -> 42.5; below, the phase-alternating
@@ -28,6 +30,7 @@ constexpr int QB = 128;                                 // tile rows and columns
 constexpr int QA_BUF = QB * BK * 2, QSTAGE = 2 * QA_BUF, QSTAGES = 5;      // 16 KB of A and of B a stage; 160 KB
 constexpr int QB_ROW = QB * 2;                          // bytes per k row of B
 constexpr int QT_PITCH = 64 * 4 + 16, QT_HALF = 32 * QT_PITCH;             // epilogue: 32 rows of a wavefront's 64 x 64 block
+constexpr int CQ = 2, C_STEPS = 8 / CQ;                 // loads of C a wavefront requests behind each of its last copying steps; such steps
 
 // Phase P: the group of step P reads it, the other one multiplies step P - 1 and issues the copies of step P + 4,
 // into the stage whose last reader was phase P - 1.  They have landed by the end of phase P + 3, where
@@ -163,17 +166,19 @@ __global__ __launch_bounds__(512) void gemm_pp128_kernel(const TiledParams p)
     };
 
     // ---- C: addresses -------------------------------------------------------------------------
-    // The wavefront's block of sums goes through LDS in halves of 32 rows, X stores the upper, Y the lower ones.
+    // A wavefront adds and stores 16 whole rows of the tile, two (512 bytes of f32) an instruction: rows of C a power of two apart are
+    // written faster that way than four rows of 256 bytes at a time (a kernel that only stores such tiles of a 2048 x 2048 f32 C 5.3 -> 4.8 us, at a pitch of 64 more 4.6 both).
     typedef typename CVec4<CT>::type ctx4;
-    const int c_col = n0 + wn_base + 4 * (lane & 15), c_row = m0 + wm_base + 32 * grp + (lane >> 4);
+    constexpr int RPP = 2;                                            // rows an instruction
+    const int c_col = n0 + 4 * (lane & 31), c_row = m0 + 16 * wave_all + (lane >> 5);
     const bool col_ok = !edge || c_col < p.N;                         // N is a multiple of 8: all 4 columns or none
     CT* const cptr = (CT*)p.C + (int64_t)c_row * p.ldc + c_col;
     ctx4 cin[8];
-    auto fetch_c = [&]() {
+    auto fetch_c = [&](int p0, int p1) {
 #pragma unroll
-        for (int ps = 0; ps < 8; ps++) {
-            const bool ok = col_ok && (!edge || c_row + 4 * ps < p.M);
-            const CT* src = ok ? cptr + (int64_t)(4 * ps) * p.ldc : (const CT*)p.C + (int64_t)m0 * p.ldc + n0;
+        for (int ps = p0; ps < p1; ps++) {
+            const bool ok = col_ok && (!edge || c_row + RPP * ps < p.M);
+            const CT* src = ok ? cptr + (int64_t)(RPP * ps) * p.ldc : (const CT*)p.C + (int64_t)m0 * p.ldc + n0;
             cin[ps] = *reinterpret_cast<const ctx4*>(src);
         }
     };
@@ -199,13 +204,33 @@ __global__ __launch_bounds__(512) void gemm_pp128_kernel(const TiledParams p)
         st += 2 * QSTAGE;
         if (st >= QSTAGES * QSTAGE) st -= QSTAGES * QSTAGE;
     };
-    for (; s + 5 < kt_full; next()) {
+    for (; s + 5 + 2 * C_STEPS < kt_full; next()) {
         read_fragments(st);
         lds_done();
         asm volatile("s_waitcnt vmcnt(8)" ::: "memory");              // step s + 1 has landed, step s + 3 may be on its way
         phase_barrier();
         multiply(s, st, I1{});
         phase_barrier();
+    }
+    // The last ones request C behind their copies, two loads each, and C is then there when the loop ends.  (All 8 behind the
+    // last copies, as before: the loop was done before C had come.)  The loads come from memory and loads complete in order, but
+    // a copy has the three steps of its own lead to wait for them.  One load a step over eight steps, or four over two, gain less.
+#pragma unroll
+    for (int c = 0; c < C_STEPS; c++) {
+        if (s + 5 < kt_full) {
+            read_fragments(st);
+            lds_done();
+            asm volatile("s_waitcnt vmcnt(%0)" :: "n"(8 + CQ * (c < 2 ? c : 2)) : "memory");      // as above; what was requested of C behind the copies of step s + 1 may be on its way too
+            phase_barrier();
+            multiply(s, st, I1{});
+            fetch_c(CQ * c, CQ * c + CQ);
+            __builtin_amdgcn_sched_barrier(0);
+            phase_barrier();
+            next();
+        } else {
+            fetch_c(CQ * c, CQ * c + CQ);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
     if constexpr (TAIL) {
         for (; s + 5 < KT; next()) {                                  // at most once: fetches the k tail
@@ -218,13 +243,12 @@ __global__ __launch_bounds__(512) void gemm_pp128_kernel(const TiledParams p)
             phase_barrier();
         }
     }
-    fetch_c();                                                        // 8 loads, on their way under the last steps
-    __builtin_amdgcn_sched_barrier(0);
     for (; s < KT; next()) {
         read_fragments(st);
         lds_done();
-        if (s + 3 < kt_full) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");     // step s + 1; step s + 3 and C may be on their way
-        else                 asm volatile("s_waitcnt vmcnt(8)" ::: "memory");      // step s + 1; C may be
+        // (at least 8 + 2 CQ loads and copies were issued behind the copies of step s + 1, or CQ where those are the last ones)
+        if (s + 3 < kt_full) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(8 + 2 * CQ) : "memory");     // step s + 1; step s + 3 and the last of C may be on their way
+        else                 asm volatile("s_waitcnt vmcnt(%0)" :: "n"(CQ) : "memory");             // step s + 1; the last of C may be
         phase_barrier();
         multiply(s, st, I0{});
         if (s + 1 < KT) phase_barrier();
@@ -236,9 +260,9 @@ __global__ __launch_bounds__(512) void gemm_pp128_kernel(const TiledParams p)
 #pragma unroll
         for (int e = 0; e < 4; e++) bias4[e] = (float)reinterpret_cast<const CT*>(p.bias)[c_col + e];
     }
-    phase_barrier();                                                  // nobody reads operands any more
+    // No barrier in front of these writes: the group that multiplies the last step has read it into registers before the last barrier, the
+    // other group, which read its last step earlier, writes its sums meanwhile.  Block ((group, half of the rows), wavefront) of 32 rows x 64 columns each.
     const uint32_t t_w = smem_base + (uint32_t)(lane & 15) * QT_PITCH + (uint32_t)(lane >> 4) * 16;
-    const uint32_t t_r = smem_base + (uint32_t)(lane >> 4) * QT_PITCH + (uint32_t)(lane & 15) * 16;
 #pragma unroll
     for (int h = 0; h < 2; h++)
 #pragma unroll
@@ -248,14 +272,16 @@ __global__ __launch_bounds__(512) void gemm_pp128_kernel(const TiledParams p)
                 *(__attribute__((address_space(3))) floatx4*)(uintptr_t)(t_w + (uint32_t)((grp * 2 + h) * 4 + wave) * QT_HALF + r * 16 * QT_PITCH + fn * 64) = acc[2 * h + r][fn];
     lds_done();
     phase_barrier();
+    const uint32_t t_r = smem_base + (uint32_t)(((wave_all >> 1) & 1) * 4 + (wave_all >> 2) * 2 + ((lane >> 4) & 1)) * QT_HALF
+                                   + (uint32_t)(16 * (wave_all & 1) + (lane >> 5)) * QT_PITCH + (uint32_t)(lane & 15) * 16;
 #pragma unroll
     for (int ps = 0; ps < 8; ps++) {
-        floatx4 s4 = *(__attribute__((address_space(3))) const floatx4*)(uintptr_t)(t_r + (uint32_t)(grp * 4 + wave) * QT_HALF + 4 * ps * QT_PITCH);
-        s4 += *(__attribute__((address_space(3))) const floatx4*)(uintptr_t)(t_r + (uint32_t)(8 + grp * 4 + wave) * QT_HALF + 4 * ps * QT_PITCH);
+        floatx4 s4 = *(__attribute__((address_space(3))) const floatx4*)(uintptr_t)(t_r + RPP * ps * QT_PITCH);
+        s4 += *(__attribute__((address_space(3))) const floatx4*)(uintptr_t)(t_r + 8 * QT_HALF + RPP * ps * QT_PITCH);
         ctx4 o;
 #pragma unroll
         for (int e = 0; e < 4; e++) o[e] = (CT)epilogue_value(s4[e] + (float)cin[ps][e], bias4[e], p.relu);     // f16: one rounding, to nearest even
-        if (col_ok && (!edge || c_row + 4 * ps < p.M)) *reinterpret_cast<ctx4*>(cptr + (int64_t)(4 * ps) * p.ldc) = o;
+        if (col_ok && (!edge || c_row + RPP * ps < p.M)) *reinterpret_cast<ctx4*>(cptr + (int64_t)(RPP * ps) * p.ldc) = o;
     }
 }
 

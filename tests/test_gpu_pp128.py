@@ -40,6 +40,22 @@ def test_every_exit_of_the_k_loop(oracle_mod, tail):
         assert np.array_equal(got, want), (M, N, K, mode)
 
 
+@pytest.mark.parametrize("tail", [0, 40])
+def test_loops_that_request_c_among_their_copies(oracle_mod, tail):
+    """14 to 21 whole k steps: the main loop runs, and either group leaves it at either parity."""
+    binding.force_config(config_id(NAME))
+    for steps in range(14, 22):
+        K = 64 * steps + tail
+        M, N = ((256, 128), (130, 272), (300, 136))[steps % 3]
+        mode = ("f32", "f16")[steps // 2 % 2]
+        A, B, _ = wl.make_inputs(M, N, K, "int2", "zeros", seed=10450 + K)
+        C0 = np.random.default_rng(K).integers(-4, 5, size=(M, N)).astype(CDT[mode])
+        got = run_gemm(A, B, C0, mode, ldc=N + 3, offs=(0, 0, 1))
+        Cref, _ = oracle_mod.gemm_f16(A, B, C0)
+        want = oracle_mod.round_to_f32(Cref) if mode == "f32" else Cref.astype(np.float16)
+        assert np.array_equal(got, want), (M, N, K, mode)
+
+
 def test_selected(oracle_mod):
     M, N, K = 2048, 1920, 2048
     assert binding.query_config(0, M, N, K, 16, K, 16, N, 16, N)["name"] == NAME
