@@ -1,4 +1,5 @@
-"""Thin ctypes binding of the C ABI in include/gemm_f16.h.
+"""Thin binding of the C ABI in include/gemm_f16.h: ctypes, and for the GEMM entry points themselves a small extension
+(csrc/fastcall.c) in front of it that marshals the usual arguments in native code.
 
 Argument marshalling only: every step of the GEMM runs in the HIP kernels of
 libgemm_f16.so.  There is no fallback: if the library has not been built (run
@@ -12,6 +13,11 @@ import ctypes
 import os
 
 import contextlib
+
+try:
+    from . import _fastcall
+except ImportError:                     # not built, or for another Python: everything goes through ctypes
+    _fastcall = None
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libgemm_f16.so")
@@ -88,6 +94,10 @@ def load() -> ctypes.CDLL:
         lib.gemm_f16_describe_config.restype = ci
         lib.gemm_f16_force_config.argtypes = [ci]
         lib.gemm_f16_force_config.restype = ci
+        # where the entry points are, for _fastcall
+        for name in ("gemm_f16_f32acc", "gemm_f16_f16acc", "gemm_f16_f16acc_static_workspace", "gemm_f16_f32acc_bias_act",
+                     "gemm_f16_f16acc_bias_act", "gemm_f16_f16acc_workspace"):
+            setattr(lib, name + "_address", ctypes.cast(getattr(lib, name), vp).value)
         _libs[_active] = lib
     return _libs[_active]
 
@@ -100,14 +110,27 @@ def _ptr(x) -> int:
     return int(x)
 
 
+def _no_fast_way(*args):
+    return NotImplemented
+
+
+# The entry points below first ask one of these, which takes ints, None and objects with data_ptr() and returns NotImplemented, having
+# called nothing, for anything else.
+_plain, _bias_act, _workspace = (_fastcall.plain, _fastcall.bias_act, _fastcall.workspace) if _fastcall else (_no_fast_way,) * 3
+
+
 def gemm_f16_f32acc(M, N, K, A, lda, B, ldb, C, ldc, stream=0) -> int:
     """C (f32) += A (f16) @ B (f16); returns the library's status code."""
-    return load().gemm_f16_f32acc(M, N, K, _ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, _ptr(stream))
+    lib = load()
+    rc = _plain(lib.gemm_f16_f32acc_address, M, N, K, A, lda, B, ldb, C, ldc, stream)
+    return rc if rc is not NotImplemented else lib.gemm_f16_f32acc(M, N, K, _ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, _ptr(stream))
 
 
 def gemm_f16_f16acc(M, N, K, A, lda, B, ldb, C, ldc, stream=0) -> int:
     """C (f16) += A (f16) @ B (f16), f32 accumulation, one rounding on store."""
-    return load().gemm_f16_f16acc(M, N, K, _ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, _ptr(stream))
+    lib = load()
+    rc = _plain(lib.gemm_f16_f16acc_address, M, N, K, A, lda, B, ldb, C, ldc, stream)
+    return rc if rc is not NotImplemented else lib.gemm_f16_f16acc(M, N, K, _ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, _ptr(stream))
 
 
 def gemm_f16_f16acc_workspace_bytes(M, N, K) -> int:
@@ -117,12 +140,16 @@ def gemm_f16_f16acc_workspace_bytes(M, N, K) -> int:
 
 def gemm_f16_f16acc_workspace(M, N, K, A, lda, B, ldb, C, ldc, workspace, workspace_bytes, stream=0) -> int:
     """gemm_f16_f16acc with caller-provided scratch memory (device, 16-byte aligned) for split-k plans."""
-    return load().gemm_f16_f16acc_workspace(M, N, K, _ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, _ptr(workspace), workspace_bytes, _ptr(stream))
+    lib = load()
+    rc = _workspace(lib.gemm_f16_f16acc_workspace_address, M, N, K, A, lda, B, ldb, C, ldc, workspace, workspace_bytes, stream)
+    return rc if rc is not NotImplemented else lib.gemm_f16_f16acc_workspace(M, N, K, _ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, _ptr(workspace), workspace_bytes, _ptr(stream))
 
 
 def gemm_f16_f16acc_static_workspace(M, N, K, A, lda, B, ldb, C, ldc, stream=0) -> int:
     """gemm_f16_f16acc_workspace on the library's own fixed scratch array: allocates nothing."""
-    return load().gemm_f16_f16acc_static_workspace(M, N, K, _ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, _ptr(stream))
+    lib = load()
+    rc = _plain(lib.gemm_f16_f16acc_static_workspace_address, M, N, K, A, lda, B, ldb, C, ldc, stream)
+    return rc if rc is not NotImplemented else lib.gemm_f16_f16acc_static_workspace(M, N, K, _ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, _ptr(stream))
 
 
 ACT_NONE, ACT_RELU = 0, 1
@@ -130,12 +157,16 @@ ACT_NONE, ACT_RELU = 0, 1
 
 def gemm_f16_f32acc_bias_act(M, N, K, A, lda, B, ldb, C, ldc, bias, act, stream=0) -> int:
     """C (f32) = act(C + A @ B + bias[None, :]); bias f32 device vector or None."""
-    return load().gemm_f16_f32acc_bias_act(M, N, K, _ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, _ptr(bias), act, _ptr(stream))
+    lib = load()
+    rc = _bias_act(lib.gemm_f16_f32acc_bias_act_address, M, N, K, A, lda, B, ldb, C, ldc, bias, act, stream)
+    return rc if rc is not NotImplemented else lib.gemm_f16_f32acc_bias_act(M, N, K, _ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, _ptr(bias), act, _ptr(stream))
 
 
 def gemm_f16_f16acc_bias_act(M, N, K, A, lda, B, ldb, C, ldc, bias, act, stream=0) -> int:
     """C (f16) = act(C + A @ B + bias[None, :]), f32 arithmetic, one rounding on store; bias f16 or None."""
-    return load().gemm_f16_f16acc_bias_act(M, N, K, _ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, _ptr(bias), act, _ptr(stream))
+    lib = load()
+    rc = _bias_act(lib.gemm_f16_f16acc_bias_act_address, M, N, K, A, lda, B, ldb, C, ldc, bias, act, stream)
+    return rc if rc is not NotImplemented else lib.gemm_f16_f16acc_bias_act(M, N, K, _ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, _ptr(bias), act, _ptr(stream))
 
 
 def strerror(code: int) -> str:

@@ -1,6 +1,7 @@
 """Build the HIP libraries in-tree for gfx950 with hipcc.
 
 libgemm_f16.so         the product: the C ABI of include/gemm_f16.h and the kernels it selects
+_fastcall.*.so         the binding's way into the product's entry points without ctypes (csrc/fastcall.c, host code only)
 libgemm_f16_ladder.so  the same sources compiled with -DGEMM_F16_LADDER plus csrc/ladder/*.hip: the
                        comparison kernels and ablation rows appended to the configuration table
                        (never selected; tests and profiles reach them by forcing their ids)
@@ -12,11 +13,13 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgemm_f16.so")
+FASTCALL = os.path.join(HERE, "_fastcall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 LADDER_LIB = os.path.join(HERE, "libgemm_f16_ladder.so")
 SOURCES = ["gemm_api.hip", "gemm_generic.hip", "gemm_unaligned.hip", "gemm_unaligned_pp.hip", "gemm_kslice.hip", "gemm_tiled.hip", "gemm_pingpong.hip", "gemm_pp128.hip", "gemm_w4a.hip", "gemm_w4a128.hip", "gemm_splitk_f16.hip"]
 LADDER_SOURCES = ["ladder/gemm_w4.hip", "ladder/gemm_overlap.hip", "ladder/gemm_interleaved.hip"]
@@ -37,10 +40,20 @@ def _compile(src: str, obj: str, extra, verbose: bool) -> str:
     return res.stdout + res.stderr
 
 
+def build_fastcall() -> None:
+    """The binding works without it (through ctypes, a microsecond a call slower), so a missing Python.h is no error."""
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        print(f"no Python.h in {include}: the binding will call through ctypes")
+        return
+    subprocess.run(["gcc", "-O2", "-Wall", "-std=c11", "-fPIC", "-shared", "-I" + include, "-o", FASTCALL, os.path.join(CSRC, "fastcall.c")], check=True)
+
+
 def build(verbose: bool = False, ladder: bool = True, extra=()) -> str:
     """Compile every source (in parallel) and link the product library and, with `ladder`,
     the ladder library.  Returns the product library's path."""
     os.makedirs(OBJ, exist_ok=True)
+    build_fastcall()
     jobs = [(s, os.path.join(OBJ, s.replace("/", "_") + ".o"), list(extra)) for s in SOURCES]
     if ladder:
         jobs += [(s, os.path.join(OBJ, s.replace("/", "_") + ".ladder.o"), ["-DGEMM_F16_LADDER", *extra])
