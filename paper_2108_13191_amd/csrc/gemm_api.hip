@@ -341,6 +341,19 @@ int chained_if_it_pays(int id, int64_t rows, int64_t N, int64_t K)
     return c->grid(rows, N) < config(ID_PP256)->grid(rows, N) ? id_chained() : id;
 }
 
+// More 128 x 128 tiles than compute units but no more than two each, and 128 x 256 tiles for at most one each: from 17 k steps on the
+// latter are faster than two workgroups of the former sharing a compute unit, which launch_cost prices as if it were a whole round of one.  128 x 128 -> 128 x 256,
+// us, three sets of operands (and share of the time on three sets | one set | from memory, 70 problems below K = 2900, from where launch_cost takes them by itself: 0.82 to
+// 0.98 from K = 1200 on, 0.86 | 0.86 | 0.92 from K = 1600 on): (4472,1016,2904) f32 54.1 -> 42.1, (2560,2560,2560) f32 41.8 -> 40.6, f16 41.5 -> 38.8, (5353,1256,1152) f16 at a pitch of 8 more 26.5 -> 23.2,
+// (2363,2144,1896) f16 0.86 | 0.85 | 0.92, (2387,1712,1112) f16 0.96 | 0.96 | 0.97, (3407,1656,1536) f32 0.95 | 0.95 | 1.01; the worst is (5409,1104,1144) f16 1.04 in all uses.
+// Below it depends: K = 850 to 1060 0.95 to 1.01, but (2353,2048,824) f16 1.07 | 1.11 | 1.08, (684,5600,960) f16 1.04 | 1.08 | 1.03; K = 500 to 700 on average 1.03.
+int one_round_if_it_pays(int id, int64_t M, int64_t N, int64_t K)
+{
+    if (id != ID_PP128x128 || K < 17 * BK_STEP) return id;
+    const int64_t tiles = config(ID_PP128x128)->grid(M, N), cus = chip().cus;
+    return tiles > cus && tiles <= 2 * cus && config(ID_PP128)->grid(M, N) <= cus ? ID_PP128 : id;
+}
+
 // Long k loops take the four-wavefront kernel, and so do f32 problems of at most one 256 x 256
 // tile per compute unit: there nothing else hides the read of C, which that kernel does inside
 // its k loop (from 36 k steps on).  Measured against the plain / chained 256 x 256 form, all
@@ -597,6 +610,7 @@ Plan select_large_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void
 {
     Plan pl = select_plan_unchained(c_is_f16, M, N, K, A, lda, B, ldb, ldc);
     if ((g_forced >= 0 && g_forced < num_configs()) || pl.id == ID_GENERIC) return pl;        // a forced configuration runs as it is
+    if (pl.id2 < 0) pl.id = one_round_if_it_pays(pl.id, M, N, K);
     pl.id = long_k_if_it_pays(chained_if_it_pays(pl.id, pl.rows1, N, K), c_is_f16, pl.rows1, N, K);
     const Operands operands = operands_of(lda, ldb);
     pl.id = deep_ring_if_it_pays(pl.id, c_is_f16, pl.rows1, N, K, operands);
