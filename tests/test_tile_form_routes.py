@@ -22,3 +22,11 @@ def test_one_round_of_128x256_in_place_of_shared_128x128(f16):
     assert name(f16, 4096, 2048, 1536) == wide                                              # 512 and 256
     assert name(f16, 4096, 2056, 1536) != wide                                              # 288 of 128 x 256
     assert name(f16, 2304, 1800, 2048) == wide and name(f16, 2048, 1920, 1280) != wide      # 270 of 128 x 128, and 240
+
+
+@pytest.mark.parametrize("f16", [0, 1])
+def test_two_short_rounds_of_128x128_in_place_of_192x256(f16):
+    tall = "pp192x256x64_w2x4_mi16"
+    assert name(f16, 4224, 4352, 400) == P                                                  # 33 x 34 = 1122 tiles of 128 x 128, two rounds are 1024, 2.2 are 1126
+    assert name(f16, 4224, 4352, 408) == tall
+    assert name(f16, 4224, 4480, 256) == tall                                               # 1155
