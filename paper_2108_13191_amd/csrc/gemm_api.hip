@@ -357,12 +357,20 @@ int one_round_if_it_pays(int id, int64_t M, int64_t N, int64_t K)
 // Short k loops on a little more than two rounds of 128 x 128 tiles, two a compute unit: those in place of one and a half rounds of 192 x 256 ones, which launch_cost
 // takes as equal; the traffic of C bounds such problems and the smaller tiles spread it.  192 x 256 -> 128 x 128 on 43 random problems, K = 48 to 400, f32 and f16, share of the time on
 // three sets | one set | from memory 0.93 | 0.93 | 0.94 on average: (1950,8856,288) f32 38.8 -> 34.6 us, (5093,3232,112) f16 25.2 -> 21.9, (8642,1944,64) f32 0.98 | 0.98 | 1.00; the worst (6548,2512,256) f32 1.02 | 1.03 | 0.92.
-// Beyond 2.2 rounds or K = 400 it depends: (4040,4472,448) f32 1.18 | 1.05 | 0.98, (7644,2752,280) f16, 2.6 rounds, 1.00 | 1.00 | 1.09, (12705,1648,48) f32, 2.5, 1.10 | 0.97 | 0.94.
+// Beyond K = 400 it depends: (4040,4472,448) f32 1.18 | 1.05 | 0.98.  At 2.2 to 2.5 rounds, K = 48 to 300, 40 problems 0.94 | 0.94 | 0.98, worst (8740,2064,64) f32 1.07 | 1.07 | 1.11;
+// longer loops and more rounds there depend: (7644,2752,280) f16, 2.6 rounds, 1.00 | 1.00 | 1.09, (12705,1648,48) f32, 2.5, 1.10 | 0.97 | 0.94, (4113,5288,408) f16, 2.7, 1.05.
 int two_short_rounds_if_it_pays(int id, int64_t M, int64_t N, int64_t K)
 {
     if (id != ID_PP192 || K > 400) return id;
     const int64_t tiles = config(ID_PP128x128)->grid(M, N), round = 2 * chip().cus;
-    return tiles > 2 * round && 5 * tiles <= 11 * round ? ID_PP128x128 : id;
+    return tiles > 2 * round && (K <= 304 ? 2 * tiles <= 5 * round : 5 * tiles <= 11 * round) ? ID_PP128x128 : id;
+}
+// ... and in place of two launches, up to 3.3 rounds: 40 random problems, K = 48 to 312, 0.91 | 0.89 | 0.93, none slower: (3138,6272,272) f32 40.2 -> 33.8, (1373,13664,192) f16 29.1 -> 23.6,
+// (15859,1616,128) f32 0.94 | 0.90 | 0.94.  From K = 450 on one is as fast as the other: (10655,2544,512) f16 1.01, (9802,2800,592) f32 0.99.
+bool one_short_launch_pays(int64_t M, int64_t N, int64_t K)
+{
+    const int64_t tiles = config(ID_PP128x128)->grid(M, N), round = 2 * chip().cus;
+    return K <= 330 && tiles > 2 * round && 10 * tiles <= 33 * round;
 }
 
 // Long k loops take the four-wavefront kernel, and so do f32 problems of at most one 256 x 256
@@ -621,6 +629,7 @@ Plan select_large_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void
 {
     Plan pl = select_plan_unchained(c_is_f16, M, N, K, A, lda, B, ldb, ldc);
     if ((g_forced >= 0 && g_forced < num_configs()) || pl.id == ID_GENERIC) return pl;        // a forced configuration runs as it is
+    if (pl.id2 >= 0 && one_short_launch_pays(M, N, K)) pl = {ID_PP128x128, M, -1};
     if (pl.id2 < 0) pl.id = two_short_rounds_if_it_pays(one_round_if_it_pays(pl.id, M, N, K), M, N, K);
     pl.id = long_k_if_it_pays(chained_if_it_pays(pl.id, pl.rows1, N, K), c_is_f16, pl.rows1, N, K);
     const Operands operands = operands_of(lda, ldb);

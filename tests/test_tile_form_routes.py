@@ -29,4 +29,13 @@ def test_two_short_rounds_of_128x128_in_place_of_192x256(f16):
     tall = "pp192x256x64_w2x4_mi16"
     assert name(f16, 4224, 4352, 400) == P                                                  # 33 x 34 = 1122 tiles of 128 x 128, two rounds are 1024, 2.2 are 1126
     assert name(f16, 4224, 4352, 408) == tall
-    assert name(f16, 4224, 4480, 256) == tall                                               # 1155
+    assert name(f16, 4224, 4480, 304) == P and name(f16, 4224, 4480, 312) == tall           # 1155
+
+
+def test_one_short_launch_in_place_of_two():
+    def q(M, N, K):
+        return binding.query_config(0, M, N, K, 256, K, 256, N, 256, N)
+    for M, N in ((15859, 1616), (7200, 3632), (4962, 5312)):                                # 1612, 1653 and 1638 tiles: up to 3.3 rounds
+        assert q(M, N, 328)["name"] == P and q(M, N, 328)["split_rows"] == 0
+        assert q(M, N, 336)["split_rows"] > 0
+    assert q(8700, 3632, 328)["name"] != P                                                  # 1972
