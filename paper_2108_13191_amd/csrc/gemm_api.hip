@@ -346,11 +346,13 @@ int chained_if_it_pays(int id, int64_t rows, int64_t N, int64_t K)
 // us, three sets of operands (and share of the time on three sets | one set | from memory, 70 problems below K = 2900, from where launch_cost takes them by itself: 0.82 to
 // 0.98 from K = 1200 on, 0.86 | 0.86 | 0.92 from K = 1600 on): (4472,1016,2904) f32 54.1 -> 42.1, (2560,2560,2560) f32 41.8 -> 40.6, f16 41.5 -> 38.8, (5353,1256,1152) f16 at a pitch of 8 more 26.5 -> 23.2,
 // (2363,2144,1896) f16 0.86 | 0.85 | 0.92, (2387,1712,1112) f16 0.96 | 0.96 | 0.97, (3407,1656,1536) f32 0.95 | 0.95 | 1.01; the worst is (5409,1104,1144) f16 1.04 in all uses.
-// Below it depends: K = 850 to 1060 0.95 to 1.01, but (2353,2048,824) f16 1.07 | 1.11 | 1.08, (684,5600,960) f16 1.04 | 1.08 | 1.03; K = 500 to 700 on average 1.03.
+// From 15 on where there are 300 tiles and more: 12 problems 0.92 to 1.01, on average 0.95 ((6594,920,1064) f16 25.3 -> 23.5, (2050,2736,1008) f32 0.94); fewer: (684,5600,960) f16 1.04 | 1.08 | 1.03.
+// Below it depends: K = 700 to 900 0.93 to 1.01, but (2353,2048,824) f16 1.07 | 1.11 | 1.08; K = 500 to 700 on average 1.03.
 int one_round_if_it_pays(int id, int64_t M, int64_t N, int64_t K)
 {
-    if (id != ID_PP128x128 || K < 17 * BK_STEP) return id;
+    if (id != ID_PP128x128) return id;
     const int64_t tiles = config(ID_PP128x128)->grid(M, N), cus = chip().cus;
+    if (K < (6 * tiles > 7 * cus ? 15 : 17) * BK_STEP) return id;
     return tiles > cus && tiles <= 2 * cus && config(ID_PP128)->grid(M, N) <= cus ? ID_PP128 : id;
 }
 

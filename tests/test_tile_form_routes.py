@@ -18,7 +18,8 @@ def name(f16, M, N, K):
 @pytest.mark.parametrize("f16", [0, 1])
 def test_one_round_of_128x256_in_place_of_shared_128x128(f16):
     wide = "pp128x256x64_w2x4_mi16"
-    assert name(f16, 2560, 2560, 1088) == wide and name(f16, 2560, 2560, 1080) == P          # 400 tiles, 200; 17 k steps
+    assert name(f16, 2560, 2560, 960) == wide and name(f16, 2560, 2560, 952) == P            # 400 tiles, 200; 15 k steps
+    assert name(f16, 2048, 2176, 1088) == wide and name(f16, 2048, 2176, 1080) == P          # 272, 144; 17
     assert name(f16, 4096, 2048, 1536) == wide                                              # 512 and 256
     assert name(f16, 4096, 2056, 1536) != wide                                              # 288 of 128 x 256
     assert name(f16, 2304, 1800, 2048) == wide and name(f16, 2048, 1920, 1280) != wide      # 270 of 128 x 128, and 240
