@@ -431,21 +431,28 @@ int long_k_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K)
 // three or more (17 problems) 0.77 to 1.02 and 0.92 to 1.03, on average 0.93 and 0.98: (428,6848,5248) 52.0 -> 40.1 | 51.7 -> 47.6, (9536,320,5888) 0.92 | 0.94, (336,10752,5376) 1.00 | 1.00.
 // Beyond K = 2048 the five-stage kernel is up to 3 % faster still, but tests/test_gpu_long_k.py states that 2048^2 at K = 4096 runs on a kernel of the phase-alternating family.
 // Below 28 k steps 55 MB are the line: (134,15744,1536) 19.9 -> 21.3 | 21.3 -> 24.5, (190,14784,1472) 19.1 -> 21.4 | 21.1 -> 22.2, (256,16000,1664) 22.4 -> 21.5 | 24.3 -> 25.5; at 44 to 55 MB still 6 % the other way round in turn.
-bool two_groups_fit(int64_t rows, int64_t N, int64_t K)
+//
+// The f16 mode takes two groups from 13 k steps to where the five-stage kernel begins, under the same limits on the matrices' size.  150 random problems of 129 to 256 tiles, rows at lines, phase-alternating kernel -> two
+// groups, share of the time on three sets | from memory, averages: K = 832 to 1088 0.91 | 1.01, to 1536 0.87 | 1.00, to 1984 0.86 | 0.99, with a k tail K = 900 to 1500 0.92 | 1.01, 2000 to 3500 0.85 | 1.00, with bias and ReLU 0.88 | 0.97:
+// (437,4864,1408) 16.5 -> 13.8 us (from memory 1.01), (609,4864,1984) 21.0 -> 17.7 (1.01), (376,5520,3472) 32.9 -> 26.3 (1.01), (275,7104,1536) 17.7 -> 14.5 (0.93); the worst (2763,1096,1032) 0.94 | 1.03, (2710,1408,960) 0.97 | 1.02.  120
+// more, three sets | one set | from memory 0.90 | 0.89 | 0.99, worst (15630,160,1440) with bias and ReLU 1.09 | 1.06 | 1.02.  K = 512 to 704 0.95 | 1.03, 320 1.05 | 1.09.  The five-stage kernel is as fast there without a tail and a fused epilogue, 3 % slower with them.
+bool two_groups_fit(int c_is_f16, int64_t rows, int64_t N, int64_t K)
 {
-    const double mb = operand_mb(rows, N, K) + 4e-6 * (double)rows * (double)N;
+    const double mb = operand_mb(rows, N, K) + (c_is_f16 ? 2e-6 : 4e-6) * (double)rows * (double)N;
     if (K < 28 * BK_STEP) return mb <= 55.0;
     return mb <= 86.0 || (rows > 256 && N > 256);
 }
-int deep_ring_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K, Operands operands)
+// second: the second of two launches
+int deep_ring_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K, Operands operands, bool second)
 {
     const int64_t tiles = config(ID_RING128)->grid(rows, N), cus = chip().cus;
     if (id != ID_PP128x128 || tiles > cus) return id;
     if (operands != Operands::lines) return K >= 6144 ? ID_RING128 : id;
     const int64_t tail = K % 64 ? 1536 : 0;
     if (2 * tiles <= cus) return K >= (c_is_f16 ? 1024 : 1536) + tail ? ID_RING128 : id;
-    if (!c_is_f16) return K >= 6144 ? ID_RING128 : K >= 1472 && two_groups_fit(rows, N, K) ? ID_PP128_K2 : id;
-    return K >= 2048 + tail ? ID_RING128 : id;
+    if (!c_is_f16) return K >= 6144 ? ID_RING128 : K >= 1472 && two_groups_fit(0, rows, N, K) ? ID_PP128_K2 : id;
+    if (K >= 2048 + tail) return ID_RING128;
+    return !second && K >= 13 * BK_STEP && two_groups_fit(1, rows, N, K) ? ID_PP128_K2 : id;
 }
 
 Plan select_plan_unchained(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, int64_t ldc)
@@ -490,8 +497,9 @@ enum class Form { plain, fused, workspace };
 // launches in a row, us: phase-alternating kernel (1024,2048,K) 14.3 / 22.4 at K = 1024 / 2048; five-stage
 // kernel 13.1 / 27.8 at 1024 / 4096; its split form (512,512,4096) 14.4, (1024,1024,4096) 26.3 (four million additions).  The split form's
 // figures were fitted before its parts were dealt to the XCDs as they are now (parts_apart): on 243 problems they are 7 % high on average, scatter 17 %.  2.8 us per million
-// additions stand for all that grows with M x N x parts, the additions alone take half of that.  The kernel of two k groups counts as the phase-alternating one.
-double other_us(const Plan& pl, int64_t M, int64_t N, int64_t K)
+// additions stand for all that grows with M x N x parts, the additions alone take half of that.  The kernel of two k groups counts as the phase-alternating one in the f32 mode; f16 11.4 at
+// K = 960, 13.8 at 1408, 17.7 at 1984 ((283,5824,1856) 15.9, on 64 x 64 tiles 19.3).
+double other_us(const Plan& pl, int c_is_f16, int64_t M, int64_t N, int64_t K)
 {
     const double k = (double)K / 1024.0, mb = operand_mb(M, N, K), memory = mb > 80.0 ? 0.08 * mb : 0.0;
     if (pl.k_split > 1) {
@@ -500,6 +508,7 @@ double other_us(const Plan& pl, int64_t M, int64_t N, int64_t K)
         return 5.0 + 0.38 * (double)per_part + 2.8 * adds + (adds > 2.7 ? 1.9 * (adds - 2.7) : 0.0) + memory;
     }
     if (pl.id == ID_RING128) return 8.2 + 4.9 * k + (K % 64 ? 2.5 : 0.0) + memory;
+    if (pl.id == ID_PP128_K2 && c_is_f16) return 5.6 + 6.1 * k + memory;
     return 6.2 + 7.8 * k + memory;
 }
 
@@ -567,7 +576,7 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
     const bool wide = N > 4 * M, tall = M > 4 * N;
     bool lifted = false;                                             // f16, limited by the count of 64 x 64 tiles unless more pay
     int64_t max_grid = INT32_MAX;
-    double other = other_us(pl, M, N, K);
+    double other = other_us(pl, c_is_f16, M, N, K);
     if (form == Form::plain && K >= 2048) {
         if (pl.k_split > 1) {
             if (wide && M >= 16 && M < 128) return -1;
@@ -635,9 +644,9 @@ Plan select_large_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void
     if (pl.id2 < 0) pl.id = two_short_rounds_if_it_pays(one_round_if_it_pays(pl.id, M, N, K), M, N, K);
     pl.id = long_k_if_it_pays(chained_if_it_pays(pl.id, pl.rows1, N, K), c_is_f16, pl.rows1, N, K);
     const Operands operands = operands_of(lda, ldb);
-    pl.id = deep_ring_if_it_pays(pl.id, c_is_f16, pl.rows1, N, K, operands);
+    pl.id = deep_ring_if_it_pays(pl.id, c_is_f16, pl.rows1, N, K, operands, false);
     if (pl.id2 >= 0) pl.id2 = long_k_if_it_pays(chained_if_it_pays(pl.id2, M - pl.rows1, N, K), c_is_f16, M - pl.rows1, N, K);
-    if (pl.id2 >= 0) pl.id2 = deep_ring_if_it_pays(pl.id2, c_is_f16, M - pl.rows1, N, K, operands);
+    if (pl.id2 >= 0) pl.id2 = deep_ring_if_it_pays(pl.id2, c_is_f16, M - pl.rows1, N, K, operands, true);
     if (pl.id2 >= 0 || pl.rows1 != M) return pl;
     if (form == Form::workspace) {
         // the rule of the f32 mode; the two passes over the workspace: (1024,2048,8192), 8 MB, 56 us against 53 unsplit; (256,4096,16384), 4 MB, 52 against 97
@@ -650,7 +659,7 @@ Plan select_large_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void
         // than they save k steps: (1024,2048,4096) 33.4 us in two parts, 28.5 whole, (1024,2048,2048) 24.9 and 18.0,
         // but (1280,1024,2048) 17.8 and 18.0; not
         // at pitches of other than whole lines: (1016,1920,3648) at 8 more 33.6 in two parts, 36.2 whole (from memory 40.9 and 52.4)
-        if (form == Form::fused || (pl.k_split > 1 && operands == Operands::lines && other_us({ID_RING128, M, -1}, M, N, K) < 0.9 * other_us(pl, M, N, K))) pl.k_split = 0;
+        if (form == Form::fused || (pl.k_split > 1 && operands == Operands::lines && other_us({ID_RING128, M, -1}, c_is_f16, M, N, K) < 0.9 * other_us(pl, c_is_f16, M, N, K))) pl.k_split = 0;
     }
     return pl;
 }

@@ -15,9 +15,7 @@
 // 2048^3 f32 25.1 -> 22.7 us when it was written, 24.2 -> 21.7 and 26.6 -> 23.4 in other sessions on other cards; C requested earlier, stored by whole rows and
 // one barrier less 23.7 -> 23.0, (2048,2048,4096) 37.5 -> 36.2, (2048,2048,1536) 20.2 -> 19.6, (1152,2432,2048) 19.4 -> 19.0.
 //
-// Automatic selection gives it f32 problems only (deep_ring_if_it_pays in gemm_api.hip).  f16 C, when forced, us, the kernel selected -> this one, three sets | from
-// memory: from K = 2048 on the five-stage kernel is ahead, (2048,2048,2048) 19.3 -> 20.0 | 24.1 -> 24.9, (4022,896,4096) 30.1 -> 30.7 | 42.0 -> 42.5; below, the phase-alternating
-// one is behind in turn and ahead from memory, (2048,2048,1536) 18.2 -> 16.5 | 20.4 -> 21.1, (1152,2432,1024) 13.8 -> 12.7 | 15.3 -> 15.8; no rule uses that.
+// Automatic selection gives it f32 problems from K = 1472 to 6143 and f16 ones from 832 to where the five-stage kernel begins (deep_ring_if_it_pays in gemm_api.hip has both sides).
 #include "gemm_device.h"
 #include "../../include/gemm_f16.h"
 #include <type_traits>

@@ -40,3 +40,13 @@ def test_one_short_launch_in_place_of_two():
         assert q(M, N, 328)["name"] == P and q(M, N, 328)["split_rows"] == 0
         assert q(M, N, 336)["split_rows"] > 0
     assert q(8700, 3632, 328)["name"] != P                                                  # 1972
+
+
+def test_two_k_groups_in_the_f16_mode():
+    two = "pp128x128x64_w2x2_k2"
+    assert name(1, 2048, 1280, 832) == two and name(1, 2048, 1280, 768) == P                # 160 tiles; 13 k steps
+    assert name(1, 2048, 1280, 1984) == two and name(1, 2048, 1280, 2048) == "w4a_128x128x64"
+    assert binding.query_config(1, 2048, 1280, 3000, 256, 3008, 256, 1280, 256, 1280)["name"] == two        # a k tail
+    assert binding.query_config(1, 2048, 1280, 1024, 256, 1032, 256, 1280, 256, 1280)["name"] == P          # rows that begin within a line
+    assert name(1, 256, 16384, 1280) == two and name(1, 256, 16384, 1408) == P              # 55 MB
+    assert name(1, 2048, 1024, 960) != two                                                  # half a chip of tiles
