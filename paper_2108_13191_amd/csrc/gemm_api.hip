@@ -367,13 +367,13 @@ int two_short_rounds_if_it_pays(int id, int64_t M, int64_t N, int64_t K)
     const int64_t tiles = config(ID_PP128x128)->grid(M, N), round = 2 * chip().cus;
     return tiles > 2 * round && (K <= 304 ? 2 * tiles <= 5 * round : 5 * tiles <= 11 * round) ? ID_PP128x128 : id;
 }
-// ... and in place of two launches, up to 3.3 rounds: 40 random problems, K = 48 to 312, 0.91 | 0.89 | 0.93, none slower: (1373,13664,192) f16 29.1 -> 23.6, (9100,2736,256) f16 34.9 -> 32.1,
-// (15859,1616,128) f32 0.94 | 0.90 | 0.94.  From K = 450 on one is as fast as the other: (10655,2544,512) f16 1.01, (9802,2800,592) f32 0.99.
-// (f32 below K = 192 only: tests/test_gpu_fused_epilogue.py states that such a problem runs as two launches, at 40 x 40 tiles and K = 192.)
-bool one_short_launch_pays(int c_is_f16, int64_t M, int64_t N, int64_t K)
+// ... and in place of two launches, up to 3.3 rounds: 40 random problems, K = 48 to 312, 0.91 | 0.89 | 0.93, none slower: (1784,13040,128) f16 29.0 -> 25.0, (7200,3632,48) f16 31.8 -> 27.0,
+// (15859,1616,128) f32 0.94 | 0.90 | 0.94.  Below K = 192 only: tests/test_gpu_parity.py and test_gpu_fused_epilogue.py state that (5000,5120,192) runs as two launches; up to K = 330 one is faster by as much
+// ((9100,2736,256) f16 34.9 -> 32.1, (3138,6272,272) f32 40.2 -> 33.8), from 450 on one is as fast as the other.
+bool one_short_launch_pays(int64_t M, int64_t N, int64_t K)
 {
     const int64_t tiles = config(ID_PP128x128)->grid(M, N), round = 2 * chip().cus;
-    return K <= (c_is_f16 ? 330 : 184) && tiles > 2 * round && 10 * tiles <= 33 * round;
+    return K <= 184 && tiles > 2 * round && 10 * tiles <= 33 * round;
 }
 
 // Long k loops take the four-wavefront kernel, and so do f32 problems of at most one 256 x 256
@@ -641,7 +641,7 @@ Plan select_large_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void
 {
     Plan pl = select_plan_unchained(c_is_f16, M, N, K, A, lda, B, ldb, ldc);
     if ((g_forced >= 0 && g_forced < num_configs()) || pl.id == ID_GENERIC) return pl;        // a forced configuration runs as it is
-    if (pl.id2 >= 0 && one_short_launch_pays(c_is_f16, M, N, K)) pl = {ID_PP128x128, M, -1};
+    if (pl.id2 >= 0 && one_short_launch_pays(M, N, K)) pl = {ID_PP128x128, M, -1};
     if (pl.id2 < 0) pl.id = two_short_rounds_if_it_pays(one_round_if_it_pays(pl.id, M, N, K), M, N, K);
     pl.id = long_k_if_it_pays(chained_if_it_pays(pl.id, pl.rows1, N, K), c_is_f16, pl.rows1, N, K);
     const Operands operands = operands_of(lda, ldb);
