@@ -437,6 +437,8 @@ int long_k_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K)
 // groups, share of the time on three sets | from memory, averages: K = 832 to 1088 0.91 | 1.01, to 1536 0.87 | 1.00, to 1984 0.86 | 0.99, with a k tail K = 900 to 1500 0.92 | 1.01, 2000 to 3500 0.85 | 1.00, with bias and ReLU 0.88 | 0.97:
 // (437,4864,1408) 16.5 -> 13.8 us (from memory 1.01), (609,4864,1984) 21.0 -> 17.7 (1.01), (376,5520,3472) 32.9 -> 26.3 (1.01), (275,7104,1536) 17.7 -> 14.5 (0.93); the worst (2763,1096,1032) 0.94 | 1.03, (2710,1408,960) 0.97 | 1.02.  120
 // more, three sets | one set | from memory 0.90 | 0.89 | 0.99, worst (15630,160,1440) with bias and ReLU 1.09 | 1.06 | 1.02.  K = 512 to 704 0.95 | 1.03, 320 1.05 | 1.09.  The five-stage kernel is as fast there without a tail and a fused epilogue, 3 % slower with them.
+// On a quarter to half a chip of tiles from 11 k steps to the five-stage kernel, 25 with a k tail: 60 random problems 0.90 | 1.00, none slower in turn: (837,1216,704) with bias and ReLU 11.3 -> 10.1 us (from
+// memory 0.95), (433,3840,960) 12.9 -> 11.5 (1.02), (3733,376,1208) 16.6 -> 15.2 (1.04); longer ones with a tail run on small tiles, 0.91 in turn and 1.03 to 1.22 from memory ((2024,632,2296) 0.98 | 1.22).
 bool two_groups_fit(int c_is_f16, int64_t rows, int64_t N, int64_t K)
 {
     const double mb = operand_mb(rows, N, K) + (c_is_f16 ? 2e-6 : 4e-6) * (double)rows * (double)N;
@@ -450,7 +452,10 @@ int deep_ring_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t 
     if (id != ID_PP128x128 || tiles > cus) return id;
     if (operands != Operands::lines) return K >= 6144 ? ID_RING128 : id;
     const int64_t tail = K % 64 ? 1536 : 0;
-    if (2 * tiles <= cus) return K >= (c_is_f16 ? 1024 : 1536) + tail ? ID_RING128 : id;
+    if (2 * tiles <= cus) {
+        if (K >= (c_is_f16 ? 1024 : 1536) + tail) return ID_RING128;
+        return c_is_f16 && !second && 4 * tiles >= cus && K >= 11 * BK_STEP && K < 26 * BK_STEP && two_groups_fit(1, rows, N, K) ? ID_PP128_K2 : id;
+    }
     if (!c_is_f16) return K >= 6144 ? ID_RING128 : K >= 1472 && two_groups_fit(0, rows, N, K) ? ID_PP128_K2 : id;
     if (K >= 2048 + tail) return ID_RING128;
     return !second && K >= 13 * BK_STEP && two_groups_fit(1, rows, N, K) ? ID_PP128_K2 : id;

@@ -51,4 +51,6 @@ def test_two_k_groups_in_the_f16_mode():
     assert binding.query_config(1, 2048, 1280, 3000, 256, 3008, 256, 1280, 256, 1280)["name"] == two        # a k tail
     assert binding.query_config(1, 2048, 1280, 1024, 256, 1032, 256, 1280, 256, 1280)["name"] == P          # rows that begin within a line
     assert name(1, 256, 16384, 1280) == two and name(1, 256, 16384, 1408) == P              # 55 MB
-    assert name(1, 2048, 1024, 960) != two                                                  # half a chip of tiles
+    assert name(1, 2048, 1024, 960) == two and name(1, 2048, 1024, 640) == P                # half a chip of tiles: 11 k steps
+    assert name(1, 2048, 1024, 1024) == "w4a_128x128x64"
+    assert name(1, 1024, 896, 960) != two                                                   # 56 tiles
