@@ -594,6 +594,9 @@ int kslice_if_it_pays(const Plan& pl, int c_is_f16, Form form, int64_t M, int64_
     }
     double us = 0, more_us = 0;
     int small = best_kslice(c_is_f16, operands, M, N, K, max_grid, &us);
+    // Tiles of 32 x 64 on about two workgroups a compute unit are 3 % faster than their estimate: they keep the problems that they had from the phase-alternating kernel.  Two k groups -> 32 x 64, 108 problems of
+    // 64 to 128 tiles, K = 832 to 1016, three sets | one set | from memory 0.97 | 0.97 | 0.92: (195,4160,896) 10.4 -> 9.9 us | 10.0 -> 9.6 | 13.2 -> 11.6, (81,9152,960) 10.8 -> 10.3 | 10.5 -> 10.0 | 13.8 -> 12.4; the worst (286,3584,960) with bias and ReLU 1.09 | 1.15 | 0.92.
+    if (c_is_f16 && pl.id == ID_PP128_K2 && small == 3 && 2 * tiles <= chip().cus) other = other_us({ID_PP128x128, M, -1}, c_is_f16, M, N, K);
     if (lifted) {
         const int64_t cus = chip().cus;
         const int more = best_kslice(c_is_f16, operands, M, N, K, INT32_MAX, &more_us, tall && K < 3600 ? 7 * cus / 2 : 2 * cus);

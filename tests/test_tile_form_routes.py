@@ -54,3 +54,9 @@ def test_two_k_groups_in_the_f16_mode():
     assert name(1, 2048, 1024, 960) == two and name(1, 2048, 1024, 640) == P                # half a chip of tiles: 11 k steps
     assert name(1, 2048, 1024, 1024) == "w4a_128x128x64"
     assert name(1, 1024, 896, 960) != two                                                   # 56 tiles
+
+
+def test_small_tiles_keep_their_problems_from_two_k_groups():
+    """f16, 66 to 77 tiles of 128 x 128: 32 x 64 tiles, which had them and are faster there in every use."""
+    for M, N, K in ((195, 4160, 896), (81, 9152, 960), (86, 9408, 960), (88, 9088, 896)):
+        assert name(1, M, N, K) == "ks32x64x64_k8"
