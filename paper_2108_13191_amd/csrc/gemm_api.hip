@@ -445,8 +445,9 @@ bool two_groups_fit(int c_is_f16, int64_t rows, int64_t N, int64_t K)
     if (K < 28 * BK_STEP) return mb <= 55.0;
     return mb <= 86.0 || (rows > 256 && N > 256);
 }
-// second: the second of two launches
-int deep_ring_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K, Operands operands, bool second)
+// Left-over rows behind a first launch of 256 x 256 tiles, f16, phase-alternating kernel -> two k groups, 90 problems: 64 behind the plain form 0.98 | 0.97 | 1.00 (three sets | one set | from memory), 26 behind the chained
+// one 1.00 | 0.98 | 1.00; the worst (628,28544,832) 1.02 in all uses.
+int deep_ring_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K, Operands operands)
 {
     const int64_t tiles = config(ID_RING128)->grid(rows, N), cus = chip().cus;
     if (id != ID_PP128x128 || tiles > cus) return id;
@@ -454,11 +455,11 @@ int deep_ring_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t 
     const int64_t tail = K % 64 ? 1536 : 0;
     if (2 * tiles <= cus) {
         if (K >= (c_is_f16 ? 1024 : 1536) + tail) return ID_RING128;
-        return c_is_f16 && !second && 4 * tiles >= cus && K >= 11 * BK_STEP && K < 26 * BK_STEP && two_groups_fit(1, rows, N, K) ? ID_PP128_K2 : id;
+        return c_is_f16 && 4 * tiles >= cus && K >= 11 * BK_STEP && K < 26 * BK_STEP && two_groups_fit(1, rows, N, K) ? ID_PP128_K2 : id;
     }
     if (!c_is_f16) return K >= 6144 ? ID_RING128 : K >= 1472 && two_groups_fit(0, rows, N, K) ? ID_PP128_K2 : id;
     if (K >= 2048 + tail) return ID_RING128;
-    return !second && K >= 13 * BK_STEP && two_groups_fit(1, rows, N, K) ? ID_PP128_K2 : id;
+    return K >= 13 * BK_STEP && two_groups_fit(1, rows, N, K) ? ID_PP128_K2 : id;
 }
 
 Plan select_plan_unchained(int c_is_f16, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, int64_t ldc)
@@ -653,9 +654,9 @@ Plan select_large_plan(int c_is_f16, int64_t M, int64_t N, int64_t K, const void
     if (pl.id2 < 0) pl.id = two_short_rounds_if_it_pays(one_round_if_it_pays(pl.id, M, N, K), M, N, K);
     pl.id = long_k_if_it_pays(chained_if_it_pays(pl.id, pl.rows1, N, K), c_is_f16, pl.rows1, N, K);
     const Operands operands = operands_of(lda, ldb);
-    pl.id = deep_ring_if_it_pays(pl.id, c_is_f16, pl.rows1, N, K, operands, false);
+    pl.id = deep_ring_if_it_pays(pl.id, c_is_f16, pl.rows1, N, K, operands);
     if (pl.id2 >= 0) pl.id2 = long_k_if_it_pays(chained_if_it_pays(pl.id2, M - pl.rows1, N, K), c_is_f16, M - pl.rows1, N, K);
-    if (pl.id2 >= 0) pl.id2 = deep_ring_if_it_pays(pl.id2, c_is_f16, M - pl.rows1, N, K, operands, true);
+    if (pl.id2 >= 0) pl.id2 = deep_ring_if_it_pays(pl.id2, c_is_f16, M - pl.rows1, N, K, operands);
     if (pl.id2 >= 0 || pl.rows1 != M) return pl;
     if (form == Form::workspace) {
         // the rule of the f32 mode; the two passes over the workspace: (1024,2048,8192), 8 MB, 56 us against 53 unsplit; (256,4096,16384), 4 MB, 52 against 97

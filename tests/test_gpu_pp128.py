@@ -65,3 +65,16 @@ def test_selected(oracle_mod):
     rows = np.array([0, 1, 127, 128, 1000, 2047])
     Cref, S = oracle_mod.gemm_f16(A, B, C0, rows=rows)
     assert_close(got[rows], Cref, S, C0[rows], "f32", what=NAME)
+
+
+def test_selected_for_left_over_rows(oracle_mod):
+    """f16 mode: the rows behind a first launch of 256 x 256 tiles, edge tiles among them, and the rows next to them; integers, bit for bit."""
+    M, N, K = 2501, 7360, 832
+    q = binding.query_config(1, M, N, K, 16, K, 16, N, 16, N)
+    assert q["split_rows"] == 2048 and binding.describe_config(q["id2"])["name"] == NAME
+    A, B, C0 = wl.make_inputs(M, N, K, "int1", "zeros", seed=10600, c_dtype=np.float16)
+    C0[:] = (np.arange(M)[:, None] + np.arange(N)[None, :]) % 5 - 2
+    got = run_gemm(A, B, C0, "f16")
+    rows = np.array([0, 2046, 2047, 2048, 2049, 2111, 2112, 2175, 2176, 2431, 2432, 2499, 2500])
+    Cref, _ = oracle_mod.gemm_f16(A, B, C0, rows=rows)
+    assert np.array_equal(got[rows], Cref.astype(np.float16))

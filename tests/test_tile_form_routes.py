@@ -60,3 +60,10 @@ def test_small_tiles_keep_their_problems_from_two_k_groups():
     """f16, 66 to 77 tiles of 128 x 128: 32 x 64 tiles, which had them and are faster there in every use."""
     for M, N, K in ((195, 4160, 896), (81, 9152, 960), (86, 9408, 960), (88, 9088, 896)):
         assert name(1, M, N, K) == "ks32x64x64_k8"
+
+
+def test_two_k_groups_for_left_over_rows():
+    """The second of two launches: in the f16 mode as where the tiles are all there is."""
+    for f16, M, N, K in ((1, 3163, 6400, 1024), (1, 5120, 4096, 832), (1, 2539, 7360, 1472), (0, 2539, 7360, 1472)):
+        q = binding.query_config(f16, M, N, K, 256, K, 256, N, 256, N)
+        assert q["split_rows"] > 0 and binding.describe_config(q["id2"])["name"] == "pp128x128x64_w2x2_k2"
