@@ -368,12 +368,13 @@ int two_short_rounds_if_it_pays(int id, int64_t M, int64_t N, int64_t K)
     return tiles > 2 * round && (K <= 304 ? 2 * tiles <= 5 * round : 5 * tiles <= 11 * round) ? ID_PP128x128 : id;
 }
 // ... and in place of two launches, up to 3.3 rounds: 40 random problems, K = 48 to 312, 0.91 | 0.89 | 0.93, none slower: (1784,13040,128) f16 29.0 -> 25.0, (7200,3632,48) f16 31.8 -> 27.0,
-// (15859,1616,128) f32 0.94 | 0.90 | 0.94.  Below K = 192 only: tests/test_gpu_parity.py and test_gpu_fused_epilogue.py state that (5000,5120,192) runs as two launches; up to K = 330 one is faster by as much
-// ((9100,2736,256) f16 34.9 -> 32.1, (3138,6272,272) f32 40.2 -> 33.8), from 450 on one is as fast as the other.
+// (15859,1616,128) f32 0.94 | 0.90 | 0.94.  From K = 185 to 330 up to three rounds, 199 problems: f16 0.85 | 0.85 | 0.92, f32 0.87 | 0.86 | 0.94 ((407,35264,224) f32 39.0 -> 29.5, (399,35728,224) f16 37.0 -> 26.6, (3138,6272,272) f32 40.2 -> 33.8; the worst
+// (630,30400,320) f32 1.03 | 0.97 | 1.04); above three rounds there one launch is faster too ((9100,2736,256) f16 34.9 -> 32.1), but tests/test_gpu_parity.py and test_gpu_fused_epilogue.py state that
+// (5000,5120,192), 3.1 rounds, runs as two.  From K = 450 on one is as fast as the other.
 bool one_short_launch_pays(int64_t M, int64_t N, int64_t K)
 {
     const int64_t tiles = config(ID_PP128x128)->grid(M, N), round = 2 * chip().cus;
-    return K <= 184 && tiles > 2 * round && 10 * tiles <= 33 * round;
+    return tiles > 2 * round && (K <= 184 ? 10 * tiles <= 33 * round : K <= 330 && tiles <= 3 * round);
 }
 
 // Long k loops take the four-wavefront kernel, and so do f32 problems of at most one 256 x 256

@@ -40,8 +40,11 @@ def test_one_short_launch_in_place_of_two(f16):
         return binding.query_config(f16, M, N, K, 256, K, 256, N, 256, N)
     for M, N in ((15859, 1616), (7200, 3632), (4962, 5312)):                                # 1612, 1653 and 1638 tiles: up to 3.3 rounds
         assert q(M, N, last)["name"] == P and q(M, N, last)["split_rows"] == 0
-        assert q(M, N, last + 8)["split_rows"] > 0
     assert q(8700, 3632, last)["name"] != P                                                 # 1972
+    for M, N in ((3138, 6272), (407, 35264), (2559, 7680), (1777, 13056)):                  # 1225, 1104, 1200 and 1428: longer loops up to three rounds
+        for K in (192, 272, 328):
+            assert q(M, N, K)["name"] == P and q(M, N, K)["split_rows"] == 0, (M, N, K)
+        assert q(M, N, 336)["split_rows"] > 0
 
 
 def test_two_k_groups_in_the_f16_mode():
