@@ -9,8 +9,10 @@ libgemm_f16_ladder.so  the same sources compiled with -DGEMM_F16_LADDER plus csr
 from __future__ import annotations
 
 import concurrent.futures
+import contextlib
 import os
 import re
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -20,6 +22,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgemm_f16.so")
 FASTCALL = os.path.join(HERE, "_fastcall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
+FASTCALL_CC = ("gcc", "cc", "amdclang", "clang")         # the first one that is there (hipcc would link the HIP runtime into it)
 LADDER_LIB = os.path.join(HERE, "libgemm_f16_ladder.so")
 SOURCES = ["gemm_api.hip", "gemm_generic.hip", "gemm_unaligned.hip", "gemm_unaligned_pp.hip", "gemm_kslice.hip", "gemm_tiled.hip", "gemm_pingpong.hip", "gemm_pp128.hip", "gemm_w4a.hip", "gemm_w4a128.hip", "gemm_splitk_f16.hip"]
 LADDER_SOURCES = ["ladder/gemm_w4.hip", "ladder/gemm_overlap.hip", "ladder/gemm_interleaved.hip"]
@@ -40,20 +43,32 @@ def _compile(src: str, obj: str, extra, verbose: bool) -> str:
     return res.stdout + res.stderr
 
 
-def build_fastcall() -> None:
-    """The binding works without it (through ctypes, a microsecond a call slower), so a missing Python.h is no error."""
+def build_fastcall() -> bool:
+    """The binding works without it (through ctypes, a microsecond a call slower): what keeps it from being built is
+    printed and is no error, and no older build of it stays behind, whose C signatures could be others."""
+    with contextlib.suppress(FileNotFoundError):
+        os.remove(FASTCALL)
     include = sysconfig.get_paths()["include"]
+    cc = next(filter(None, map(shutil.which, FASTCALL_CC)), None)
     if not os.path.exists(os.path.join(include, "Python.h")):
-        print(f"no Python.h in {include}: the binding will call through ctypes")
-        return
-    subprocess.run(["gcc", "-O2", "-Wall", "-std=c11", "-fPIC", "-shared", "-I" + include, "-o", FASTCALL, os.path.join(CSRC, "fastcall.c")], check=True)
+        why = f"no Python.h in {include}"
+    elif cc is None:
+        why = "no C compiler"
+    else:
+        res = subprocess.run([cc, "-O2", "-Wall", "-std=c11", "-fPIC", "-shared", "-I" + include, "-o", FASTCALL, os.path.join(CSRC, "fastcall.c")],
+                             capture_output=True, text=True)
+        sys.stderr.write(res.stderr)
+        if res.returncode == 0:
+            return True
+        why = f"{cc} failed"
+    print(f"the binding will call through ctypes: {why}")
+    return False
 
 
 def build(verbose: bool = False, ladder: bool = True, extra=()) -> str:
     """Compile every source (in parallel) and link the product library and, with `ladder`,
     the ladder library.  Returns the product library's path."""
     os.makedirs(OBJ, exist_ok=True)
-    build_fastcall()
     jobs = [(s, os.path.join(OBJ, s.replace("/", "_") + ".o"), list(extra)) for s in SOURCES]
     if ladder:
         jobs += [(s, os.path.join(OBJ, s.replace("/", "_") + ".ladder.o"), ["-DGEMM_F16_LADDER", *extra])
@@ -64,6 +79,7 @@ def build(verbose: bool = False, ladder: bool = True, extra=()) -> str:
     subprocess.run([*link, "-o", LIB, *[j[1] for j in jobs[:len(SOURCES)]]], check=True)
     if ladder:
         subprocess.run([*link, "-o", LADDER_LIB, *[j[1] for j in jobs[len(SOURCES):]]], check=True)
+    build_fastcall()
     if verbose:
         print(resource_table("".join(logs[:len(SOURCES)])))
     return LIB
