@@ -129,7 +129,7 @@ bool aligned_for_tiled(int64_t N, int64_t K, const void* A, int64_t lda, const v
 }
 
 // Small results: the kernel whose eight wavefronts take the k steps of one small tile in turn
-// (gemm_kslice.hip).  Estimated microseconds of a launch: 1.6 for the launch itself, and per round of
+// (gemm_kslice.hip).  Estimated microseconds of a launch: 1.6 that do not grow with the rounds (part of the fit; an empty launch in a row takes 2.4), and per round of
 // workgroups a fixed part (first loads, the sums' way through LDS, C) and one per 1024 k; the second
 // pair is a round of two workgroups a compute unit.  Fitted to launches in a row on three sets of operands, us:
 // (256,256,1024) 16x32 4.0, 32x32 4.5, 64x64 7.2; (512,512,1024) 5.9, 4.9, 7.4; (1024,1024,1024) 18.5,
@@ -345,7 +345,9 @@ int chained_if_it_pays(int id, int64_t rows, int64_t N, int64_t K)
 // latter are faster than two workgroups of the former sharing a compute unit, which launch_cost prices as if it were a whole round of one.  128 x 128 -> 128 x 256,
 // us, three sets of operands (and share of the time on three sets | one set | from memory, 70 problems below K = 2900, from where launch_cost takes them by itself: 0.82 to
 // 0.98 from K = 1200 on, 0.86 | 0.86 | 0.92 from K = 1600 on): (4472,1016,2904) f32 54.1 -> 42.1, (2560,2560,2560) f32 41.8 -> 40.6, f16 41.5 -> 38.8, (5353,1256,1152) f16 at a pitch of 8 more 26.5 -> 23.2,
-// (2363,2144,1896) f16 0.86 | 0.85 | 0.92, (2387,1712,1112) f16 0.96 | 0.96 | 0.97, (3407,1656,1536) f32 0.95 | 0.95 | 1.01; the worst is (5409,1104,1144) f16 1.04 in all uses.
+// (2363,2144,1896) f16 0.86 | 0.85 | 0.92, (2387,1712,1112) f16 0.96 | 0.96 | 0.97, (3407,1656,1536) f32 0.95 | 0.95 | 1.01; the worst is (5409,1104,1144) f16 at a pitch of 8 more, 1.04 | 1.04 | 1.05 (with rows behind one another 0.95 | 0.95 | 0.96).
+// 381 problems more: f16 0.93 | 0.93 | 0.92, f32 0.93 | 0.94 | 0.91.  18 of them are slower in every use, up to 8 %, most with rows at lines, three to eight rows or columns of tiles and K below 1280 ((611,6656,1152) f16 1.04 | 1.05 | 1.08, (5470,832,960) f16 at 64 more
+// 1.07 | 1.07 | 1.02).  Lines by these, or by columns of the wider tiles beyond N, were tried on 220 others and lose more: with rows at lines and 128 x 256 tiles that cover a ninth more columns than 128 x 128 ones, 149 problems, the former are 2 % behind in turn and 4 % ahead from memory, with other rows 3 to 6 % ahead in every use.
 // From 15 on where there are 300 tiles and more: 12 problems 0.92 to 1.01, on average 0.95 ((6594,920,1064) f16 25.3 -> 23.5, (2050,2736,1008) f32 0.94); fewer: (684,5600,960) f16 1.04 | 1.08 | 1.03.
 // Below it depends: K = 700 to 900 0.93 to 1.01, but (2353,2048,824) f16 1.07 | 1.11 | 1.08; K = 500 to 700 on average 1.03.
 int one_round_if_it_pays(int id, int64_t M, int64_t N, int64_t K)
@@ -359,7 +361,8 @@ int one_round_if_it_pays(int id, int64_t M, int64_t N, int64_t K)
 // Short k loops on a little more than two rounds of 128 x 128 tiles, two a compute unit: those in place of one and a half rounds of 192 x 256 ones, which launch_cost
 // takes as equal; the traffic of C bounds such problems and the smaller tiles spread it.  192 x 256 -> 128 x 128 on 43 random problems, K = 48 to 400, f32 and f16, share of the time on
 // three sets | one set | from memory 0.93 | 0.93 | 0.94 on average: (1950,8856,288) f32 38.8 -> 34.6 us, (5093,3232,112) f16 25.2 -> 21.9, (8642,1944,64) f32 0.98 | 0.98 | 1.00; the worst (6548,2512,256) f32 1.02 | 1.03 | 0.92.
-// Beyond K = 400 it depends: (4040,4472,448) f32 1.18 | 1.05 | 0.98.  At 2.2 to 2.5 rounds, K = 48 to 300, 40 problems 0.94 | 0.94 | 0.98, worst (8740,2064,64) f32 1.07 | 1.07 | 1.11;
+// Beyond K = 400 it depends: (4040,4472,448) f32 1.18 | 1.05 | 0.98.  At 2.2 to 2.5 rounds, K = 48 to 300, 40 problems 0.94 | 0.94 | 0.98, worst (8740,2064,64) f32 at a pitch of 8 more 1.06 | 1.07 | 1.10
+// (with rows behind one another 1.03 | 1.03 | 0.97).  381 problems more: f16 0.90 | 0.89 | 0.96, f32 0.95 | 0.96 | 0.94; the only kind that does not gain in turn is f32 with K = 56 to 64 above 2.35 rounds, 22 problems 1.00 | 1.01 | 0.97;
 // longer loops and more rounds there depend: (7644,2752,280) f16, 2.6 rounds, 1.00 | 1.00 | 1.09, (12705,1648,48) f32, 2.5, 1.10 | 0.97 | 0.94, (4113,5288,408) f16, 2.7, 1.05.
 int two_short_rounds_if_it_pays(int id, int64_t M, int64_t N, int64_t K)
 {
@@ -437,9 +440,9 @@ int long_k_if_it_pays(int id, int c_is_f16, int64_t rows, int64_t N, int64_t K)
 // The f16 mode takes two groups from 13 k steps to where the five-stage kernel begins, under the same limits on the matrices' size.  150 random problems of 129 to 256 tiles, rows at lines, phase-alternating kernel -> two
 // groups, share of the time on three sets | from memory, averages: K = 832 to 1088 0.91 | 1.01, to 1536 0.87 | 1.00, to 1984 0.86 | 0.99, with a k tail K = 900 to 1500 0.92 | 1.01, 2000 to 3500 0.85 | 1.00, with bias and ReLU 0.88 | 0.97:
 // (437,4864,1408) 16.5 -> 13.8 us (from memory 1.01), (609,4864,1984) 21.0 -> 17.7 (1.01), (376,5520,3472) 32.9 -> 26.3 (1.01), (275,7104,1536) 17.7 -> 14.5 (0.93); the worst (2763,1096,1032) 0.94 | 1.03, (2710,1408,960) 0.97 | 1.02.  120
-// more, three sets | one set | from memory 0.90 | 0.89 | 0.99, worst (15630,160,1440) with bias and ReLU 1.09 | 1.06 | 1.02.  K = 512 to 704 0.95 | 1.03, 320 1.05 | 1.09.  The five-stage kernel is as fast there without a tail and a fused epilogue, 3 % slower with them.
+// more, three sets | one set | from memory 0.90 | 0.89 | 0.99, and 190 more 0.88 | 0.86 | 0.99, the worst of those (10019,384,1536) 1.02 | 1.02 | 1.01 (in another session 0.90 | 0.89 | 1.02); (15630,160,1440) at a pitch of 32 more with bias and ReLU, 1.09 | 1.06 | 1.02 in one session, took 0.97 | 0.99 | 0.99 in another.  K = 512 to 704 0.95 | 1.03, 320 1.05 | 1.09.  The five-stage kernel is as fast there without a tail and a fused epilogue, 3 % slower with them.
 // On a quarter to half a chip of tiles from 11 k steps to the five-stage kernel, 25 with a k tail: 60 random problems 0.90 | 1.00, none slower in turn: (837,1216,704) with bias and ReLU 11.3 -> 10.1 us (from
-// memory 0.95), (433,3840,960) 12.9 -> 11.5 (1.02), (3733,376,1208) 16.6 -> 15.2 (1.04); longer ones with a tail run on small tiles, 0.91 in turn and 1.03 to 1.22 from memory ((2024,632,2296) 0.98 | 1.22).
+// memory 0.95), (433,3840,960) 12.9 -> 11.5 (1.02), (3733,376,1208) 16.6 -> 15.2 (1.04); 184 more 0.89 | 0.86 | 1.00 (three sets | one set | from memory), none slower in turn; longer ones with a tail run on small tiles, 0.91 in turn and 1.03 to 1.22 from memory ((2024,632,2296) 0.98 | 1.22).
 bool two_groups_fit(int c_is_f16, int64_t rows, int64_t N, int64_t K)
 {
     const double mb = operand_mb(rows, N, K) + (c_is_f16 ? 2e-6 : 4e-6) * (double)rows * (double)N;

@@ -13,9 +13,9 @@
 // Outside the loop, start and C take about 8 us: an empty launch of this size 2.4, the stores and the sums' way through LDS 4.5 (17 MB; a kernel that
 // only stores them 1.8 more than an empty one), the first operands; the read of C, requested during the last steps, 1.
 // 2048^3 f32 25.1 -> 22.7 us when it was written, 24.2 -> 21.7 and 26.6 -> 23.4 in other sessions on other cards; C requested earlier, stored by whole rows and
-// one barrier less 23.7 -> 23.0, (2048,2048,4096) 37.5 -> 36.2, (2048,2048,1536) 20.2 -> 19.6, (1152,2432,2048) 19.4 -> 19.0.
+// one barrier less, the three together 23.7 -> 23.0 (the barrier 0.2 of it: put back 22.4 -> 22.6), (2048,2048,4096) 37.5 -> 36.2, (2048,2048,1536) 20.2 -> 19.6, (1152,2432,2048) 19.4 -> 19.0.
 //
-// Automatic selection gives it f32 problems from K = 1472 to 6143 and f16 ones from 832 to where the five-stage kernel begins (deep_ring_if_it_pays in gemm_api.hip has both sides).
+// Automatic selection gives it f32 problems from K = 1472 to 6143 and f16 ones from 832 (on 64 to 128 tiles 704) to where the five-stage kernel begins (deep_ring_if_it_pays in gemm_api.hip has both sides).
 #include "gemm_device.h"
 #include "../../include/gemm_f16.h"
 #include <type_traits>

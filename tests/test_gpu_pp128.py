@@ -1,6 +1,6 @@
 """The 128 x 128 kernel whose two groups of wavefronts take the k steps in turn: its loops left at every exit (0 to 13 whole
 k steps, with and without a k tail), edge tiles beside whole ones, both types of C, a pitch of C that is not N; integers
-bit for bit against the oracle, NaN around A and B; and the problem that automatic selection gives it."""
+bit for bit against the oracle, NaN around A and B; and problems that automatic selection gives it, alone and as the second of two launches."""
 import numpy as np
 import pytest
 
@@ -42,7 +42,7 @@ def test_every_exit_of_the_k_loop(oracle_mod, tail):
 
 @pytest.mark.parametrize("tail", [0, 40])
 def test_loops_that_request_c_among_their_copies(oracle_mod, tail):
-    """14 to 21 whole k steps: the main loop runs, and either group leaves it at either parity."""
+    """14 to 21 whole k steps: the main loop runs, for both groups from 15 on, and either group leaves it at either parity."""
     binding.force_config(config_id(NAME))
     for steps in range(14, 22):
         K = 64 * steps + tail
